@@ -6,21 +6,23 @@
 // Work is split into tiles, one per (request, layer, block, K|V, head); one
 // wave encodes one tile.  A wave's lanes cover a head's row in pieces of 8
 // channels (D/8 lanes per row, 64/(D/8) rows per load), so the tile's
-// min/max is a wave reduction: no LDS and no barrier.  A lane holds its rows
-// in NL 16-byte registers between the range pass and the encode pass.
+// min/max is a wave reduction.  A lane holds its rows in NL 16-byte registers
+// between the range pass and the encode pass.
 //
-// Three kernels.  The tile kernel (blocks whose tile fits NL <= 8 loads per
-// lane and spans at most three cache pages, layer slices below 4 GiB; tiles
-// of 9 to 16 loads go to its two-waves-per-tile form) takes the
-// block's source pages from its work item, so no page-table load sits in
-// front of the row loads; it uses 32-bit buffer offsets, consumes every
-// loaded register on every path, and issues every store (lanes with nothing
-// to write get an offset the hardware drops), which keeps register use low
-// and occupancy high.  The general kernel (any valid model) reads the page
-// table per row and reads a tile twice when it needs more than 16 loads per
-// lane (range pass, then encode pass).  In
-// both, the waves of one workgroup encode the heads of one (block, K|V), so
-// they write neighbouring pieces of the same rows into one L2.
+// Three kernels.  The tile kernel takes tiles of at most 8 loads per lane,
+// the split kernel larger ones, dealt to 2 to 16 waves of 8 loads each that
+// exchange their range through LDS.  Both keep every load of a tile in flight
+// at once, consume every loaded register on every path, and issue every
+// store (lanes with nothing to write get an offset the hardware drops), which
+// keeps register use low and occupancy high.  Blocks on at most three pages of
+// a layer slice below 4 GiB take their source pages from their work item and
+// address rows with 32-bit buffer offsets; all others (load_tile's WIDE form)
+// first load each row's page from the page table, all of them at once, and
+// then the rows through 64-bit addresses.  The general kernel remains for
+// tiles of more than 128 loads per lane (it reads a tile twice: range pass,
+// then encode pass).  In all, the waves of one workgroup encode
+// neighbouring tiles, so they write neighbouring pieces of the same rows into
+// one L2.
 //
 // Arithmetic follows the format's definition exactly: the zero is the
 // largest binary16 not above the minimum, the scale the smallest binary16
@@ -44,10 +46,6 @@
 
 namespace pkv {
 namespace {
-
-#ifndef GATHER_MIN_WAVES
-#define GATHER_MIN_WAVES 1
-#endif
 
 struct GatherArgs {
   const Unit* units;
@@ -295,7 +293,7 @@ __device__ void encode_tile(const GatherArgs& a, const Unit& u, int which, int h
 }
 
 template <bool BF16, int NL>
-__global__ __launch_bounds__(kGatherMaxWaves * 64, GATHER_MIN_WAVES) void gather_kernel(GatherArgs a) {
+__global__ __launch_bounds__(kGatherMaxWaves * 64) void gather_kernel(GatherArgs a) {
   const int64_t g = xcd_grouped(blockIdx.x, gridDim.x);
   const Unit u = a.units[g >> 1];
   const int which = int(g & 1);
@@ -308,9 +306,12 @@ __global__ __launch_bounds__(kGatherMaxWaves * 64, GATHER_MIN_WAVES) void gather
   for (int head = wave; head < a.H; head += nwaves) encode_tile<BF16, NL>(a, u, which, head, r, c, on);
 }
 
+// Loads per lane and pass of the general kernel.
+constexpr int kGeneralLoads = 16;
+
 // ---------------------------------------------------------------------------
-// Tile kernel for blocks that fit in registers (NL <= 8 loads per lane)
-// and span at most three pages.  Workgroup b's wave w encodes tile
+// Tile kernel for blocks that fit in registers (NL <= 8 loads per lane).
+// Workgroup b's wave w encodes tile
 // b * waves + w of the (unit, K|V, head) order; the unit header, with the
 // block's source pages, is one uniform scalar load; the tile's range is a DPP
 // wave reduction (no LDS traffic, no barrier).
@@ -343,7 +344,8 @@ __device__ __forceinline__ void wave_range(float& mn, float& mx) {
 
 struct TileArgs {
   GatherArgs g;
-  int64_t num_tiles;  // units * 2 * H
+  int64_t num_tiles;     // units * 2 * H
+  int32_t split, group;  // split kernel: waves per tile, tiles per workgroup
 };
 
 // Uniform description of one (unit, K|V, head) tile.
@@ -356,6 +358,7 @@ struct TileHdr {
   int64_t row0;
   int32_t n_valid, bits, head;
   int32_t page0, page1, page2;  // kUnitPages source pages
+  const int32_t* pages;         // the request's page table from the block's first page on
 };
 
 __device__ __forceinline__ TileHdr tile_header(const GatherArgs& a, const Unit* __restrict__ units, int64_t T) {
@@ -379,6 +382,7 @@ __device__ __forceinline__ TileHdr tile_header(const GatherArgs& a, const Unit* 
   h.page0 = __builtin_amdgcn_readfirstlane(u.page0);
   h.page1 = __builtin_amdgcn_readfirstlane(u.page1);
   h.page2 = __builtin_amdgcn_readfirstlane(u.page2);
+  h.pages = a.page_tables + u.pt_off + (u.row0 >> a.log2P);
   return h;
 }
 
@@ -389,32 +393,63 @@ __device__ __forceinline__ TileHdr tile_header(const GatherArgs& a, const Unit* 
 // alone 5%, nt loads alone 2%).
 constexpr int kNonTemporal = 2;
 
-// Every lane loads every one of its NL rows; rows past n_valid (and idle
-// lanes) read the block's first row instead, so the loads carry no branch and
-// stay in flight together.  Offsets are 32-bit from the tile's base (the
-// launch checks that a layer's cache slice is below 4 GiB); the buffer range
-// check returns zeros past the slice rather than faulting.
-template <int NL>
-__device__ __forceinline__ void load_tile(const GatherArgs& a, const TileHdr& h, int r, int c, uint4 (&w)[NL]) {
-  const __amdgpu_buffer_rsrc_t rsrc =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(h.src), 0, h.range, 0x00020000);
-  const uint32_t row_bytes = uint32_t(a.H) * uint32_t(a.D) * 2u;
+using u32x2 = __attribute__((ext_vector_type(2))) unsigned;
+using u32x4 = __attribute__((ext_vector_type(4))) unsigned;
+
+// Every lane loads every one of its NL rows, rows [t_base, t_base + NL * rpl) of
+// the block; rows past n_valid (and idle lanes) read the block's first row
+// instead, so the loads carry no branch and stay in flight together.
+//
+// Narrow form: the block's pages come with its work item and offsets are
+// 32-bit from the tile's base (the launch checks that a layer's cache slice is
+// below 4 GiB and a block is on at most three pages); the buffer range check
+// returns zeros past the slice rather than faulting.
+//
+// WIDE form: any block and any slice.  The NL page numbers of a lane are loaded
+// together (neighbouring rows share a page, so they come from one or two lines
+// of the table), then the NL rows through 64-bit addresses: one table latency
+// in front of a tile instead of one in front of every row.  Bound by the
+// memory streams: 64-token blocks on 16-token pages (32 layers x 8150 tokens, 8
+// heads x 128, fp16, 1.54 GB) take 280 us, 5.5 TB/s, against 467 us when each
+// row waited for its own page.
+template <int NL, bool WIDE>
+__device__ __forceinline__ void load_tile(const GatherArgs& a, const TileHdr& h, int t_base, int r, int c,
+                                          uint4 (&w)[NL]) {
   const uint32_t slot_mask = (1u << a.log2P) - 1;
   const uint32_t slot0 = uint32_t(h.row0) & slot_mask;  // the block's first row within its first page
+  if constexpr (WIDE) {
+    const int64_t row_elems = int64_t(a.H) * a.D;
+    int32_t page[NL];
 #pragma unroll
-  for (int i = 0; i < NL; ++i) {
-    const int t = i * a.rpl + r;
-    const uint32_t pos = slot0 + uint32_t(t < h.n_valid ? t : 0);  // rows from the first page's start
-    const uint32_t k = pos >> a.log2P;                               // 0, 1 or 2
-    const uint32_t page = uint32_t(h.page0) + (k >= 1 ? uint32_t(h.page1 - h.page0) : 0u) +
-                          (k >= 2 ? uint32_t(h.page2 - h.page1) : 0u);
-    const uint32_t off = ((page << a.page_shift) | (pos & slot_mask)) * row_bytes + 16u * uint32_t(c);
-    w[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, kNonTemporal));
+    for (int i = 0; i < NL; ++i) {
+      const int t = t_base + i * a.rpl + r;
+      page[i] = h.pages[(slot0 + uint32_t(t < h.n_valid ? t : 0)) >> a.log2P];
+    }
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int t = t_base + i * a.rpl + r;
+      const uint32_t pos = slot0 + uint32_t(t < h.n_valid ? t : 0);
+      const int64_t slot = (int64_t(page[i]) << a.page_shift) | (pos & slot_mask);
+      w[i] = __builtin_bit_cast(
+          uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(h.src + slot * row_elems + 8 * c)));
+    }
+  } else {
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(h.src), 0, h.range, 0x00020000);
+    const uint32_t row_bytes = uint32_t(a.H) * uint32_t(a.D) * 2u;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int t = t_base + i * a.rpl + r;
+      const uint32_t pos = slot0 + uint32_t(t < h.n_valid ? t : 0);  // rows from the first page's start
+      const uint32_t k = pos >> a.log2P;                               // 0, 1 or 2
+      const uint32_t page = uint32_t(h.page0) + (k >= 1 ? uint32_t(h.page1 - h.page0) : 0u) +
+                            (k >= 2 ? uint32_t(h.page2 - h.page1) : 0u);
+      const uint32_t off = ((page << a.page_shift) | (pos & slot_mask)) * row_bytes + 16u * uint32_t(c);
+      w[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, kNonTemporal));
+    }
   }
 }
 
-using u32x2 = __attribute__((ext_vector_type(2))) unsigned;
-using u32x4 = __attribute__((ext_vector_type(4))) unsigned;
 constexpr uint32_t kDropOffset = 0x80000000u;  // past every tile's range: the store is discarded
 
 // The packed word again, opaque to the optimiser, so the range pass's float
@@ -424,31 +459,15 @@ __device__ __forceinline__ uint4 fresh(uint4 w) {
   return w;
 }
 
-// A tile's work in two steps.  tile_range consumes every loaded register
-// (the range pass; FP16 tiles are converted in place), so once it returns no
-// load of this tile is outstanding and the next tile's loads can be issued
-// without the hardware wait counts having to cover them.  tile_store then
-// encodes and writes; every store is issued (a lane with nothing to write
-// gets an offset past the tile's buffer range, which the hardware drops).
+// Range of the values a wave holds.  Every loaded value belongs to the tile
+// (rows past n_valid and idle lanes load rows of the block), so the range runs
+// over all of them unmasked.  For bf16 the high value of a word is compared as
+// the raw 32-bit word: its low half only adds less than one bf16 step of
+// magnitude, which never changes the order against another value, and is
+// cleared by make_quant.
 template <bool BF16, int NL>
-__device__ __forceinline__ Quant tile_range(const GatherArgs& a, const TileHdr& h, int r, uint4 (&w)[NL],
-                                            uint16_t& sb, uint16_t& zb) {
-  Quant q;
-  if (h.bits == 16) {
-#pragma unroll
-    for (int i = 0; i < NL; ++i) {
-      const int t = i * a.rpl + r;
-      w[i] = t < h.n_valid ? to_half8<BF16>(w[i]) : make_uint4(0, 0, 0, 0);
-    }
-    sb = zb = 0;
-    return q;
-  }
-  // Every loaded value belongs to the tile (rows past n_valid and idle lanes
-  // load rows of the block), so the range runs over all of them unmasked.
-  // For bf16 the high value of a word is compared as the raw 32-bit word:
-  // its low half only adds less than one bf16 step of magnitude, which never
-  // changes the order against another value, and is cleared at the end.
-  float mn = __builtin_inff(), mx = -__builtin_inff();
+__device__ __forceinline__ void tile_minmax(const uint4 (&w)[NL], float& mn, float& mx) {
+  mn = __builtin_inff(), mx = -__builtin_inff();
 #pragma unroll
   for (int i = 0; i < NL; ++i) {
 #pragma unroll
@@ -461,21 +480,46 @@ __device__ __forceinline__ Quant tile_range(const GatherArgs& a, const TileHdr& 
     }
   }
   wave_range(mn, mx);
+}
+
+// Zero and scale of a tile from its range.
+template <bool BF16>
+__device__ __forceinline__ Quant make_quant(float mn, float mx, int bits, uint16_t& sb, uint16_t& zb) {
   if (BF16) {
     mn = __uint_as_float(__float_as_uint(mn) & 0xFFFF0000u);
     mx = __uint_as_float(__float_as_uint(mx) & 0xFFFF0000u);
   }
-  const double qmax = double((1 << h.bits) - 1);
+  Quant q;
+  const double qmax = double((1 << bits) - 1);
   zb = f16_floor(static_cast<double>(mn) + 0.0);  // -0 counts as +0
   q.zero = f16_value(zb);
   sb = f16_ceil(((static_cast<double>(mx) - q.zero) + 0.0) / qmax);  // -0 span counts as +0
   q.scale = f16_value(sb);
   q.zf = static_cast<float>(q.zero);
   q.invf = q.scale != 0.0 ? static_cast<float>(1.0 / q.scale) : 0.0f;
-  q.qmax = uint32_t((1 << h.bits) - 1);
+  q.qmax = uint32_t((1 << bits) - 1);
   return q;
 }
 
+// FP16 tiles: the binary16 rows, padding rows zero, stored as they lie.  Every
+// store is issued (a lane with nothing to write gets an offset past the
+// tile's buffer range, which the hardware drops).
+template <bool BF16, int NL>
+__device__ __forceinline__ void store_half_tile(const GatherArgs& a, const TileHdr& h, __amdgpu_buffer_rsrc_t out,
+                                                int t_base, int r, int c, bool on, const uint4 (&w)[NL]) {
+#pragma unroll
+  for (int i = 0; i < NL; ++i) {
+    const int t = t_base + i * a.rpl + r;
+    const uint4 v = t < h.n_valid ? to_half8<BF16>(w[i]) : make_uint4(0, 0, 0, 0);
+    const uint32_t off = on && t < a.B
+                             ? (uint32_t(t) * uint32_t(a.H) + uint32_t(h.head)) * uint32_t(a.D) * 2 + 16u * uint32_t(c)
+                             : kDropOffset;
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), out, off, 0, kNonTemporal);
+  }
+}
+
+// Codes of rows [t_base, t_base + NL * rpl) of a tile.
+//
 // STAGE: the workgroup's waves encode every head of one (block, K|V), whose
 // code tile [B][H][D] is one contiguous run of the checkpoint.  Each wave
 // puts its head's codes into the tile's image in LDS; after a barrier the
@@ -485,26 +529,14 @@ __device__ __forceinline__ Quant tile_range(const GatherArgs& a, const TileHdr& 
 // other half).  FP16 tiles are stored directly either way (each head row is
 // whole lines).
 template <bool BF16, int NL, bool STAGE>
-__device__ __forceinline__ void tile_store(const GatherArgs& a, const TileHdr& h, int r, int c, bool on,
-                                           const uint4 (&w)[NL], const Quant& q, uint16_t sb, uint16_t zb,
-                                           uint8_t* __restrict__ lds) {
+__device__ __forceinline__ void store_codes(const GatherArgs& a, const TileHdr& h, __amdgpu_buffer_rsrc_t out,
+                                            int t_base, int r, int c, bool on, const uint4 (&w)[NL], const Quant& q,
+                                            uint8_t* __restrict__ lds) {
   const uint32_t H = uint32_t(a.H), D = uint32_t(a.D);
-  const bool lane0 = (threadIdx.x & 63) == 0;
-  const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(h.tile, 0, h.tile_bytes, 0x00020000);
-  if (h.bits == 16) {
-#pragma unroll
-    for (int i = 0; i < NL; ++i) {
-      const int t = i * a.rpl + r;
-      const uint32_t off = on && t < a.B ? (uint32_t(t) * H + uint32_t(h.head)) * D * 2 + 16u * uint32_t(c) : kDropOffset;
-      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, w[i]), out, off, 0, kNonTemporal);
-    }
-    if (lane0) *h.scale_word = 0u;
-    return;
-  }
   const bool flat = q.scale == 0.0;  // every value equals the zero: code 0
 #pragma unroll
   for (int i = 0; i < NL; ++i) {
-    const int t = i * a.rpl + r;
+    const int t = t_base + i * a.rpl + r;
     const bool valid = t < h.n_valid && !flat;
     const bool store = on && t < a.B;
     const uint4 x = fresh(w[i]);
@@ -530,17 +562,9 @@ __device__ __forceinline__ void tile_store(const GatherArgs& a, const TileHdr& h
       }
     }
   }
-  if (lane0) *h.scale_word = uint32_t(sb) | (uint32_t(zb) << 16);
-  if constexpr (STAGE) {
-    __syncthreads();  // every head's codes are in the image
-    const uint32_t n16 = h.tile_bytes / 16;
-    for (uint32_t i = threadIdx.x; i < n16; i += blockDim.x)
-      __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4*>(lds + 16 * i), out, 16 * i, 0,
-                                             kNonTemporal);
-  }
 }
 
-template <bool BF16, int NL, bool STAGE>
+template <bool BF16, int NL, bool STAGE, bool WIDE>
 __global__ __launch_bounds__(kGatherMaxWaves * 64) void gather_tile_kernel(TileArgs s, const Unit* __restrict__ units) {
   extern __shared__ __attribute__((aligned(16))) uint8_t tile_image[];
   const GatherArgs& a = s.g;
@@ -553,165 +577,106 @@ __global__ __launch_bounds__(kGatherMaxWaves * 64) void gather_tile_kernel(TileA
   if (T >= s.num_tiles) return;
   const TileHdr h = tile_header(a, units, T);
   uint4 w[NL];
+  load_tile<NL, WIDE>(a, h, 0, r, c, w);
+  const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(h.tile, 0, h.tile_bytes, 0x00020000);
+  if (h.bits == 16) {
+    store_half_tile<BF16, NL>(a, h, out, 0, r, c, on, w);
+    if (lane == 0) *h.scale_word = 0u;
+    return;
+  }
+  float mn, mx;
+  tile_minmax<BF16, NL>(w, mn, mx);
   uint16_t sb, zb;
-  load_tile<NL>(a, h, r, c, w);
-  const Quant q = tile_range<BF16, NL>(a, h, r, w, sb, zb);
-  tile_store<BF16, NL, STAGE>(a, h, r, c, on, w, q, sb, zb, tile_image);
+  const Quant q = make_quant<BF16>(mn, mx, h.bits, sb, zb);
+  store_codes<BF16, NL, STAGE>(a, h, out, 0, r, c, on, w, q, tile_image);
+  if (lane == 0) *h.scale_word = uint32_t(sb) | (uint32_t(zb) << 16);
+  if constexpr (STAGE) {
+    __syncthreads();  // every head's codes are in the image
+    const uint32_t n16 = h.tile_bytes / 16;
+    for (uint32_t i = threadIdx.x; i < n16; i += blockDim.x)
+      __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4*>(tile_image + 16 * i), out, 16 * i, 0,
+                                             kNonTemporal);
+  }
 }
 
-// Tiles of 9 to 16 loads per lane (64-token blocks at head_dim 128) as two
-// halves on two waves: each wave holds 8 loads (rows [32h, 32h + 32) at
-// head_dim 128), the pair exchanges its tile's range through LDS behind the
-// workgroup's one barrier, then each wave encodes and stores its half.  An
-// 8-wave workgroup holds the two halves of four consecutive tiles.  Held
-// whole by one wave, such a tile needs 150 registers and a workgroup per CU;
-// as halves it takes 76 (three workgroups per CU), measured 6.6% faster on the
-// 70B-shaped write (5488-5494 against 5880-5889 us).  Every wave passes the
-// barrier exactly once, FP16 tiles and waves past the last tile included.
-constexpr int kHalfWaves = 8;
+// Tiles of more than 8 loads per lane (64-token blocks at head_dim 128) dealt
+// to `split` waves: wave p of a tile holds 8 loads (rows [32p, 32p + 32) at
+// head_dim 128), the tile's waves exchange their ranges through LDS behind the
+// workgroup's one barrier, then each wave encodes and stores its part.  A
+// workgroup holds the waves of `group` consecutive tiles (kSplitWaves waves
+// where they fit).  Held whole by one wave, a 16-load tile needs 150 registers
+// and a workgroup per CU; as halves it takes 76 (three workgroups per CU),
+// measured 6.6% faster on the 70B-shaped write (5488-5494 against 5880-5889
+// us).  Every wave passes the barrier exactly once, FP16 tiles and waves past
+// the last tile included.
+constexpr int kSplitLoads = 8;
+constexpr int kSplitWaves = 8;
 
-template <bool BF16>
-__global__ __launch_bounds__(kHalfWaves * 64) void gather_half_kernel(TileArgs s, const Unit* __restrict__ units) {
-  __shared__ float s_rng[kHalfWaves][2];
+template <bool BF16, bool WIDE>
+__global__ __launch_bounds__(kGatherMaxWaves * 64) void gather_split_kernel(TileArgs s, const Unit* __restrict__ units) {
+  __shared__ float s_rng[kGatherMaxWaves][2];
   const GatherArgs& a = s.g;
-  constexpr int NL = 8;
+  constexpr int NL = kSplitLoads;
   const int lane = threadIdx.x & 63;
   const int r = lane / a.lpr;
   const int c = lane - r * a.lpr;
   const bool on = r < a.rpl;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t W = xcd_grouped(blockIdx.x, gridDim.x) * kHalfWaves + wave;
-  const int64_t T = W >> 1;
-  const int half = int(W & 1);
+  const int local = wave / s.split, part = wave - local * s.split;
+  const int64_t T = xcd_grouped(blockIdx.x, gridDim.x) * s.group + local;
   const bool live = T < s.num_tiles;  // uniform per wave; every wave still passes the barrier
   const TileHdr h = tile_header(a, units, live ? T : 0);
-  const int t_base = half * NL * a.rpl;
+  const int t_base = part * NL * a.rpl;
   uint4 w[NL];
-  {
-    const __amdgpu_buffer_rsrc_t rsrc =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(h.src), 0, h.range, 0x00020000);
-    const uint32_t row_bytes = uint32_t(a.H) * uint32_t(a.D) * 2u;
-    const uint32_t slot_mask = (1u << a.log2P) - 1;
-    const uint32_t slot0 = uint32_t(h.row0) & slot_mask;
-#pragma unroll
-    for (int i = 0; i < NL; ++i) {
-      const int t = t_base + i * a.rpl + r;
-      const uint32_t pos = slot0 + uint32_t(t < h.n_valid ? t : 0);
-      const uint32_t k = pos >> a.log2P;
-      const uint32_t page = uint32_t(h.page0) + (k >= 1 ? uint32_t(h.page1 - h.page0) : 0u) +
-                            (k >= 2 ? uint32_t(h.page2 - h.page1) : 0u);
-      const uint32_t off = ((page << a.page_shift) | (pos & slot_mask)) * row_bytes + 16u * uint32_t(c);
-      w[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, kNonTemporal));
-    }
-  }
-  const uint32_t H = uint32_t(a.H), D = uint32_t(a.D);
-  const bool lane0 = lane == 0;
+  load_tile<NL, WIDE>(a, h, t_base, r, c, w);
+  const bool lead = lane == 0 && part == 0 && live;
   const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(h.tile, 0, live ? h.tile_bytes : 0u, 0x00020000);
   if (h.bits == 16) {
-    __syncthreads();  // matches the range exchange of the other tags (uniform per workgroup)
-#pragma unroll
-    for (int i = 0; i < NL; ++i) {
-      const int t = t_base + i * a.rpl + r;
-      const uint4 v = t < h.n_valid ? to_half8<BF16>(w[i]) : make_uint4(0, 0, 0, 0);
-      const uint32_t off = on && t < a.B ? (uint32_t(t) * H + uint32_t(h.head)) * D * 2 + 16u * uint32_t(c) : kDropOffset;
-      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), out, off, 0, kNonTemporal);
-    }
-    if (lane0 && half == 0 && live) *h.scale_word = 0u;
+    __syncthreads();  // matches the range exchange of the other tags
+    store_half_tile<BF16, NL>(a, h, out, t_base, r, c, on, w);
+    if (lead) *h.scale_word = 0u;
     return;
   }
-  float mn = __builtin_inff(), mx = -__builtin_inff();
-#pragma unroll
-  for (int i = 0; i < NL; ++i) {
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      const uint32_t word = word_of(w[i], 2 * p);
-      const float x0 = cache_value<BF16>(word, 0);
-      const float x1 = BF16 ? __uint_as_float(word) : cache_value<BF16>(word, 1);
-      mn = __builtin_fminf(__builtin_fminf(mn, x0), x1);
-      mx = __builtin_fmaxf(__builtin_fmaxf(mx, x0), x1);
-    }
-  }
-  wave_range(mn, mx);
-  if (lane0) {
+  float mn, mx;
+  tile_minmax<BF16, NL>(w, mn, mx);
+  if (lane == 0) {
     s_rng[wave][0] = mn;
     s_rng[wave][1] = mx;
   }
   __syncthreads();
-  mn = __builtin_fminf(mn, s_rng[wave ^ 1][0]);
-  mx = __builtin_fmaxf(mx, s_rng[wave ^ 1][1]);
-  if (BF16) {
-    mn = __uint_as_float(__float_as_uint(mn) & 0xFFFF0000u);
-    mx = __uint_as_float(__float_as_uint(mx) & 0xFFFF0000u);
+  for (int p = 0; p < s.split; ++p) {
+    mn = __builtin_fminf(mn, s_rng[local * s.split + p][0]);
+    mx = __builtin_fmaxf(mx, s_rng[local * s.split + p][1]);
   }
-  Quant q;
-  const double qmax = double((1 << h.bits) - 1);
-  const uint16_t zb = f16_floor(static_cast<double>(mn) + 0.0);
-  q.zero = f16_value(zb);
-  const uint16_t sb = f16_ceil(((static_cast<double>(mx) - q.zero) + 0.0) / qmax);
-  q.scale = f16_value(sb);
-  q.zf = static_cast<float>(q.zero);
-  q.invf = q.scale != 0.0 ? static_cast<float>(1.0 / q.scale) : 0.0f;
-  q.qmax = uint32_t((1 << h.bits) - 1);
-  const bool flat = q.scale == 0.0;
-#pragma unroll
-  for (int i = 0; i < NL; ++i) {
-    const int t = t_base + i * a.rpl + r;
-    const bool valid = t < h.n_valid && !flat;
-    const bool store = on && t < a.B;
-    const uint4 x = fresh(w[i]);
-    if (h.bits == 8) {
-      uint2 v = make_uint2(encode_word<BF16, 4>(make_uint4(x.x, x.y, 0, 0), q),
-                           encode_word<BF16, 4>(make_uint4(x.z, x.w, 0, 0), q));
-      v = valid ? v : make_uint2(0, 0);
-      const uint32_t at = (uint32_t(t) * H + uint32_t(h.head)) * D + 8u * uint32_t(c);
-      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), out, store ? at : kDropOffset, 0, kNonTemporal);
-    } else {
-      uint32_t v = encode_word<BF16, 8>(x, q);
-      v = valid ? v : 0u;
-      const uint32_t at = (uint32_t(t) * H + uint32_t(h.head)) * (D / 2) + 4u * uint32_t(c);
-      __builtin_amdgcn_raw_buffer_store_b32(v, out, store ? at : kDropOffset, 0, kNonTemporal);
-    }
-  }
-  if (lane0 && half == 0 && live) *h.scale_word = uint32_t(sb) | (uint32_t(zb) << 16);
+  uint16_t sb, zb;
+  const Quant q = make_quant<BF16>(mn, mx, h.bits, sb, zb);
+  store_codes<BF16, NL, false>(a, h, out, t_base, r, c, on, w, q, nullptr);
+  if (lead) *h.scale_word = uint32_t(sb) | (uint32_t(zb) << 16);
 }
 
 // The staged store needs a workgroup to hold exactly the heads of one
 // (block, K|V) -- one wave per head -- and the 8-bit image of a tile in LDS.
 constexpr uint32_t kTileImageMax = 64u << 10;
 
-template <bool BF16, int NL>
-hipError_t launch_tile_nl(const TileArgs& s, const Unit* units, int wg, uint32_t image, hipStream_t stream) {
+template <bool BF16, bool WIDE, int NL>
+void launch_tile(const TileArgs& s, const Unit* units, int wg, uint32_t image, hipStream_t stream) {
   const int64_t waves = wg / 64;
   const dim3 grid(static_cast<uint32_t>((s.num_tiles + waves - 1) / waves));
   if (image)
-    hipLaunchKernelGGL((gather_tile_kernel<BF16, NL, true>), grid, dim3(wg), image, stream, s, units);
+    hipLaunchKernelGGL((gather_tile_kernel<BF16, NL, true, WIDE>), grid, dim3(wg), image, stream, s, units);
   else
-    hipLaunchKernelGGL((gather_tile_kernel<BF16, NL, false>), grid, dim3(wg), 0, stream, s, units);
-  return hipGetLastError();
+    hipLaunchKernelGGL((gather_tile_kernel<BF16, NL, false, WIDE>), grid, dim3(wg), 0, stream, s, units);
 }
 
-template <bool BF16>
-hipError_t launch_tile(const TileArgs& s, const Unit* units, int nl, int wg, uint32_t image, hipStream_t stream) {
-  switch (nl) {
-    case 2: return launch_tile_nl<BF16, 2>(s, units, wg, image, stream);
-    case 4: return launch_tile_nl<BF16, 4>(s, units, wg, image, stream);
-    case 8: return launch_tile_nl<BF16, 8>(s, units, wg, image, stream);
-    default: {
-      const dim3 grid(static_cast<uint32_t>((2 * s.num_tiles + kHalfWaves - 1) / kHalfWaves));
-      hipLaunchKernelGGL((gather_half_kernel<BF16>), grid, dim3(kHalfWaves * 64), 0, stream, s, units);
-      return hipGetLastError();
-    }
-  }
-}
-
-template <bool BF16>
-void launch_gather(const GatherArgs& a, int nl, dim3 grid, dim3 block, hipStream_t stream) {
-  switch (nl) {
-    case 2: hipLaunchKernelGGL((gather_kernel<BF16, 2>), grid, block, 0, stream, a); break;
-    case 4: hipLaunchKernelGGL((gather_kernel<BF16, 4>), grid, block, 0, stream, a); break;
-    case 8: hipLaunchKernelGGL((gather_kernel<BF16, 8>), grid, block, 0, stream, a); break;
-    default: hipLaunchKernelGGL((gather_kernel<BF16, 16>), grid, block, 0, stream, a); break;
-  }
+template <bool BF16, bool WIDE>
+void launch_tiles(TileArgs s, const Unit* units, int nload, int wg, uint32_t image, hipStream_t stream) {
+  if (nload <= 2) return launch_tile<BF16, WIDE, 2>(s, units, wg, image, stream);
+  if (nload <= 4) return launch_tile<BF16, WIDE, 4>(s, units, wg, image, stream);
+  if (nload <= 8) return launch_tile<BF16, WIDE, 8>(s, units, wg, image, stream);
+  s.split = (nload + kSplitLoads - 1) / kSplitLoads;
+  s.group = s.split < kSplitWaves ? kSplitWaves / s.split : 1;
+  const dim3 grid(static_cast<uint32_t>((s.num_tiles + s.group - 1) / s.group)), block(64 * s.split * s.group);
+  hipLaunchKernelGGL((gather_split_kernel<BF16, WIDE>), grid, block, 0, stream, s, units);
 }
 
 bool overlap(const void* a, uint64_t na, const void* b, uint64_t nb) {
@@ -783,33 +748,34 @@ pkv_status_t pkv_quantize_gather(const pkv_plan_t* plan, const void* k_cache, co
   a.lpr = m.head_dim / 8;
   a.rpl = 64 / a.lpr;
   const int nload = (m.block_tokens + a.rpl - 1) / a.rpl;  // loads per lane covering a block
-  const int nl = pkv::gather_loads_per_chunk(nload);
-  a.nchunk = (nload + nl - 1) / nl;
+  a.nchunk = (nload + pkv::kGeneralLoads - 1) / pkv::kGeneralLoads;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  if (a.nchunk == 1 && m.block_tokens <= 2 * m.page_size + 1 && a.layer_elems * 2 < (int64_t(1) << 32)) {
-    // Tiles of at most 16 loads per lane on at most kUnitPages pages, layer
-    // slices below 4 GiB: the tile kernel (up to 8 loads) or the half-tile
-    // kernel (9 to 16).
+  const bool bf16 = m.out_dtype == PKV_OUT_BF16;
+  if (nload <= pkv::kSplitLoads * pkv::kGatherMaxWaves) {
     pkv::TileArgs sa;
     sa.g = a;
     sa.num_tiles = info.num_units * 2 * m.num_kv_heads;
+    sa.split = sa.group = 1;
     // Staged stores when a workgroup is one wave per head of one (block, K|V)
     // of at most 8 loads per lane.  (Larger tiles staged whole in a
     // workgroup per CU ran 18-20% slower on the 70B-shaped write: the barrier
     // left the CU without loads in flight while it wrote.)
     const uint64_t image = uint64_t(m.block_tokens) * m.num_kv_heads * m.head_dim;
     const uint32_t stage =
-        nl <= 8 && plan->host.workgroup == 64 * m.num_kv_heads && image <= pkv::kTileImageMax ? uint32_t(image) : 0;
-    const hipError_t e = m.out_dtype == PKV_OUT_BF16
-                             ? pkv::launch_tile<true>(sa, plan->d_units, nl, plan->host.workgroup, stage, stream)
-                             : pkv::launch_tile<false>(sa, plan->d_units, nl, plan->host.workgroup, stage, stream);
-    return e == hipSuccess ? PKV_OK : PKV_ERR_DEVICE;
+        nload <= 8 && plan->host.workgroup == 64 * m.num_kv_heads && image <= pkv::kTileImageMax ? uint32_t(image) : 0;
+    // Blocks on more than kUnitPages pages, and layer slices whose rows are
+    // out of a 32-bit offset's reach, look their pages up (load_tile).
+    const bool wide = m.block_tokens > 2 * m.page_size + 1 || a.layer_elems * 2 >= (int64_t(1) << 32);
+    const auto launch = bf16 ? wide ? pkv::launch_tiles<true, true> : pkv::launch_tiles<true, false>
+                             : wide ? pkv::launch_tiles<false, true> : pkv::launch_tiles<false, false>;
+    launch(sa, plan->d_units, nload, plan->host.workgroup, stage, stream);
+  } else {
+    const dim3 grid(static_cast<uint32_t>(2 * info.num_units)), block(plan->host.workgroup);
+    if (bf16)
+      hipLaunchKernelGGL((pkv::gather_kernel<true, pkv::kGeneralLoads>), grid, block, 0, stream, a);
+    else
+      hipLaunchKernelGGL((pkv::gather_kernel<false, pkv::kGeneralLoads>), grid, block, 0, stream, a);
   }
-  const dim3 grid(static_cast<uint32_t>(2 * info.num_units)), block(plan->host.workgroup);
-  if (m.out_dtype == PKV_OUT_BF16)
-    pkv::launch_gather<true>(a, nl, grid, block, stream);
-  else
-    pkv::launch_gather<false>(a, nl, grid, block, stream);
   return hipGetLastError() == hipSuccess ? PKV_OK : PKV_ERR_DEVICE;
 }
 

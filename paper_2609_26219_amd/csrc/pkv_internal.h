@@ -176,15 +176,14 @@ pkv_status_t build_host_plan(const pkv_model_t* model, const pkv_request_t* requ
 pkv_status_t build_checkpoint_plan(const pkv_model_t* model, const pkv_checkpoint_request_t* requests,
                                    int32_t num_requests, HostPlan* out);
 
-// Checkpoint kernel: one wave per (head, K|V) tile of a block, at most
-// kGatherMaxWaves waves per workgroup; a lane holds up to
-// gather_loads_per_chunk(n) 16-byte loads of a tile in registers.
+// Checkpoint kernel: one wave per (head, K|V) tile of a block (larger tiles
+// are dealt to several), at most kGatherMaxWaves waves per workgroup.
 constexpr int kGatherMaxWaves = 16;
 // A checkpoint unit carries the block's first three source pages, enough
-// for every block when block_tokens <= 2 * page_size + 1.
+// for every block when block_tokens <= 2 * page_size + 1; blocks on more
+// pages are looked up in the page table.
 constexpr int kUnitPages = 3;
 int32_t gather_workgroup(const pkv_model_t& m);
-inline int gather_loads_per_chunk(int nload) { return nload <= 2 ? 2 : nload <= 4 ? 4 : nload <= 8 ? 8 : 16; }
 
 // The plan object behind pkv_plan_t (host metadata + one device allocation).
 }  // namespace pkv

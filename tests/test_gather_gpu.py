@@ -62,6 +62,60 @@ def test_checkpoint_bit_exact_paired_pages(params, torch):
     check_checkpoint_write(case, torch)
 
 
+@pytest.mark.parametrize("paired", [False, True], ids=["separate", "paired"])
+@pytest.mark.parametrize("params", [
+    # blocks on more than three pages: staged tiles of 2, 4 and 8 loads per lane, idle lanes
+    dict(L=2, H=8, D=32, B=32, P=4, n_tokens=(70,), deltas=(1,), rho0s=(3,), out_dtype=wl.OUT_BF16),
+    dict(L=1, H=8, D=80, B=16, P=2, n_tokens=(45, 16), deltas=(0, 3), rho0s=(1, 6), out_dtype=wl.OUT_FP16),
+    dict(L=2, H=8, D=128, B=32, P=1, n_tokens=(75,), deltas=(2,), rho0s=(9,), out_dtype=wl.OUT_BF16),
+    # more than 16 heads: not staged
+    dict(L=1, H=17, D=64, B=16, P=4, n_tokens=(37,), deltas=(2,), rho0s=(6,), out_dtype=wl.OUT_BF16),
+    # tiles split over 2, 3, 4, 8, 9 and 16 waves, on many pages and on few
+    dict(L=2, H=8, D=128, B=64, P=16, n_tokens=(150, 64), deltas=(4, 0), rho0s=(13, 96), out_dtype=wl.OUT_FP16),
+    dict(L=1, H=3, D=128, B=96, P=8, n_tokens=(200,), deltas=(4,), rho0s=(5,), out_dtype=wl.OUT_BF16),
+    dict(L=1, H=5, D=128, B=128, P=64, n_tokens=(300,), deltas=(4,), rho0s=(61,), out_dtype=wl.OUT_BF16),
+    dict(L=1, H=2, D=512, B=64, P=1, n_tokens=(130,), deltas=(4,), rho0s=(2,), out_dtype=wl.OUT_FP16),
+    dict(L=1, H=1, D=128, B=288, P=256, n_tokens=(600,), deltas=(4,), rho0s=(250,), out_dtype=wl.OUT_BF16),
+    dict(L=1, H=1, D=128, B=512, P=16, n_tokens=(700,), deltas=(4,), rho0s=(9,), out_dtype=wl.OUT_BF16),
+    # one load past the split kernel's largest tile: the general kernel
+    dict(L=1, H=1, D=128, B=516, P=16, n_tokens=(700,), deltas=(4,), rho0s=(9,), out_dtype=wl.OUT_BF16),
+], ids=["nl2_staged", "nl4_staged_d80", "nl8_staged_p1", "h17_unstaged", "split2", "split3", "split4_narrow",
+        "split8_p1", "split9_narrow", "split16", "general"])
+def test_checkpoint_bit_exact_long_blocks(params, paired, torch):
+    """Blocks on more pages than their work item carries, and tiles of more loads than one wave holds."""
+    import dataclasses
+    case = wl.make_custom(13, tag_set=(0, 1, 2, 3), mix=(1, 1, 1, 1), outlier_pairs=1, **params)
+    case.shape = dataclasses.replace(case.shape, kv_layout=wl.KV_PAIRED if paired else wl.KV_SEPARATE)
+    check_checkpoint_write(case, torch)
+
+
+@pytest.mark.parametrize("block", [32, 64], ids=["tile", "split"])
+def test_checkpoint_from_a_layer_slice_of_4_gib(block, torch):
+    """The same rows on the first pages of a small pool and on the last pages
+    of one whose layer slice is 4 GiB give the same checkpoint."""
+    import dataclasses
+    case = wl.make_custom(14, L=1, H=8, D=128, B=block, P=16, n_tokens=(200,), deltas=(3,), rho0s=(7,),
+                          tag_set=(0, 1, 2, 3), mix=(1, 1, 1, 1), outlier_pairs=1, out_dtype=wl.OUT_BF16)
+    _, _, dk, dv = _old_device_caches(case, torch)
+    small = case.src_shape
+    big = dataclasses.replace(small, pool_pages=1 << 17)
+    assert big.layer_elems * 2 == 1 << 32
+    move = big.pool_pages - small.pool_pages
+    bk, bv = (torch.empty((1, big.pool_pages) + tuple(dk.shape[2:]), dtype=dk.dtype, device="cuda") for _ in range(2))
+    bk[:, move:], bv[:, move:] = dk, dv
+    moved = [dataclasses.replace(r, src_page_table=r.src_page_table + move) for r in case.requests]
+    out = []
+    for shape, requests, k, v in ((small, case.requests, dk, dv), (big, moved, bk, bv)):
+        payload = torch.zeros(case.payload_nbytes, dtype=torch.uint8, device="cuda")
+        scales = torch.zeros(case.scale_elems, dtype=torch.int16, device="cuda")
+        plan = pb.pkv_checkpoint_plan(shape, requests)
+        pb.quantize_gather_tensors(plan, k, v, payload, scales)
+        torch.cuda.synchronize()
+        out.append((payload, scales))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    assert int(out[0][0].count_nonzero()) > 0
+
+
 @pytest.mark.parametrize("out", [wl.OUT_FP16, wl.OUT_BF16])
 def test_checkpoint_exact_and_near_ties(out, torch):
     """Rows on a grid of half-integer multiples of the scale (exact ties, which

@@ -265,3 +265,46 @@ def test_half_tile_kernel_mapping(maker):
             if half == 0:
                 scale_writes[T] += 1
     assert (rows_of == 1).all() and (scale_writes == 1).all()
+
+
+SPLIT_LOADS, SPLIT_WAVES = 8, 8  # loads per lane of one wave; waves per workgroup where the tiles' waves fit
+
+
+@pytest.mark.parametrize("B,D,H,split,group", [
+    (64, 128, 8, 2, 4),    # 16 loads: halves
+    (36, 128, 1, 2, 4),    # 9 loads: the smallest split, its second wave holds one load
+    (96, 128, 3, 3, 2),    # 24 loads: 6-wave workgroups
+    (128, 80, 2, 3, 2),    # 22 loads of 6 rows, idle lanes
+    (64, 512, 2, 8, 1),    # 64 loads
+    (288, 128, 1, 9, 1),   # 72 loads: more than 8 waves per tile
+    (512, 128, 1, 16, 1),  # 128 loads: the largest
+])
+def test_split_kernel_mapping(B, D, H, split, group):
+    """Split kernel (9 to 128 loads per lane): `split` waves of a workgroup hold
+    one tile, `group` tiles to a workgroup; every row of every tile belongs to
+    one wave of its workgroup, and workgroups stay within 16 waves."""
+    lpr = D // 8
+    rpl = 64 // lpr
+    nload = -(-B // rpl)
+    assert split == -(-nload // SPLIT_LOADS) and group == max(1, SPLIT_WAVES // split)
+    assert 1 < split * group <= MAX_WAVES
+    ntiles = 2 * H * 3
+    grid = -(-ntiles // group)
+    lane = np.arange(64)
+    r, c = lane // lpr, lane % lpr
+    on = r < rpl
+    rows_of = np.zeros((ntiles, B, lpr), dtype=np.int32)
+    leads = np.zeros(ntiles, dtype=np.int32)
+    for b in range(grid):
+        for w in range(split * group):
+            local, part = w // split, w % split
+            T = b * group + local
+            assert local < group and local * split + part == w  # the range exchange reads waves of this workgroup
+            if T >= ntiles:
+                continue
+            for i in range(SPLIT_LOADS):
+                t = part * SPLIT_LOADS * rpl + i * rpl + r
+                st = on & (t < B)
+                np.add.at(rows_of[T], (t[st], c[st]), 1)
+            leads[T] += part == 0
+    assert (rows_of == 1).all() and (leads == 1).all()
