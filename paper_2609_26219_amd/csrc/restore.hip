@@ -109,11 +109,19 @@ constexpr uint32_t kWholeRange = 0xFFFFFFFFu;
 // An offset past every bounded buffer of the kernel (a cache page is below
 // 2 GiB, a unit's payload run a few MiB): accesses there are dropped.
 constexpr uint32_t kOutside = 0x80000000u;
-// Cache-policy operand of the buffer intrinsics: nt (non-temporal) on gfx950.
+// Cache-policy operands of the buffer intrinsics on gfx950: nt (non-temporal),
+// and nt with sc1 (device scope).
 constexpr int kNonTemporal = 2;
+constexpr int kNonTemporalDevice = 18;
 
 // Restored rows are written once and not read again by this launch: store
-// them non-temporally (measured 2% faster on the 8B-shaped workload).
+// them non-temporally (2% faster than the default policy), and in the early
+// order, which deep launches of wide rows take, at device scope too, so that a
+// line leaves its XCD's L2 as it is written and not when another one evicts
+// it.  The write stream bounds those launches: the 8B-shaped 32-layer restore
+// takes 847 us that way against 886 (5.34 GB, 6.3 against 6.0 TB/s).  Narrow
+// rows and shallow launches, which take the late order, gain nothing from it
+// (one head of 128, 80 layers: 643 us against 638).
 //
 // The whole offset goes in the VGPR operand and the SGPR offset is 0.  A
 // 16-byte store reads its data registers after it issues, so an instruction
@@ -122,8 +130,10 @@ constexpr int kNonTemporal = 2;
 // a register SGPR offset gfx950 was seen storing the next instruction's
 // result (a token's 16 outputs replaced, now and then, by an address or a
 // decoded value).
+template <bool LATE>
 __device__ __forceinline__ void store_row_piece(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, uint4 v) {
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, voff + soff, 0, kNonTemporal);
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, voff + soff, 0,
+                                         LATE ? kNonTemporal : kNonTemporalDevice);
 }
 
 // Two floats to two bfloat16 / binary16 values, round to nearest even, in
@@ -264,7 +274,7 @@ __device__ __forceinline__ void decode_run(const Chunk8<KBITS>& c, float s, floa
 
 // Keys of one (token, head), piece p, from its two loaded runs: decode,
 // rotate, round, store.
-template <int KBITS, bool ROT, int STYLE, bool BF16>
+template <int KBITS, bool ROT, int STYLE, bool BF16, bool LATE>
 __device__ __forceinline__ void key_store(const Chunk8<KBITS>& lo, const Chunk8<KBITS>& hi, const KeyPiece& p, float ks,
                                           float kz, const double2* __restrict__ cs, __amdgpu_buffer_rsrc_t dst,
                                           uint32_t doff, uint32_t soff) {
@@ -305,12 +315,12 @@ __device__ __forceinline__ void key_store(const Chunk8<KBITS>& lo, const Chunk8<
     out_lo = pack8<BF16>(a);
     out_hi = pack8<BF16>(b);
   }
-  store_row_piece(dst, doff + 2 * p.lo, soff, out_lo);
-  store_row_piece(dst, doff + 2 * p.hi, soff, out_hi);
+  store_row_piece<LATE>(dst, doff + 2 * p.lo, soff, out_lo);
+  store_row_piece<LATE>(dst, doff + 2 * p.hi, soff, out_hi);
 }
 
 // Values of one (token, head), piece j (never rotated).
-template <int VBITS, bool BF16>
+template <int VBITS, bool BF16, bool LATE>
 __device__ __forceinline__ void value_store(const Chunk8<VBITS>& lo, const Chunk8<VBITS>& hi, int j, int D, float vs,
                                             float vz, __amdgpu_buffer_rsrc_t dst, uint32_t doff, uint32_t soff) {
   uint4 out_lo, out_hi;
@@ -327,8 +337,8 @@ __device__ __forceinline__ void value_store(const Chunk8<VBITS>& lo, const Chunk
     out_lo = pack8<BF16>(a);
     out_hi = pack8<BF16>(b);
   }
-  store_row_piece(dst, doff + 16 * j, soff, out_lo);
-  store_row_piece(dst, doff + D + 16 * j, soff, out_hi);
+  store_row_piece<LATE>(dst, doff + 16 * j, soff, out_lo);
+  store_row_piece<LATE>(dst, doff + D + 16 * j, soff, out_hi);
 }
 
 // What a thread needs for every token of its unit.
@@ -421,8 +431,8 @@ __device__ __forceinline__ void restore_tokens(const KernelArgs& a, const Unit& 
 #pragma unroll
   for (int k = 0; k < NK; ++k) {
     const uint32_t d = !LATE || k < valid ? doff : kOutside;
-    key_store<KB, ROT, STYLE, BF16>(klo[k], khi[k], q.kp, q.ks, q.kz, cs, q.kdst, d, k * tpp * H * D * 2);
-    value_store<VB, BF16>(vlo[k], vhi[k], q.j, D, q.vs, q.vz, q.vdst, d, k * tpp * H * D * 2);
+    key_store<KB, ROT, STYLE, BF16, LATE>(klo[k], khi[k], q.kp, q.ks, q.kz, cs, q.kdst, d, k * tpp * H * D * 2);
+    value_store<VB, BF16, LATE>(vlo[k], vhi[k], q.j, D, q.vs, q.vz, q.vdst, d, k * tpp * H * D * 2);
   }
 }
 
