@@ -39,6 +39,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <new>
 
 #include "pkv.h"
@@ -501,20 +502,25 @@ __device__ __forceinline__ Quant make_quant(float mn, float mx, int bits, uint16
   return q;
 }
 
-// FP16 tiles: the binary16 rows, padding rows zero, stored as they lie.  Every
+// FP16 tiles: the binary16 rows, padding rows zero, stored as they lie, all of
+// them once the last has arrived (1% faster than each as it comes).  Every
 // store is issued (a lane with nothing to write gets an offset past the
 // tile's buffer range, which the hardware drops).
 template <bool BF16, int NL>
 __device__ __forceinline__ void store_half_tile(const GatherArgs& a, const TileHdr& h, __amdgpu_buffer_rsrc_t out,
-                                                int t_base, int r, int c, bool on, const uint4 (&w)[NL]) {
+                                                int t_base, int r, int c, bool on, uint4 (&w)[NL]) {
 #pragma unroll
   for (int i = 0; i < NL; ++i) {
     const int t = t_base + i * a.rpl + r;
-    const uint4 v = t < h.n_valid ? to_half8<BF16>(w[i]) : make_uint4(0, 0, 0, 0);
+    w[i] = fresh(t < h.n_valid ? to_half8<BF16>(w[i]) : make_uint4(0, 0, 0, 0));
+  }
+#pragma unroll
+  for (int i = 0; i < NL; ++i) {
+    const int t = t_base + i * a.rpl + r;
     const uint32_t off = on && t < a.B
                              ? (uint32_t(t) * uint32_t(a.H) + uint32_t(h.head)) * uint32_t(a.D) * 2 + 16u * uint32_t(c)
                              : kDropOffset;
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), out, off, 0, kNonTemporal);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, w[i]), out, off, 0, kNonTemporal);
   }
 }
 
@@ -654,25 +660,23 @@ __global__ __launch_bounds__(kGatherMaxWaves * 64) void gather_split_kernel(Tile
   if (lead) *h.scale_word = uint32_t(sb) | (uint32_t(zb) << 16);
 }
 
-// The staged store needs a workgroup to hold exactly the heads of one
-// (block, K|V) -- one wave per head -- and the 8-bit image of a tile in LDS.
-constexpr uint32_t kTileImageMax = 64u << 10;
-
 template <bool BF16, bool WIDE, int NL>
-void launch_tile(const TileArgs& s, const Unit* units, int wg, uint32_t image, hipStream_t stream) {
+void launch_tile(const TileArgs& s, const Unit* units, int wg, uint32_t image, uint32_t cap, hipStream_t stream) {
   const int64_t waves = wg / 64;
   const dim3 grid(static_cast<uint32_t>((s.num_tiles + waves - 1) / waves));
   if (image)
-    hipLaunchKernelGGL((gather_tile_kernel<BF16, NL, true, WIDE>), grid, dim3(wg), image, stream, s, units);
+    hipLaunchKernelGGL((gather_tile_kernel<BF16, NL, true, WIDE>), grid, dim3(wg), std::max(image, cap), stream, s,
+                       units);
   else
     hipLaunchKernelGGL((gather_tile_kernel<BF16, NL, false, WIDE>), grid, dim3(wg), 0, stream, s, units);
 }
 
 template <bool BF16, bool WIDE>
-void launch_tiles(TileArgs s, const Unit* units, int nload, int wg, uint32_t image, hipStream_t stream) {
-  if (nload <= 2) return launch_tile<BF16, WIDE, 2>(s, units, wg, image, stream);
-  if (nload <= 4) return launch_tile<BF16, WIDE, 4>(s, units, wg, image, stream);
-  if (nload <= 8) return launch_tile<BF16, WIDE, 8>(s, units, wg, image, stream);
+void launch_tiles(TileArgs s, const Unit* units, int nload, int wg, uint32_t image, uint32_t cap,
+                  hipStream_t stream) {
+  if (nload <= 2) return launch_tile<BF16, WIDE, 2>(s, units, wg, image, cap, stream);
+  if (nload <= 4) return launch_tile<BF16, WIDE, 4>(s, units, wg, image, cap, stream);
+  if (nload <= 8) return launch_tile<BF16, WIDE, 8>(s, units, wg, image, cap, stream);
   s.split = (nload + kSplitLoads - 1) / kSplitLoads;
   s.group = s.split < kSplitWaves ? kSplitWaves / s.split : 1;
   const dim3 grid(static_cast<uint32_t>((s.num_tiles + s.group - 1) / s.group)), block(64 * s.split * s.group);
@@ -747,7 +751,7 @@ pkv_status_t pkv_quantize_gather(const pkv_plan_t* plan, const void* k_cache, co
   a.log2P = plan->host.log2_page;
   a.lpr = m.head_dim / 8;
   a.rpl = 64 / a.lpr;
-  const int nload = (m.block_tokens + a.rpl - 1) / a.rpl;  // loads per lane covering a block
+  const int nload = pkv::gather_loads(m);
   a.nchunk = (nload + pkv::kGeneralLoads - 1) / pkv::kGeneralLoads;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const bool bf16 = m.out_dtype == PKV_OUT_BF16;
@@ -756,19 +760,12 @@ pkv_status_t pkv_quantize_gather(const pkv_plan_t* plan, const void* k_cache, co
     sa.g = a;
     sa.num_tiles = info.num_units * 2 * m.num_kv_heads;
     sa.split = sa.group = 1;
-    // Staged stores when a workgroup is one wave per head of one (block, K|V)
-    // of at most 8 loads per lane.  (Larger tiles staged whole in a
-    // workgroup per CU ran 18-20% slower on the 70B-shaped write: the barrier
-    // left the CU without loads in flight while it wrote.)
-    const uint64_t image = uint64_t(m.block_tokens) * m.num_kv_heads * m.head_dim;
-    const uint32_t stage =
-        nload <= 8 && plan->host.workgroup == 64 * m.num_kv_heads && image <= pkv::kTileImageMax ? uint32_t(image) : 0;
     // Blocks on more than kUnitPages pages, and layer slices whose rows are
     // out of a 32-bit offset's reach, look their pages up (load_tile).
     const bool wide = m.block_tokens > 2 * m.page_size + 1 || a.layer_elems * 2 >= (int64_t(1) << 32);
     const auto launch = bf16 ? wide ? pkv::launch_tiles<true, true> : pkv::launch_tiles<true, false>
                              : wide ? pkv::launch_tiles<false, true> : pkv::launch_tiles<false, false>;
-    launch(sa, plan->d_units, nload, plan->host.workgroup, stage, stream);
+    launch(sa, plan->d_units, nload, plan->host.workgroup, pkv::gather_image(m), plan->cap_lds, stream);
   } else {
     const dim3 grid(static_cast<uint32_t>(2 * info.num_units)), block(plan->host.workgroup);
     if (bf16)

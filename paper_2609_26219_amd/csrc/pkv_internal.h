@@ -168,6 +168,22 @@ struct HostPlan {
 // one-wave workgroups and 243 at 12 or 16.
 int restore_workgroups_per_cu(const HostPlan& hp);
 
+// The same for the checkpoint write, 0 for no cap: staged tiles of 8 loads per
+// lane (32-token blocks at head_dim 128) run best with 16 waves, 128 KB of
+// loads, on a compute unit instead of the 24 that fit, while the checkpoint
+// is between 0.4 and 0.85 of the cache rows it is read from.  Measured on the
+// 8B-shaped 32-layer write, us with 24 / 16 waves (written / read in
+// parentheses), 8 heads:
+//   FP16 and K8V8 in halves (0.75)  1368 / 1293    K8V8 (0.50)             1097 / 1022
+//   30% FP16, 70% K8V8 (0.65)       1277 / 1180    the mixed tags (0.47)   1094 / 1029
+//   K8V4 (0.38)                     1019 / 1001    K8V4, K4V4 (0.31)        943 / 983
+//   FP16 (1.00)                     1447 / 1454    K4V4 (0.25)              908 / 983
+// four heads: mixed 551 / 525, K8V4 504 / 490, K4V4 452 / 474, FP16 707 / 743;
+// one and two heads alike.  Tiles of 4 loads, and tiles split over several
+// waves, measured level or slower with a cap, and so did workgroups whose waves
+// do not make 16 (five heads: 647 at 24 waves, 755 at 15).
+int gather_workgroups_per_cu(const HostPlan& hp);
+
 // Validate and build the host side of a plan.  Makes no HIP call.
 pkv_status_t build_host_plan(const pkv_model_t* model, const pkv_request_t* requests, int32_t num_requests,
                              HostPlan* out);
@@ -184,6 +200,16 @@ constexpr int kGatherMaxWaves = 16;
 // pages are looked up in the page table.
 constexpr int kUnitPages = 3;
 int32_t gather_workgroup(const pkv_model_t& m);
+// 16-byte loads per lane that cover a tile.
+int32_t gather_loads(const pkv_model_t& m);
+// Bytes of LDS in which a workgroup of the tile kernel assembles a tile of
+// every head's codes before it writes them as one run; 0 where a workgroup is
+// not one wave per head, a tile is more than 8 loads per lane or its 8-bit
+// image more than kTileImageMax.  (Larger tiles staged whole in a workgroup
+// per CU ran 18-20% slower on the 70B-shaped write: the barrier left the CU
+// without loads in flight while it wrote.)
+constexpr uint32_t kTileImageMax = 64u << 10;
+uint32_t gather_image(const pkv_model_t& m);
 
 // The plan object behind pkv_plan_t (host metadata + one device allocation).
 }  // namespace pkv
@@ -194,9 +220,9 @@ struct pkv_plan {
   double* d_tables = nullptr;
   int32_t* d_page_tables = nullptr;
   int device = -1;
-  // Dynamic LDS bytes per restore workgroup, sized so that at most
-  // restore_workgroups_per_cu() workgroups are resident on a compute unit.
-  uint32_t restore_lds = 0;
+  // LDS bytes a workgroup claims so that at most restore_workgroups_per_cu() or
+  // gather_workgroups_per_cu() of them are resident on a compute unit (0: no cap).
+  uint32_t cap_lds = 0;
   // Restore launches of at most this many units (a few rounds of compute
   // units x restore_workgroups_per_cu() resident workgroups; every launch for
   // rows narrow enough for workgroups under kWorkgroup threads) take the late

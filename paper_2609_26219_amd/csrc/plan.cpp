@@ -416,6 +416,24 @@ int32_t gather_workgroup(const pkv_model_t& m) {
   return 64 * std::min<int32_t>(m.num_kv_heads, kGatherMaxWaves);
 }
 
+int32_t gather_loads(const pkv_model_t& m) {
+  const int32_t rows = 64 / (m.head_dim / 8);  // per load
+  return (m.block_tokens + rows - 1) / rows;
+}
+
+uint32_t gather_image(const pkv_model_t& m) {
+  const uint64_t image = uint64_t(m.block_tokens) * m.num_kv_heads * m.head_dim;
+  return gather_loads(m) <= 8 && m.num_kv_heads <= kGatherMaxWaves && image <= kTileImageMax ? uint32_t(image) : 0;
+}
+
+int gather_workgroups_per_cu(const HostPlan& hp) {
+  const pkv_plan_info_t& info = hp.info;
+  const int waves = hp.workgroup / 64;
+  if (gather_image(hp.model) == 0 || gather_loads(hp.model) <= 4 || 16 % waves != 0 || info.bytes_read == 0) return 0;
+  const double ratio = double(info.bytes_written) / double(info.bytes_read);
+  return ratio >= 0.4 && ratio <= 0.85 ? 16 / waves : 0;
+}
+
 pkv_status_t build_checkpoint_plan(const pkv_model_t* model, const pkv_checkpoint_request_t* requests,
                                    int32_t num_requests, HostPlan* out) {
   pkv_status_t st = check_model(model);

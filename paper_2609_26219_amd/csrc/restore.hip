@@ -597,17 +597,20 @@ pkv_status_t upload_plan(HostPlan&& hp, pkv_plan** out) {
   }
   plan->device = dev;
   plan->host.info.device = dev;
-  // Residency cap through LDS: each restore workgroup claims a share of the
-  // compute unit's LDS (it needs only its table) so that no more than
-  // restore_workgroups_per_cu() fit.
+  // Residency cap through LDS: each workgroup claims a share of the compute
+  // unit's LDS (it needs only its table, or its tile's image) so that no more
+  // than restore_workgroups_per_cu() or gather_workgroups_per_cu() fit.
   int lds_cu = 0, lds_wg = 0;
   if (hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) == hipSuccess &&
       hipDeviceGetAttribute(&lds_wg, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && lds_cu > 0) {
-    const int64_t table = int64_t(kMaxHeadDim) * int64_t(sizeof(double));
-    const int64_t n = restore_workgroups_per_cu(plan->host);
-    const int64_t share = (int64_t(lds_cu) / n + int64_t(lds_cu) / (n + 1)) / 2;
-    const int64_t dyn = std::min<int64_t>((share - table) & ~int64_t(255), int64_t(lds_wg) - table);
-    plan->restore_lds = n < 16 / std::max(1, plan->host.workgroup / 64) && dyn > 0 ? uint32_t(dyn) : 0;
+    const bool write = plan->host.kind == 1;
+    const int64_t fixed = write ? 0 : int64_t(kMaxHeadDim) * int64_t(sizeof(double));
+    const int64_t n = write ? gather_workgroups_per_cu(plan->host) : restore_workgroups_per_cu(plan->host);
+    if (n > 0 && n < 16 / std::max(1, plan->host.workgroup / 64) + (write ? 1 : 0)) {
+      const int64_t share = (int64_t(lds_cu) / n + int64_t(lds_cu) / (n + 1)) / 2;
+      const int64_t dyn = std::min<int64_t>((share - fixed) & ~int64_t(255), int64_t(lds_wg) - fixed);
+      plan->cap_lds = dyn > 0 ? uint32_t(dyn) : 0;
+    }
   } else {
     (void)hipGetLastError();
   }
@@ -751,7 +754,7 @@ pkv_status_t launch_restore(const pkv_plan* plan, const void* payload, const voi
   const bool bf16 = m.out_dtype == PKV_OUT_BF16, half = m.rope_style == PKV_ROPE_HALF;
   const int order = g_restore_order.load(std::memory_order_relaxed);
   const bool late = order == 2 || (order == 0 && n <= plan->restore_late_units);
-  const uint32_t lds = plan->restore_lds;
+  const uint32_t lds = plan->cap_lds;
   if (late) {
     if (bf16 && half)
       hipLaunchKernelGGL((restore_kernel<true, PKV_ROPE_HALF, true>), grid, block, lds, stream, a);
