@@ -49,7 +49,9 @@ namespace pkv {
 namespace {
 
 struct GatherArgs {
-  const Unit* units;
+  const Unit* units;  // of one layer
+  LayerItems items;
+  Divider heads;      // H
   const int32_t* page_tables;
   const uint16_t* k_cache;
   const uint16_t* v_cache;
@@ -181,7 +183,9 @@ __device__ __forceinline__ uint4 to_half8(const uint4& w) {
 struct TileLane {
   const uint16_t* src;  // cache + layer + head + lane's channel piece
   uint8_t* tile;        // the tile's first byte
-  int64_t row0, pt_off, row_elems, slot_mask;
+  const int32_t* pages; // page table from the block's first page on
+  int64_t row_elems;
+  uint32_t slot0, slot_mask;
   int32_t r, c, n_valid, log2P;
   bool on;              // lane holds a piece of a row
 };
@@ -193,31 +197,32 @@ __device__ __forceinline__ void load_chunk(const GatherArgs& a, const TileLane& 
     const int t = (ch * NL + i) * a.rpl + L.r;
     w[i] = make_uint4(0, 0, 0, 0);
     if (L.on && t < L.n_valid) {
-      const int64_t row = L.row0 + t;
-      const int64_t page = a.page_tables[L.pt_off + (row >> L.log2P)];
-      w[i] = *reinterpret_cast<const uint4*>(L.src + ((page << a.page_shift) | (row & L.slot_mask)) * L.row_elems);
+      const uint32_t pos = L.slot0 + uint32_t(t);
+      const int64_t page = L.pages[pos >> L.log2P];
+      w[i] = *reinterpret_cast<const uint4*>(L.src + ((page << a.page_shift) | (pos & L.slot_mask)) * L.row_elems);
     }
   }
 }
 
 template <bool BF16, int NL>
-__device__ void encode_tile(const GatherArgs& a, const Unit& u, int which, int head, int r, int c, bool on) {
-  const int tag = u.tag & 0xFF;
+__device__ void encode_tile(const GatherArgs& a, const Unit& u, uint32_t layer, int which, int head, int r, int c,
+                            bool on) {
+  const int tag = unit_tag(u);
   const int bits = which ? kValueBits[tag] : kKeyBits[tag];
   const int H = a.H, D = a.D;
   TileLane L;
-  L.src = (which ? a.v_cache : a.k_cache) + int64_t(u.layer) * a.layer_elems + int64_t(head) * D + 8 * c;
-  L.tile = a.payload + (which ? u.v_off : u.k_off);
-  L.row0 = u.row0;
-  L.pt_off = u.pt_off;
+  L.src = (which ? a.v_cache : a.k_cache) + int64_t(layer) * a.layer_elems + int64_t(head) * D + 8 * c;
+  L.tile = a.payload + (which ? unit_v_off(u, layer) : unit_k_off(u, layer));
+  L.pages = a.page_tables + u.ref;
   L.row_elems = int64_t(H) * D;
-  L.slot_mask = (int64_t(1) << a.log2P) - 1;
+  L.slot0 = uint32_t(u.slot0);
+  L.slot_mask = (1u << a.log2P) - 1;
   L.r = r;
   L.c = c;
-  L.n_valid = u.n_valid;
+  L.n_valid = unit_tokens_of(u);
   L.log2P = a.log2P;
   L.on = on;
-  uint32_t* scale_word = reinterpret_cast<uint32_t*>(a.scales + u.scale_off + 4 * head + 2 * which);
+  uint32_t* scale_word = reinterpret_cast<uint32_t*>(a.scales + unit_scale_off(u, layer) + 4 * head + 2 * which);
   const bool lane0 = (threadIdx.x & 63) == 0;
   uint4 w[NL];
 
@@ -295,8 +300,9 @@ __device__ void encode_tile(const GatherArgs& a, const Unit& u, int which, int h
 
 template <bool BF16, int NL>
 __global__ __launch_bounds__(kGatherMaxWaves * 64) void gather_kernel(GatherArgs a) {
-  const int64_t g = xcd_grouped(blockIdx.x, gridDim.x);
-  const Unit u = a.units[g >> 1];
+  const uint32_t g = uint32_t(xcd_grouped(blockIdx.x, gridDim.x));
+  const uint32_t layer = layer_of(a.items, g >> 1);
+  const Unit u = a.units[(g >> 1) - layer * a.items.count.d];
   const int which = int(g & 1);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -304,7 +310,7 @@ __global__ __launch_bounds__(kGatherMaxWaves * 64) void gather_kernel(GatherArgs
   const int r = lane / a.lpr;
   const int c = lane - r * a.lpr;
   const bool on = r < a.rpl;
-  for (int head = wave; head < a.H; head += nwaves) encode_tile<BF16, NL>(a, u, which, head, r, c, on);
+  for (int head = wave; head < a.H; head += nwaves) encode_tile<BF16, NL>(a, u, layer, which, head, r, c, on);
 }
 
 // Loads per lane and pass of the general kernel.
@@ -345,7 +351,7 @@ __device__ __forceinline__ void wave_range(float& mn, float& mx) {
 
 struct TileArgs {
   GatherArgs g;
-  int64_t num_tiles;     // units * 2 * H
+  uint32_t num_tiles;    // items * 2 * H (a grid is below 2^32 threads, so 64 times fewer tiles)
   int32_t split, group;  // split kernel: waves per tile, tiles per workgroup
 };
 
@@ -356,34 +362,33 @@ struct TileHdr {
   uint8_t* tile;
   uint32_t tile_bytes;  // B * H * D * bits / 8
   uint32_t* scale_word;
-  int64_t row0;
+  uint32_t slot0;       // the block's first row within its first page
   int32_t n_valid, bits, head;
   int32_t page0, page1, page2;  // kUnitPages source pages
   const int32_t* pages;         // the request's page table from the block's first page on
 };
 
-__device__ __forceinline__ TileHdr tile_header(const GatherArgs& a, const Unit* __restrict__ units, int64_t T) {
-  const int64_t per_unit = 2 * int64_t(a.H);
-  const int64_t ui = T / per_unit;
-  const int32_t rest = int32_t(T - ui * per_unit);
-  const int32_t which = rest >= a.H ? 1 : 0;
-  const int32_t head = rest - which * a.H;
-  const Unit u = units[ui];
-  const int tag = u.tag & 0xFF;
+// Tile (work item, K|V, head); `kv` is 2 * item + (V).
+__device__ __forceinline__ TileHdr tile_header(const GatherArgs& a, const Unit* __restrict__ units, uint32_t kv,
+                                               int32_t head) {
+  const uint32_t layer = layer_of(a.items, kv >> 1);
+  const bool which = (kv & 1) != 0;
+  const Unit u = units[(kv >> 1) - layer * a.items.count.d];
+  const int tag = unit_tag(u);
   TileHdr h;
-  h.src = (which ? a.v_cache : a.k_cache) + int64_t(u.layer) * a.layer_elems + int64_t(head) * a.D;
+  h.src = (which ? a.v_cache : a.k_cache) + int64_t(layer) * a.layer_elems + int64_t(head) * a.D;
   h.range = uint32_t((a.layer_elems - int64_t(head) * a.D) * 2);
-  h.tile = a.payload + (which ? u.v_off : u.k_off);
-  h.scale_word = reinterpret_cast<uint32_t*>(a.scales + u.scale_off + 4 * head + 2 * which);
-  h.row0 = u.row0;
-  h.n_valid = u.n_valid;
+  h.tile = a.payload + (which ? unit_v_off(u, layer) : unit_k_off(u, layer));
+  h.scale_word = reinterpret_cast<uint32_t*>(a.scales + unit_scale_off(u, layer) + 4 * head + (which ? 2 : 0));
+  h.slot0 = uint32_t(u.slot0);
+  h.n_valid = unit_tokens_of(u);
   h.bits = which ? kValueBits[tag] : kKeyBits[tag];
   h.tile_bytes = uint32_t(a.B) * uint32_t(a.H) * uint32_t(a.D) * uint32_t(h.bits) / 8u;
   h.head = head;
-  h.page0 = __builtin_amdgcn_readfirstlane(u.page0);
-  h.page1 = __builtin_amdgcn_readfirstlane(u.page1);
-  h.page2 = __builtin_amdgcn_readfirstlane(u.page2);
-  h.pages = a.page_tables + u.pt_off + (u.row0 >> a.log2P);
+  h.page0 = u.page0;
+  h.page1 = u.page1;
+  h.page2 = u.page2;
+  h.pages = a.page_tables + u.ref;
   return h;
 }
 
@@ -417,7 +422,7 @@ template <int NL, bool WIDE>
 __device__ __forceinline__ void load_tile(const GatherArgs& a, const TileHdr& h, int t_base, int r, int c,
                                           uint4 (&w)[NL]) {
   const uint32_t slot_mask = (1u << a.log2P) - 1;
-  const uint32_t slot0 = uint32_t(h.row0) & slot_mask;  // the block's first row within its first page
+  const uint32_t slot0 = h.slot0;
   if constexpr (WIDE) {
     const int64_t row_elems = int64_t(a.H) * a.D;
     int32_t page[NL];
@@ -578,10 +583,16 @@ __global__ __launch_bounds__(kGatherMaxWaves * 64) void gather_tile_kernel(TileA
   const int r = lane / a.lpr;
   const int c = lane - r * a.lpr;
   const bool on = r < a.rpl;
-  const int64_t T =
-      xcd_grouped(blockIdx.x, gridDim.x) * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (T >= s.num_tiles) return;
-  const TileHdr h = tile_header(a, units, T);
+  const uint32_t b = uint32_t(xcd_grouped(blockIdx.x, gridDim.x));
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t kv = b, head = wave;  // staged: a workgroup is the heads of one (unit, K|V)
+  if constexpr (!STAGE) {
+    const uint32_t T = b * (blockDim.x >> 6) + wave;
+    if (T >= s.num_tiles) return;
+    kv = divide(a.heads, T);
+    head = T - kv * a.heads.d;
+  }
+  const TileHdr h = tile_header(a, units, kv, int32_t(head));
   uint4 w[NL];
   load_tile<NL, WIDE>(a, h, 0, r, c, w);
   const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(h.tile, 0, h.tile_bytes, 0x00020000);
@@ -629,9 +640,10 @@ __global__ __launch_bounds__(kGatherMaxWaves * 64) void gather_split_kernel(Tile
   const bool on = r < a.rpl;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int local = wave / s.split, part = wave - local * s.split;
-  const int64_t T = xcd_grouped(blockIdx.x, gridDim.x) * s.group + local;
+  const uint32_t T = uint32_t(xcd_grouped(blockIdx.x, gridDim.x)) * uint32_t(s.group) + uint32_t(local);
   const bool live = T < s.num_tiles;  // uniform per wave; every wave still passes the barrier
-  const TileHdr h = tile_header(a, units, live ? T : 0);
+  const uint32_t kv = live ? divide(a.heads, T) : 0;
+  const TileHdr h = tile_header(a, units, kv, live ? int32_t(T - kv * a.heads.d) : 0);
   const int t_base = part * NL * a.rpl;
   uint4 w[NL];
   load_tile<NL, WIDE>(a, h, t_base, r, c, w);
@@ -662,8 +674,8 @@ __global__ __launch_bounds__(kGatherMaxWaves * 64) void gather_split_kernel(Tile
 
 template <bool BF16, bool WIDE, int NL>
 void launch_tile(const TileArgs& s, const Unit* units, int wg, uint32_t image, uint32_t cap, hipStream_t stream) {
-  const int64_t waves = wg / 64;
-  const dim3 grid(static_cast<uint32_t>((s.num_tiles + waves - 1) / waves));
+  const uint32_t waves = uint32_t(wg) / 64;
+  const dim3 grid((s.num_tiles + waves - 1) / waves);
   if (image)
     hipLaunchKernelGGL((gather_tile_kernel<BF16, NL, true, WIDE>), grid, dim3(wg), std::max(image, cap), stream, s,
                        units);
@@ -679,7 +691,7 @@ void launch_tiles(TileArgs s, const Unit* units, int nload, int wg, uint32_t ima
   if (nload <= 8) return launch_tile<BF16, WIDE, 8>(s, units, wg, image, cap, stream);
   s.split = (nload + kSplitLoads - 1) / kSplitLoads;
   s.group = s.split < kSplitWaves ? kSplitWaves / s.split : 1;
-  const dim3 grid(static_cast<uint32_t>((s.num_tiles + s.group - 1) / s.group)), block(64 * s.split * s.group);
+  const dim3 grid((s.num_tiles + s.group - 1) / s.group), block(64 * s.split * s.group);
   hipLaunchKernelGGL((gather_split_kernel<BF16, WIDE>), grid, block, 0, stream, s, units);
 }
 
@@ -738,6 +750,8 @@ pkv_status_t pkv_quantize_gather(const pkv_plan_t* plan, const void* k_cache, co
   const pkv_model_t& m = plan->host.model;
   pkv::GatherArgs a;
   a.units = plan->d_units;
+  a.items = pkv::layer_items(0, m.num_layers, plan->host.layer_units);
+  a.heads = pkv::divider(uint32_t(m.num_kv_heads));
   a.page_tables = plan->d_page_tables;
   a.k_cache = static_cast<const uint16_t*>(k_cache);
   a.v_cache = static_cast<const uint16_t*>(v_cache);
@@ -756,9 +770,11 @@ pkv_status_t pkv_quantize_gather(const pkv_plan_t* plan, const void* k_cache, co
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const bool bf16 = m.out_dtype == PKV_OUT_BF16;
   if (nload <= pkv::kSplitLoads * pkv::kGatherMaxWaves) {
+    const int64_t tiles = info.num_units * 2 * m.num_kv_heads;
+    if (tiles * 64 >= (int64_t(1) << 32)) return PKV_ERR_DEVICE;  // no grid holds them
     pkv::TileArgs sa;
     sa.g = a;
-    sa.num_tiles = info.num_units * 2 * m.num_kv_heads;
+    sa.num_tiles = uint32_t(tiles);
     sa.split = sa.group = 1;
     // Blocks on more than kUnitPages pages, and layer slices whose rows are
     // out of a 32-bit offset's reach, look their pages up (load_tile).

@@ -37,32 +37,102 @@ constexpr int kUnitElems = 16384;
 constexpr int kKeyBits[4] = {16, 8, 8, 4};
 constexpr int kValueBits[4] = {16, 8, 4, 4};
 
-// One work item.  Restore: every head of up to `n_valid` consecutive tokens
-// of one reused block of one layer of one request.  Checkpoint write: one
-// whole block of one layer of one request.  64 bytes.
+// Division of 32-bit numbers by a divisor known on the host, by a
+// multiplication: with m = ceil(2^64 / d), floor(x / d) is the high word of
+// x * m, exactly, for every x below 2^32 (the error x * (m * d - 2^64) stays
+// below 2^64).  m = 0 stands for d = 1.
+struct Divider {
+  uint64_t m;
+  uint32_t d;
+};
+constexpr Divider divider(uint32_t d) { return Divider{d == 1 ? 0 : ~uint64_t(0) / d + 1, d}; }
+constexpr uint32_t divide(const Divider& v, uint32_t x) {
+  return v.m == 0 ? x : uint32_t(((v.m >> 32) * x + ((v.m & 0xFFFFFFFFu) * x >> 32)) >> 32);
+}
+
+// The work items of a launch: `count` to a layer, from layer `first` on.  (A
+// launch of one layer skips the division: it is on the way to the first load.)
+struct LayerItems {
+  Divider count;
+  uint32_t first, layers;
+};
+constexpr LayerItems layer_items(int64_t first, int64_t layers, int64_t count) {
+  return LayerItems{divider(uint32_t(count)), uint32_t(first), uint32_t(layers)};
+}
+constexpr uint32_t layer_of(const LayerItems& v, uint32_t item) { return v.layers == 1 ? 0 : divide(v.count, item); }
+
+// One work item of one layer.  Restore: every head of up to n_valid consecutive
+// tokens of one reused block of one request.  Checkpoint write: one whole block
+// of one request.  The checkpoint and the caches repeat themselves layer by
+// layer, so a plan holds the work items of layer 0 and the strides that lead to
+// the other layers: work item w of a launch is item w % count of its layer
+// w / count (LayerItems).  64 bytes.  (A list of every layer's items took 0.5-2 ms to build
+// and upload for the 32- and 80-layer models, as long as the restore itself,
+// and was read from HBM; one layer's takes 0.03-0.05 ms and stays in the L2s.)
 struct Unit {
-  uint64_t k_off;      // byte offset of the unit's first K row in the payload
-  uint64_t v_off;      // byte offset of its first V row
-  uint64_t scale_off;  // binary16-element offset of the block's (head 0, K, scale) entry
-  int64_t row0;        // logical row of the unit's first token (destination / old context)
-  int64_t pt_off;      // offset, in int32, of the request's page table
-  union {
-    int32_t table_off;  // restore: offset, in doubles, of the request's [D/2][2] (cos, sin) table
-    int32_t page0;      // checkpoint: physical page of logical page row0 >> log2(P)
-  };
-  int32_t layer;
-  int32_t tag;         // bits 0-7: pkv_tag_t; bit 8: rotate keys (Delta != 0)
-  int32_t n_valid;     // tokens in the unit
-  int32_t page1;       // checkpoint: the next two physical pages of the block's rows, -1 past its
-  int32_t page2;       //   last page; restore: page1 = the one physical page of the unit's rows, page2 = 0
+  uint64_t k_off;           // byte offset of the unit's first K row in the payload, layer 0
+  uint64_t v_off;           // byte offset of its first V row, layer 0
+  uint64_t scale_off;       // binary16-element offset of the block's (head 0, K, scale) entry, layer 0
+  uint64_t payload_stride;  // payload bytes from one layer of the request to the next
+  uint64_t meta;            // unit_meta(): tokens, tag, rotation, scale stride
+  int64_t ref;              // restore: offset, in doubles, of the request's [D/2][2] (cos, sin) table;
+                            //   checkpoint: index of the block's first page in the page tables
+  int32_t slot0;            // slot of the unit's first row in its (first) page
+  int32_t page0;            // physical page of the unit's rows, or of a checkpoint block's first rows
+  int32_t page1, page2;     // checkpoint: the block's next two physical pages, -1 past its last page
 };
 static_assert(sizeof(Unit) == 64, "Unit layout");
-constexpr int32_t kUnitRotate = 1 << 8;
 
-// Per-request metadata kept on the host.
-struct ReqInfo {
-  int64_t table_off;  // offset, in doubles, of the request's table
-  int64_t pt_off;     // offset, in int32, of the request's page table
+// meta: bits 0-10 tokens of the unit, 11-12 pkv_tag_t, 13 rotate keys (Delta != 0),
+// 16-63 the request's (block, head) pairs: the scale entries of one layer, four elements each.
+constexpr uint64_t unit_meta(int64_t n_valid, int tag, bool rotate, uint64_t scale_entries) {
+  return uint64_t(n_valid) | uint64_t(tag) << 11 | uint64_t(rotate) << 13 | scale_entries << 16;
+}
+constexpr int32_t unit_tokens_of(const Unit& u) { return int32_t(u.meta & 0x7FF); }
+constexpr int32_t unit_tag(const Unit& u) { return int32_t(u.meta >> 11 & 3); }
+constexpr bool unit_rotates(const Unit& u) { return (u.meta >> 13 & 1) != 0; }
+constexpr uint64_t unit_k_off(const Unit& u, uint32_t layer) { return u.k_off + layer * u.payload_stride; }
+constexpr uint64_t unit_v_off(const Unit& u, uint32_t layer) { return u.v_off + layer * u.payload_stride; }
+constexpr uint64_t unit_scale_off(const Unit& u, uint32_t layer) { return u.scale_off + layer * (u.meta >> 16 << 2); }
+
+#ifdef __HIPCC__
+// sizeof(T) / 64 scalar loads of 64 bytes from `p`, all of them in registers
+// before anything that uses them (the empty asm).  A workgroup's first load of
+// data waits for its launch arguments and then for its work item.  Left alone
+// the compiler loads both piece by piece, each where it is first used, seven
+// scalar loads one behind the other; in one go each, the restore of one layer
+// (690 workgroups) takes 10.4 us against 10.7.
+typedef uint32_t ScalarLine __attribute__((ext_vector_type(16), aligned(4)));
+template <typename T>
+__device__ __forceinline__ T load_scalars(const __attribute__((address_space(4))) void* p) {
+  static_assert(sizeof(T) == 64 || sizeof(T) == 128, "whole 64-byte loads");
+  const auto* lines = static_cast<const __attribute__((address_space(4))) ScalarLine*>(p);
+  if constexpr (sizeof(T) == 64) {
+    ScalarLine a = lines[0];
+    asm volatile("" : "+s"(a));
+    return __builtin_bit_cast(T, a);
+  } else {
+    struct {
+      ScalarLine a, b;
+    } v{lines[0], lines[1]};
+    asm volatile("" : "+s"(v.a), "+s"(v.b));
+    return __builtin_bit_cast(T, v);
+  }
+}
+// A kernel's arguments (its one parameter, of type T), and a work item.
+template <typename T>
+__device__ __forceinline__ T launch_args() {
+  return load_scalars<T>((const __attribute__((address_space(4))) void*)__builtin_amdgcn_kernarg_segment_ptr());
+}
+__device__ __forceinline__ Unit load_unit(const Unit* u) {
+  return load_scalars<Unit>((const __attribute__((address_space(4))) void*)(reinterpret_cast<uintptr_t>(u)));
+}
+#endif
+
+// Where a unit sits in its request, kept only for the test hooks.
+struct UnitRows {
+  int64_t row0;    // logical row of the unit's first token (destination / old context)
+  int64_t pt_off;  // index of the request's first page-table entry
 };
 
 struct CopyRange {
@@ -99,23 +169,41 @@ constexpr uint64_t kHostChunkBytes = PKV_HOST_CHUNK_BYTES;
 constexpr uint64_t kStagePayloadBytes = 64ull << 20;
 constexpr uint64_t kStageScaleBytes = 4ull << 20;
 
-// One step of that restore, all on the caller's stream: copy the step's
-// scales (if any) and payload ranges from host memory into the stage, then
-// restore units [u0, u1) -- one layer of one request -- whose K rows start in
-// payload bytes [win_lo, win_hi).  A window holds the most consecutive reused
-// blocks, in payload order, that span at most kStagePayloadBytes; payload
-// byte o of the window sits at stage offset o - win_lo.
-struct StageStep {
-  int64_t u0, u1;
-  uint64_t win_lo, win_hi;  // absolute payload bytes
-  uint64_t scale0;          // absolute binary16 element of the request-layer's scales
-  uint64_t scale_elems;     // elements staged before this step (0: none; the stage already holds them)
-  int64_t copy0, copy1;     // its payload copies in HostPlan::stage_copies
+// One window of that restore, of one request, relative to a layer's payload:
+// the most consecutive reused blocks, in payload order, that span at most
+// kStagePayloadBytes.  Payload byte o of the window sits at stage offset
+// o - lo.  For each layer and request in turn, all on the caller's stream: the
+// request-layer's scales and then each window's copies go from host memory into
+// the stage, and the units whose K rows start in the window are restored.
+struct StageWindow {
+  uint64_t lo, hi;
+  int64_t copy0, copy1;  // its payload copies in RequestCopies::stage_copies
 };
 struct StageCopy {
-  uint64_t src;  // absolute payload byte offset
+  uint64_t src;  // payload byte offset from the layer's start
   uint64_t dst;  // byte offset into the stage
   uint64_t len;
+};
+
+struct RequestCopies;
+// One window of one layer, in absolute checkpoint offsets.
+struct StageStep {
+  uint64_t payload_base;    // payload byte the window's copies are relative to
+  uint64_t win_lo, win_hi;  // payload bytes
+  uint64_t scale0;          // binary16 element of the request-layer's scales
+  uint64_t scale_elems;     // elements staged before this step (0: none; the stage already holds them)
+};
+StageStep stage_step(const RequestCopies& rc, int64_t l, size_t window);
+
+// What the host-memory restores move for one request, the same in every layer.
+struct RequestCopies {
+  uint64_t payload_offset, layer_bytes;  // bytes
+  uint64_t scale_offset, layer_scales;   // binary16 elements
+  bool scales_needed;                    // some reused block is quantized
+  int64_t unit0, unit1;                  // the request's units of a layer
+  std::vector<CopyRange> ranges;         // merged payload copies, from the layer's start, ascending
+  std::vector<StageWindow> windows;
+  std::vector<StageCopy> stage_copies;
 };
 
 // Everything the plan needs on the device, built on the host.
@@ -123,28 +211,24 @@ struct HostPlan {
   int32_t kind = 0;  // 0 = restore, 1 = checkpoint write
   int32_t workgroup = kWorkgroup;
   pkv_model_t model;
-  std::vector<Unit> units;
-  std::vector<ReqInfo> reqs;
+  std::vector<Unit> units;         // of one layer, request by request
   std::vector<double> tables;      // per request [D/2][2]
-  std::vector<int32_t> page_tables;
+  std::vector<int32_t> page_tables;  // checkpoint plans
   pkv_plan_info_t info;
   int32_t log2_page;
-  // Restore plans: units are layer-major; layer l owns units
-  // [layer_units[l], layer_units[l + 1]).  Host -> device copy ranges of the
-  // streamed restore, merged, layer-major: payload bytes and scale bytes,
-  // layer l owning [*_layer[l], *_layer[l + 1]).  Kept on the host.
-  std::vector<int64_t> layer_units;
-  std::vector<CopyRange> payload_ranges, scale_ranges;
-  std::vector<int64_t> payload_layer, scale_layer;
+  int64_t layer_units = 0;                  // units.size(), kept when the list itself is dropped
+  std::vector<RequestCopies> copies;        // restore plans, per request
   int64_t rotated_rows = 0;  // restore plans: restored rows whose keys rotate (shift != 0)
   std::vector<uint64_t> req_payload_bytes;  // per request: bytes of its checkpoint payload, all layers
-  // Restore plans: the schedule of the restore staged through the library's
-  // static buffer (add_stage_steps in plan.cpp), or stage_ok = false when a
-  // request-layer's scales do not fit it.
-  std::vector<StageStep> stage_steps;
-  std::vector<StageCopy> stage_copies;
+  // Restore plans: whether every request-layer's scales fit the staged restore's static buffer.
   bool stage_ok = false;
+  bool keep_rows = false;  // test hooks: fill `rows`, one entry per unit
+  std::vector<UnitRows> rows;
 };
+
+// Copies of layer l of a streamed restore, in order: payload byte ranges and
+// scale byte ranges (neighbouring requests' scales as one).
+void layer_copies(const HostPlan& hp, int64_t l, std::vector<CopyRange>& payload, std::vector<CopyRange>& scales);
 
 // Restore workgroups resident per compute unit, chosen per plan: 8 to 16
 // waves (for 4-wave workgroups two to four, one wave per SIMD each; 16 waves

@@ -9,7 +9,6 @@
 #include <cmath>
 #include <limits>
 #include <new>
-#include <tuple>
 #include <vector>
 
 #include "pkv.h"
@@ -100,38 +99,73 @@ uint64_t tile_bytes(const pkv_model_t& m, int bits) {
   return uint64_t(m.block_tokens) * m.num_kv_heads * m.head_dim * bits / 8;
 }
 
-// Steps of the staged restore for the units [u0, u1) of one request-layer:
-// windows of the most consecutive reused blocks (payload order, offsets
-// relative to layer_base) that span at most kStagePayloadBytes (one block,
-// at most 16 MiB, always fits), each with its copies (blocks closer than
-// kHostGapBytes merged); the request-layer's scales, if any, go with the
-// first window.
-void add_stage_steps(HostPlan& hp, const std::vector<CopyRange>& blocks, int64_t u0, int64_t u1, uint64_t layer_base,
-                     uint64_t scale0, uint64_t scale_elems) {
+// Append a range, merging it with the previous one (if that one is at index
+// >= first) when it starts at most `gap` bytes after that one ends.
+void add_range(std::vector<CopyRange>& v, size_t first, uint64_t off, uint64_t len, uint64_t gap) {
+  if (v.size() > first && v.back().off + v.back().len <= off && off - (v.back().off + v.back().len) <= gap)
+    v.back().len = off + len - v.back().off;
+  else
+    v.push_back(CopyRange{off, len});
+}
+
+// Windows of the staged restore for one request: the most consecutive reused
+// blocks (payload order, offsets from the layer's start) that span at most
+// kStagePayloadBytes (one block, at most 16 MiB, always fits), each with its
+// copies (blocks closer than kHostGapBytes merged).
+void add_stage_windows(RequestCopies& rc, const std::vector<CopyRange>& blocks) {
   for (size_t i = 0; i < blocks.size();) {
     const uint64_t lo = blocks[i].off;
     size_t j = i + 1;
     while (j < blocks.size() && blocks[j].off + blocks[j].len - lo <= kStagePayloadBytes) ++j;
-    StageStep st;
-    st.u0 = u0;
-    st.u1 = u1;
-    st.win_lo = layer_base + lo;
-    st.win_hi = layer_base + blocks[j - 1].off + blocks[j - 1].len;
-    st.scale0 = scale0;
-    st.scale_elems = i == 0 ? scale_elems : 0;
-    st.copy0 = int64_t(hp.stage_copies.size());
+    StageWindow w;
+    w.lo = lo;
+    w.hi = blocks[j - 1].off + blocks[j - 1].len;
+    w.copy0 = int64_t(rc.stage_copies.size());
     for (size_t a = i; a < j;) {
       size_t b = a + 1;
       while (b < j && blocks[b].off - (blocks[b - 1].off + blocks[b - 1].len) <= kHostGapBytes) ++b;
       const uint64_t c0 = blocks[a].off, c1 = blocks[b - 1].off + blocks[b - 1].len;
-      hp.stage_copies.push_back(StageCopy{layer_base + c0, c0 - lo, c1 - c0});
+      rc.stage_copies.push_back(StageCopy{c0, c0 - lo, c1 - c0});
       a = b;
     }
-    st.copy1 = int64_t(hp.stage_copies.size());
-    hp.stage_steps.push_back(st);
+    w.copy1 = int64_t(rc.stage_copies.size());
+    rc.windows.push_back(w);
     i = j;
   }
 }
+
+// Marks physical pages as written; a page marked twice is written through two
+// (request, logical page) pairs, since each pair is marked once.  One bit per
+// page of the pool while the pool is not far larger than the pages touched, a
+// sorted list of the pages otherwise.
+class PageOwners {
+ public:
+  PageOwners(int64_t pool_pages, int64_t touched) {
+    if (pool_pages / 1024 <= touched) bits_.assign(size_t(pool_pages + 63) / 64, 0);
+  }
+  void mark(int32_t page) {
+    if (bits_.empty()) {
+      pages_.push_back(page);
+      return;
+    }
+    uint64_t& w = bits_[size_t(page) / 64];
+    const uint64_t bit = uint64_t(1) << (page % 64);
+    twice_ |= (w & bit) != 0;
+    w |= bit;
+  }
+  bool twice() {
+    if (!pages_.empty()) {
+      std::sort(pages_.begin(), pages_.end());
+      twice_ = std::adjacent_find(pages_.begin(), pages_.end()) != pages_.end();
+    }
+    return twice_;
+  }
+
+ private:
+  std::vector<uint64_t> bits_;
+  std::vector<int32_t> pages_;
+  bool twice_ = false;
+};
 
 }  // namespace
 
@@ -206,6 +240,37 @@ uint64_t layer_payload_bytes(const pkv_model_t& m, const uint8_t* tags, int64_t 
   return total;
 }
 
+namespace {
+
+// The scale copies of layer l: each request's layer as one, neighbours merged.
+void layer_scale_copies(const HostPlan& hp, int64_t l, std::vector<CopyRange>& scales) {
+  for (const RequestCopies& rc : hp.copies)
+    if (rc.scales_needed)
+      add_range(scales, 0, (rc.scale_offset + uint64_t(l) * rc.layer_scales) * 2, rc.layer_scales * 2, 0);
+}
+
+}  // namespace
+
+void layer_copies(const HostPlan& hp, int64_t l, std::vector<CopyRange>& payload, std::vector<CopyRange>& scales) {
+  payload.clear();
+  scales.clear();
+  for (const RequestCopies& rc : hp.copies)
+    for (const CopyRange& c : rc.ranges)
+      payload.push_back(CopyRange{rc.payload_offset + uint64_t(l) * rc.layer_bytes + c.off, c.len});
+  layer_scale_copies(hp, l, scales);
+}
+
+StageStep stage_step(const RequestCopies& rc, int64_t l, size_t window) {
+  const StageWindow& w = rc.windows[window];
+  StageStep st;
+  st.payload_base = rc.payload_offset + uint64_t(l) * rc.layer_bytes;
+  st.win_lo = st.payload_base + w.lo;
+  st.win_hi = st.payload_base + w.hi;
+  st.scale0 = rc.scales_needed ? rc.scale_offset + uint64_t(l) * rc.layer_scales : 0;
+  st.scale_elems = rc.scales_needed && window == 0 ? rc.layer_scales : 0;
+  return st;
+}
+
 pkv_status_t build_host_plan(const pkv_model_t* model, const pkv_request_t* requests, int32_t num_requests,
                              HostPlan* out) {
   pkv_status_t st = check_model(model);
@@ -222,65 +287,58 @@ pkv_status_t build_host_plan(const pkv_model_t* model, const pkv_request_t* requ
     const int64_t nb = ceil_div(q.suffix_tokens, B);
     if ((st = check_tags(q, nb)) != PKV_OK) return st;
   }
-  // Every page touched by a row of a reused block: in range and mapped;
-  // collect (physical page, request, logical page) for the ownership check.
-  std::vector<std::tuple<int64_t, int32_t, int64_t>> touched;
-  for (int32_t r = 0; r < num_requests; ++r) {
-    const pkv_request_t& q = requests[r];
-    const int64_t nb = ceil_div(q.suffix_tokens, B);
-    int64_t last_lp = -1;
-    for (int64_t b = 0; b < nb; ++b) {
-      if (q.repair_mask[b]) continue;
-      const int64_t n_valid = std::min<int64_t>(B, q.suffix_tokens - b * B);
-      const int64_t first_row = q.dst_row0 + b * B;
-      const int64_t last_row = first_row + n_valid - 1;
-      for (int64_t lp = std::max(first_row >> lp2, last_lp + 1); lp <= (last_row >> lp2); ++lp) {
-        if (lp >= q.num_logical_pages) return PKV_ERR_PAGE_OUT_OF_RANGE;
-        const int32_t pp = q.page_table[lp];
-        if (pp == -1) return PKV_ERR_PAGE_UNMAPPED;
-        if (pp < -1 || pp >= m.pool_pages) return PKV_ERR_PAGE_OUT_OF_RANGE;
-        touched.emplace_back(pp, r, lp);
-        last_lp = lp;
-      }
-    }
-  }
-  std::sort(touched.begin(), touched.end());
-  for (size_t i = 1; i < touched.size(); ++i) {
-    if (std::get<0>(touched[i]) == std::get<0>(touched[i - 1]) &&
-        (std::get<1>(touched[i]) != std::get<1>(touched[i - 1]) ||
-         std::get<2>(touched[i]) != std::get<2>(touched[i - 1])))
-      return PKV_ERR_PAGE_ALIAS;
-  }
-
-  // Build: tile list, per-request metadata, page tables, cos/sin tables.
   HostPlan& hp = *out;
-  hp.model = m;
-  hp.log2_page = lp2;
-  hp.units.clear();
-  hp.reqs.clear();
-  hp.tables.clear();
-  hp.page_tables.clear();
-  memset(&hp.info, 0, sizeof(hp.info));
-  hp.info.num_requests = num_requests;
-  hp.info.cache_bytes = cache_bytes(m);
-
-  if (int64_t(num_requests) * D > std::numeric_limits<int32_t>::max()) return PKV_ERR_INVALID_ARGUMENT;
   try {
-    hp.reqs.resize(num_requests);
-    hp.req_payload_bytes.assign(size_t(num_requests), 0);
-    hp.stage_steps.clear();
-    hp.stage_copies.clear();
-    hp.tables.resize(size_t(num_requests) * size_t(D));
-    // Per request: page table, cos/sin table, block offsets inside a layer.
-    std::vector<std::vector<uint64_t>> block_off(num_requests);
-    std::vector<uint64_t> layer_bytes(num_requests, 0);
+    // Every page touched by a row of a reused block: in range, mapped, and
+    // written through one (request, logical page) pair only.
+    int64_t pages = 0;
+    for (int32_t r = 0; r < num_requests; ++r) pages += (requests[r].suffix_tokens >> lp2) + 1;
+    PageOwners owners(m.pool_pages, pages);
     for (int32_t r = 0; r < num_requests; ++r) {
       const pkv_request_t& q = requests[r];
       const int64_t nb = ceil_div(q.suffix_tokens, B);
-      ReqInfo& rd = hp.reqs[r];
-      rd.table_off = int64_t(r) * D;
-      rd.pt_off = int64_t(hp.page_tables.size());
-      hp.page_tables.insert(hp.page_tables.end(), q.page_table, q.page_table + q.num_logical_pages);
+      int64_t last_lp = -1;
+      for (int64_t b = 0; b < nb; ++b) {
+        if (q.repair_mask[b]) continue;
+        const int64_t n_valid = std::min<int64_t>(B, q.suffix_tokens - b * B);
+        const int64_t first_row = q.dst_row0 + b * B;
+        const int64_t last_row = first_row + n_valid - 1;
+        for (int64_t lp = std::max(first_row >> lp2, last_lp + 1); lp <= (last_row >> lp2); ++lp) {
+          if (lp >= q.num_logical_pages) return PKV_ERR_PAGE_OUT_OF_RANGE;
+          const int32_t pp = q.page_table[lp];
+          if (pp == -1) return PKV_ERR_PAGE_UNMAPPED;
+          if (pp < -1 || pp >= m.pool_pages) return PKV_ERR_PAGE_OUT_OF_RANGE;
+          owners.mark(pp);
+          last_lp = lp;
+        }
+      }
+    }
+    if (owners.twice()) return PKV_ERR_PAGE_ALIAS;
+    if (int64_t(num_requests) * D > std::numeric_limits<int32_t>::max()) return PKV_ERR_INVALID_ARGUMENT;
+
+    // Build: the work items of one layer, the cos/sin tables, what the
+    // host-memory restores copy.
+    hp.model = m;
+    hp.log2_page = lp2;
+    hp.units.clear();
+    hp.rows.clear();
+    hp.page_tables.clear();
+    memset(&hp.info, 0, sizeof(hp.info));
+    hp.info.num_requests = num_requests;
+    hp.info.cache_bytes = cache_bytes(m);
+    hp.req_payload_bytes.assign(size_t(num_requests), 0);
+    hp.copies.assign(size_t(num_requests), RequestCopies());
+    hp.tables.assign(size_t(num_requests) * size_t(D), 0.0);
+    hp.workgroup = restore_workgroup(m);
+    hp.rotated_rows = 0;
+    hp.stage_ok = true;
+    const int64_t per_unit = unit_tokens(m);
+    std::vector<uint64_t> block_off;
+    std::vector<CopyRange> reused;  // the reused blocks' K + V tiles, payload order
+    int64_t pt_off = 0;
+    for (int32_t r = 0; r < num_requests; ++r) {
+      const pkv_request_t& q = requests[r];
+      const int64_t nb = ceil_div(q.suffix_tokens, B);
       // cos / sin of Delta * f_i in double precision, laid out in the
       // kernel's element order: entry 8j + e is the pair that element e of
       // key piece j rotates (rope_table_pair); pass-through entries are (1, 0).
@@ -290,124 +348,98 @@ pkv_status_t build_host_plan(const pkv_model_t* model, const pkv_request_t* requ
         hp.tables[size_t(r) * D + 2 * k] = q.delta && i >= 0 ? cos(ang) : 1.0;
         hp.tables[size_t(r) * D + 2 * k + 1] = q.delta && i >= 0 ? sin(ang) : 0.0;
       }
-      if (nb == 0) continue;
-      // Block offsets inside one layer: runs by tag, ascending blocks.
-      block_off[r].resize(nb);
-      uint64_t pos = 0;
-      for (int tag = 0; tag < 4; ++tag)
-        for (int64_t b = 0; b < nb; ++b)
-          if (q.tags[b] == tag) {
-            block_off[r][b] = pos;
-            pos += tile_bytes(m, kKeyBits[tag]) + tile_bytes(m, kValueBits[tag]);
-          }
-      layer_bytes[r] = pos;
-      hp.req_payload_bytes[r] = uint64_t(L) * pos;
-      hp.info.payload_bytes = std::max<uint64_t>(hp.info.payload_bytes, q.payload_offset + uint64_t(L) * pos);
-      hp.info.scale_bytes =
-          std::max<uint64_t>(hp.info.scale_bytes, (q.scale_offset + uint64_t(L) * nb * H * 4) * 2);
-    }
-    // Work list, layer-major, and the streamed restore's copy ranges.
-    const int64_t per_unit = unit_tokens(m);
-    hp.workgroup = restore_workgroup(m);
-    // Append a copy, merging it with the previous one (if that one is at
-    // index >= first) when it starts at most `gap` bytes after that one ends.
-    auto add_range = [](std::vector<CopyRange>& v, int64_t first, uint64_t off, uint64_t len, uint64_t gap) {
-      if (int64_t(v.size()) > first && v.back().off + v.back().len <= off &&
-          off - (v.back().off + v.back().len) <= gap)
-        v.back().len = off + len - v.back().off;
-      else
-        v.push_back(CopyRange{off, len});
-    };
-    hp.layer_units.assign(1, 0);
-    hp.payload_layer.assign(1, 0);
-    hp.scale_layer.assign(1, 0);
-    // Staged restore: per request, the reused blocks' K + V tile ranges
-    // relative to a layer's payload start, in payload order.
-    std::vector<std::vector<CopyRange>> reused(static_cast<size_t>(num_requests));
-    std::vector<bool> scales_needed(static_cast<size_t>(num_requests), false);
-    hp.stage_ok = true;
-    for (int32_t r = 0; r < num_requests; ++r) {
-      const pkv_request_t& q = requests[r];
-      const int64_t nb = ceil_div(q.suffix_tokens, B);
-      for (int tag = 0; tag < 4; ++tag)
-        for (int64_t b = 0; b < nb; ++b)
-          if (q.tags[b] == tag && !q.repair_mask[b]) {
-            reused[size_t(r)].push_back(
-                CopyRange{block_off[r][b], tile_bytes(m, kKeyBits[tag]) + tile_bytes(m, kValueBits[tag])});
-            if (tag != PKV_TAG_FP16) scales_needed[size_t(r)] = true;
-          }
-      if (scales_needed[size_t(r)] && uint64_t(nb) * H * 4 * 2 > kStageScaleBytes) hp.stage_ok = false;
-    }
-    for (int64_t l = 0; l < L; ++l) {
-      for (int32_t r = 0; r < num_requests; ++r) {
-        const int64_t u_begin = int64_t(hp.units.size());
-        const pkv_request_t& q = requests[r];
-        const int64_t nb = ceil_div(q.suffix_tokens, B);
-        const ReqInfo& rd = hp.reqs[r];
-        const uint64_t layer_base = q.payload_offset + uint64_t(l) * layer_bytes[r];
-        bool any_quantized = false;
-        // Payload ranges in layout order (runs by tag, ascending blocks) so
-        // that neighbouring reused blocks merge into one copy; merging stays
-        // inside this request's layer, so copies never overlap.
-        const int64_t first_range = int64_t(hp.payload_ranges.size());
-        for (int tag = 0; tag < 4; ++tag)
-          for (int64_t b = 0; b < nb; ++b)
-            if (q.tags[b] == tag && !q.repair_mask[b]) {
-              add_range(hp.payload_ranges, first_range, layer_base + block_off[r][b],
-                        tile_bytes(m, kKeyBits[tag]) + tile_bytes(m, kValueBits[tag]), kHostGapBytes);
-              any_quantized |= tag != PKV_TAG_FP16;
-            }
-        if (any_quantized)
-          add_range(hp.scale_ranges, hp.scale_layer.back(), (q.scale_offset + uint64_t(l) * nb * H * 4) * 2,
-                    uint64_t(nb) * H * 4 * 2, 0);
+      RequestCopies& rc = hp.copies[size_t(r)];
+      rc.unit0 = rc.unit1 = int64_t(hp.units.size());
+      rc.payload_offset = q.payload_offset;
+      rc.scale_offset = q.scale_offset;
+      rc.layer_scales = uint64_t(nb) * H * 4;
+      rc.layer_bytes = 0;
+      rc.scales_needed = false;
+      // Block offsets inside one layer (runs by tag, ascending blocks) and the
+      // reused ones' ranges in that order, so that neighbours merge into one
+      // copy; merging stays inside this request's layer, so copies never overlap.
+      block_off.resize(size_t(nb));
+      reused.clear();
+      for (int tag = 0; tag < 4; ++tag) {
+        const uint64_t len = tile_bytes(m, kKeyBits[tag]) + tile_bytes(m, kValueBits[tag]);
         for (int64_t b = 0; b < nb; ++b) {
-          if (q.repair_mask[b]) continue;
-          const int tag = q.tags[b];
-          const int64_t n_valid = std::min<int64_t>(B, q.suffix_tokens - b * B);
-          // Split the block into units of at most `per_unit` tokens that
-          // never cross a page boundary, so a unit writes slots of one page.
-          // A page's run of rows is cut into equal parts (17 -> 9 + 8, not 16 + 1).
-          for (int64_t t0 = 0, len = 0; t0 < n_valid; t0 += len) {
-            const int64_t run = std::min<int64_t>(P - ((q.dst_row0 + b * B + t0) & (P - 1)), n_valid - t0);
-            len = ceil_div(run, ceil_div(run, per_unit));
-            Unit u;
-            const uint64_t block_base = layer_base + block_off[r][b];
-            u.k_off = block_base + uint64_t(t0) * H * D * kKeyBits[tag] / 8;
-            u.v_off = block_base + tile_bytes(m, kKeyBits[tag]) + uint64_t(t0) * H * D * kValueBits[tag] / 8;
-            u.scale_off = q.scale_offset + (uint64_t(l) * nb + b) * H * 4;
-            u.row0 = q.dst_row0 + b * B + t0;
-            u.pt_off = rd.pt_off;
-            u.table_off = int32_t(rd.table_off);
-            u.layer = int32_t(l);
-            u.tag = tag | (q.delta != 0 ? kUnitRotate : 0);
-            u.n_valid = int32_t(len);
-            u.page1 = q.page_table[(q.dst_row0 + b * B + t0) >> lp2];  // validated above; one page per unit
-            u.page2 = 0;
-            hp.units.push_back(u);
+          if (q.tags[b] != tag) continue;
+          block_off[size_t(b)] = rc.layer_bytes;
+          if (!q.repair_mask[b]) {
+            reused.push_back(CopyRange{rc.layer_bytes, len});
+            add_range(rc.ranges, 0, rc.layer_bytes, len, kHostGapBytes);
+            rc.scales_needed |= tag != PKV_TAG_FP16;
           }
-          hp.info.restored_rows += n_valid;
-          if (q.delta != 0) hp.rotated_rows += n_valid;
-          hp.info.bytes_read += uint64_t(n_valid) * H * D * (kKeyBits[tag] + kValueBits[tag]) / 8;
-          if (tag != PKV_TAG_FP16) hp.info.bytes_read += uint64_t(H) * 4 * 2;
+          rc.layer_bytes += len;
         }
-        if (hp.stage_ok && int64_t(hp.units.size()) > u_begin)
-          add_stage_steps(hp, reused[size_t(r)], u_begin, int64_t(hp.units.size()), layer_base,
-                          scales_needed[size_t(r)] ? (q.scale_offset + uint64_t(l) * nb * H * 4) : 0,
-                          scales_needed[size_t(r)] ? uint64_t(nb) * H * 4 : 0);
       }
-      hp.layer_units.push_back(int64_t(hp.units.size()));
-      hp.payload_layer.push_back(int64_t(hp.payload_ranges.size()));
-      hp.scale_layer.push_back(int64_t(hp.scale_ranges.size()));
+      if (rc.scales_needed && rc.layer_scales * 2 > kStageScaleBytes) hp.stage_ok = false;
+      add_stage_windows(rc, reused);
+      hp.req_payload_bytes[size_t(r)] = uint64_t(L) * rc.layer_bytes;
+      if (nb > 0) {
+        hp.info.payload_bytes =
+            std::max<uint64_t>(hp.info.payload_bytes, q.payload_offset + uint64_t(L) * rc.layer_bytes);
+        hp.info.scale_bytes =
+            std::max<uint64_t>(hp.info.scale_bytes, (q.scale_offset + uint64_t(L) * rc.layer_scales) * 2);
+      }
+      for (int64_t b = 0; b < nb; ++b) {
+        if (q.repair_mask[b]) continue;
+        const int tag = q.tags[b];
+        const int64_t n_valid = std::min<int64_t>(B, q.suffix_tokens - b * B);
+        const uint64_t k_base = q.payload_offset + block_off[size_t(b)];
+        const uint64_t v_base = k_base + tile_bytes(m, kKeyBits[tag]);
+        // Split the block into units of at most `per_unit` tokens that
+        // never cross a page boundary, so a unit writes slots of one page.
+        // A page's run of rows is cut into equal parts (17 -> 9 + 8, not 16 + 1).
+        for (int64_t t0 = 0, len = 0; t0 < n_valid; t0 += len) {
+          const int64_t row = q.dst_row0 + b * B + t0, slot = row & (P - 1);
+          const int64_t run = std::min<int64_t>(P - slot, n_valid - t0);
+          len = ceil_div(run, ceil_div(run, per_unit));
+          Unit u;
+          u.k_off = k_base + uint64_t(t0) * H * D * kKeyBits[tag] / 8;
+          u.v_off = v_base + uint64_t(t0) * H * D * kValueBits[tag] / 8;
+          u.scale_off = q.scale_offset + uint64_t(b) * H * 4;
+          u.payload_stride = rc.layer_bytes;
+          u.meta = unit_meta(len, tag, q.delta != 0, uint64_t(nb) * H);
+          u.ref = int64_t(r) * D;
+          u.slot0 = int32_t(slot);
+          u.page0 = q.page_table[row >> lp2];  // validated above; one page per unit
+          u.page1 = u.page2 = 0;
+          hp.units.push_back(u);
+          if (hp.keep_rows) hp.rows.push_back(UnitRows{row, pt_off});
+        }
+        hp.info.restored_rows += n_valid;
+        if (q.delta != 0) hp.rotated_rows += n_valid;
+        hp.info.bytes_read += uint64_t(n_valid) * H * D * (kKeyBits[tag] + kValueBits[tag]) / 8;
+        if (tag != PKV_TAG_FP16) hp.info.bytes_read += uint64_t(H) * 4 * 2;
+      }
+      rc.unit1 = int64_t(hp.units.size());
+      pt_off += q.num_logical_pages;
     }
-    for (const CopyRange& c : hp.payload_ranges) hp.info.host_copy_bytes += c.len;
-    for (const CopyRange& c : hp.scale_ranges) hp.info.host_copy_bytes += c.len;
-    for (const auto* v : {&hp.payload_ranges, &hp.scale_ranges})
-      for (const CopyRange& c : *v) hp.info.host_copies += int64_t((c.len + kHostChunkBytes - 1) / kHostChunkBytes);
+    // Every layer repeats the one built.
+    hp.layer_units = int64_t(hp.units.size());
+    hp.info.restored_rows *= L;
+    hp.rotated_rows *= L;
+    hp.info.bytes_read *= uint64_t(L);
+    for (const RequestCopies& rc : hp.copies)
+      for (const CopyRange& c : rc.ranges) {
+        hp.info.host_copy_bytes += uint64_t(L) * c.len;
+        hp.info.host_copies += L * int64_t((c.len + kHostChunkBytes - 1) / kHostChunkBytes);
+      }
+    std::vector<CopyRange> scales;
+    for (int64_t l = 0; l < L; ++l) {
+      scales.clear();
+      layer_scale_copies(hp, l, scales);
+      for (const CopyRange& c : scales) {
+        hp.info.host_copy_bytes += c.len;
+        hp.info.host_copies += int64_t((c.len + kHostChunkBytes - 1) / kHostChunkBytes);
+      }
+    }
   } catch (const std::bad_alloc&) {
     return PKV_ERR_OUT_OF_MEMORY;
   }
-  if (hp.units.size() > size_t(std::numeric_limits<int32_t>::max())) return PKV_ERR_INVALID_ARGUMENT;
-  hp.info.num_units = int64_t(hp.units.size());
+  if (hp.layer_units > std::numeric_limits<int32_t>::max() / L) return PKV_ERR_INVALID_ARGUMENT;
+  hp.info.num_units = hp.layer_units * L;
   hp.info.bytes_written = uint64_t(hp.info.restored_rows) * H * D * 2 * 2;
   return PKV_OK;
 }
@@ -489,7 +521,7 @@ pkv_status_t build_checkpoint_plan(const pkv_model_t* model, const pkv_checkpoin
   hp.model = m;
   hp.log2_page = lp2;
   hp.units.clear();
-  hp.reqs.clear();
+  hp.rows.clear();
   hp.tables.clear();
   hp.page_tables.clear();
   memset(&hp.info, 0, sizeof(hp.info));
@@ -516,38 +548,68 @@ pkv_status_t build_checkpoint_plan(const pkv_model_t* model, const pkv_checkpoin
       hp.req_payload_bytes[r] = uint64_t(L) * layer_bytes;
       hp.info.payload_bytes = std::max<uint64_t>(hp.info.payload_bytes, q.payload_offset + uint64_t(L) * layer_bytes);
       hp.info.scale_bytes = std::max<uint64_t>(hp.info.scale_bytes, (q.scale_offset + uint64_t(L) * nb * H * 4) * 2);
-      for (int64_t l = 0; l < L; ++l) {
-        for (int64_t b = 0; b < nb; ++b) {
-          const int tag = q.tags[b];
-          Unit u;
-          u.k_off = q.payload_offset + uint64_t(l) * layer_bytes + block_off[b];
-          u.v_off = u.k_off + tile_bytes(m, kKeyBits[tag]);
-          u.scale_off = q.scale_offset + (uint64_t(l) * nb + b) * H * 4;
-          u.row0 = q.src_row0 + b * B;
-          u.pt_off = pt_off;
-          u.layer = int32_t(l);
-          u.tag = tag;
-          u.n_valid = int32_t(std::min<int64_t>(B, q.suffix_tokens - b * B));
-          const int64_t first = u.row0 >> lp2, last = (u.row0 + u.n_valid - 1) >> lp2;
-          u.page0 = q.page_table[first];
-          u.page1 = first + 1 <= last ? q.page_table[first + 1] : -1;
-          u.page2 = first + 2 <= last ? q.page_table[first + 2] : -1;
-          hp.units.push_back(u);
-        }
-        hp.info.bytes_written += layer_bytes + uint64_t(nb) * H * 4 * 2;
+      for (int64_t b = 0; b < nb; ++b) {
+        const int tag = q.tags[b];
+        const int64_t row = q.src_row0 + b * B, n_valid = std::min<int64_t>(B, q.suffix_tokens - b * B);
+        const int64_t first = row >> lp2, last = (row + n_valid - 1) >> lp2;
+        Unit u;
+        u.k_off = q.payload_offset + block_off[size_t(b)];
+        u.v_off = u.k_off + tile_bytes(m, kKeyBits[tag]);
+        u.scale_off = q.scale_offset + uint64_t(b) * H * 4;
+        u.payload_stride = layer_bytes;
+        u.meta = unit_meta(n_valid, tag, false, uint64_t(nb) * H);
+        u.ref = pt_off + first;
+        u.slot0 = int32_t(row & (P - 1));
+        u.page0 = q.page_table[first];
+        u.page1 = first + 1 <= last ? q.page_table[first + 1] : -1;
+        u.page2 = first + 2 <= last ? q.page_table[first + 2] : -1;
+        hp.units.push_back(u);
+        if (hp.keep_rows) hp.rows.push_back(UnitRows{row, pt_off});
       }
+      hp.info.bytes_written += uint64_t(L) * (layer_bytes + uint64_t(nb) * H * 4 * 2);
       hp.info.restored_rows += int64_t(L) * q.suffix_tokens;
     }
+    hp.layer_units = int64_t(hp.units.size());
   } catch (const std::bad_alloc&) {
     return PKV_ERR_OUT_OF_MEMORY;
   }
-  if (hp.units.size() > size_t(std::numeric_limits<int32_t>::max())) return PKV_ERR_INVALID_ARGUMENT;
-  hp.info.num_units = int64_t(hp.units.size());
+  if (hp.layer_units > std::numeric_limits<int32_t>::max() / L) return PKV_ERR_INVALID_ARGUMENT;
+  hp.info.num_units = hp.layer_units * L;
   hp.info.bytes_read = uint64_t(hp.info.restored_rows) * H * D * 2 * 2;
   return PKV_OK;
 }
 
 }  // namespace pkv
+
+namespace {
+
+// A work item of one layer in full, as the test hooks report it.
+struct UnitView {
+  uint64_t k_off, v_off, scale_off;
+  int64_t row0, pt_off;
+  int32_t table_off;  // checkpoint: the block's first page
+  int32_t layer;
+  int32_t tag;        // bits 0-7: pkv_tag_t; bit 8: rotate keys
+  int32_t n_valid;
+  int32_t page1, page2;  // restore: the unit's page and 0; checkpoint: the block's next two pages
+};
+static_assert(sizeof(UnitView) == 64, "UnitView layout");
+
+// Every layer's work items, in launch order.
+void unit_views(const pkv::HostPlan& hp, void* out) {
+  UnitView* v = static_cast<UnitView*>(out);
+  for (int32_t l = 0; l < hp.model.num_layers; ++l)
+    for (size_t i = 0; i < hp.units.size(); ++i) {
+      const pkv::Unit& u = hp.units[i];
+      const bool write = hp.kind == 1;
+      *v++ = UnitView{pkv::unit_k_off(u, uint32_t(l)), pkv::unit_v_off(u, uint32_t(l)),
+                      pkv::unit_scale_off(u, uint32_t(l)), hp.rows[i].row0, hp.rows[i].pt_off,
+                      write ? u.page0 : int32_t(u.ref), l, pkv::unit_tag(u) | (pkv::unit_rotates(u) ? 256 : 0),
+                      pkv::unit_tokens_of(u), write ? u.page1 : u.page0, write ? u.page2 : 0};
+    }
+}
+
+}  // namespace
 
 extern "C" {
 
@@ -571,11 +633,11 @@ pkv_status_t pkv_internal_host_units(const pkv_model_t* model, const pkv_request
                                      void* units_out, int64_t capacity, int64_t* count) {
   if (!count) return PKV_ERR_INVALID_ARGUMENT;
   pkv::HostPlan hp;
+  hp.keep_rows = true;
   pkv_status_t st = pkv::build_host_plan(model, requests, num_requests, &hp);
   if (st != PKV_OK) return st;
-  *count = int64_t(hp.units.size());
-  if (units_out && capacity >= *count && *count > 0)
-    memcpy(units_out, hp.units.data(), hp.units.size() * sizeof(pkv::Unit));
+  *count = hp.info.num_units;
+  if (units_out && capacity >= *count) unit_views(hp, units_out);
   return PKV_OK;
 }
 
@@ -649,17 +711,22 @@ pkv_status_t pkv_internal_stream_schedule(const pkv_model_t* model, const pkv_re
   pkv::HostPlan hp;
   pkv_status_t st = pkv::build_host_plan(model, requests, num_requests, &hp);
   if (st != PKV_OK) return st;
-  *n_payload = int64_t(hp.payload_ranges.size());
-  *n_scale = int64_t(hp.scale_ranges.size());
-  const size_t L1 = size_t(model->num_layers) + 1;
-  for (size_t i = 0; i < L1; ++i) {
-    layers_out[i] = hp.layer_units[i];
-    layers_out[L1 + i] = hp.payload_layer[i];
-    layers_out[2 * L1 + i] = hp.scale_layer[i];
+  const int64_t L = model->num_layers;
+  std::vector<pkv::CopyRange> payload, scales, all_payload, all_scales;
+  for (int64_t l = 0; l <= L; ++l) {
+    layers_out[l] = l * hp.layer_units;
+    layers_out[L + 1 + l] = int64_t(all_payload.size());
+    layers_out[2 * (L + 1) + l] = int64_t(all_scales.size());
+    if (l == L) break;
+    pkv::layer_copies(hp, l, payload, scales);
+    all_payload.insert(all_payload.end(), payload.begin(), payload.end());
+    all_scales.insert(all_scales.end(), scales.begin(), scales.end());
   }
+  *n_payload = int64_t(all_payload.size());
+  *n_scale = int64_t(all_scales.size());
   if (ranges_out && capacity >= *n_payload + *n_scale) {
     size_t k = 0;
-    for (const auto* v : {&hp.payload_ranges, &hp.scale_ranges})
+    for (const auto* v : {&all_payload, &all_scales})
       for (const pkv::CopyRange& c : *v) {
         ranges_out[2 * k] = c.off;
         ranges_out[2 * k + 1] = c.len;
@@ -682,22 +749,27 @@ pkv_status_t pkv_internal_stage_schedule(const pkv_model_t* model, const pkv_req
   pkv::HostPlan hp;
   pkv_status_t st = pkv::build_host_plan(model, requests, num_requests, &hp);
   if (st != PKV_OK) return st;
-  *n_steps = int64_t(hp.stage_steps.size());
-  *n_copies = int64_t(hp.stage_copies.size());
+  *n_steps = *n_copies = 0;
   *stage_ok = hp.stage_ok ? 1 : 0;
-  if (steps_out && step_capacity >= *n_steps)
-    for (size_t i = 0; i < hp.stage_steps.size(); ++i) {
-      const pkv::StageStep& s = hp.stage_steps[i];
-      const int64_t v[8] = {s.u0, s.u1, int64_t(s.win_lo), int64_t(s.win_hi), int64_t(s.scale0),
-                            int64_t(s.scale_elems), s.copy0, s.copy1};
-      memcpy(steps_out + 8 * i, v, sizeof(v));
-    }
-  if (copies_out && copy_capacity >= *n_copies)
-    for (size_t i = 0; i < hp.stage_copies.size(); ++i) {
-      copies_out[3 * i] = hp.stage_copies[i].src;
-      copies_out[3 * i + 1] = hp.stage_copies[i].dst;
-      copies_out[3 * i + 2] = hp.stage_copies[i].len;
-    }
+  for (int64_t l = 0; hp.stage_ok && l < model->num_layers; ++l)
+    for (const pkv::RequestCopies& rc : hp.copies)
+      for (size_t w = 0; w < rc.windows.size(); ++w) {
+        const pkv::StageStep s = pkv::stage_step(rc, l, w);
+        const int64_t copy0 = *n_copies, u = l * hp.layer_units;
+        for (int64_t c = rc.windows[w].copy0; c < rc.windows[w].copy1; ++c, ++*n_copies)
+          if (copies_out && *n_copies < copy_capacity) {
+            const pkv::StageCopy& cp = rc.stage_copies[size_t(c)];
+            copies_out[3 * *n_copies] = s.payload_base + cp.src;
+            copies_out[3 * *n_copies + 1] = cp.dst;
+            copies_out[3 * *n_copies + 2] = cp.len;
+          }
+        if (steps_out && *n_steps < step_capacity) {
+          const int64_t v[8] = {u + rc.unit0, u + rc.unit1, int64_t(s.win_lo), int64_t(s.win_hi), int64_t(s.scale0),
+                                int64_t(s.scale_elems), copy0, *n_copies};
+          memcpy(steps_out + 8 * *n_steps, v, sizeof(v));
+        }
+        ++*n_steps;
+      }
   return PKV_OK;
 }
 
@@ -707,12 +779,12 @@ pkv_status_t pkv_internal_checkpoint_units(const pkv_model_t* model, const pkv_c
                                            int32_t* workgroup) {
   if (!count || !workgroup) return PKV_ERR_INVALID_ARGUMENT;
   pkv::HostPlan hp;
+  hp.keep_rows = true;
   pkv_status_t st = pkv::build_checkpoint_plan(model, requests, num_requests, &hp);
   if (st != PKV_OK) return st;
-  *count = int64_t(hp.units.size());
+  *count = hp.info.num_units;
   *workgroup = hp.workgroup;
-  if (units_out && capacity >= *count && *count > 0)
-    memcpy(units_out, hp.units.data(), hp.units.size() * sizeof(pkv::Unit));
+  if (units_out && capacity >= *count) unit_views(hp, units_out);
   return PKV_OK;
 }
 

@@ -63,22 +63,26 @@ constexpr int kMinWavesPerEU = 4;
 constexpr int64_t kLateRounds = 6;
 
 struct KernelArgs {
-  const Unit* units;
+  const Unit* units;  // of one layer
+  LayerItems items;
+  uint32_t grid;      // workgroups of the launch
+  int32_t threads;    // threads of a workgroup
   const double* tables;
   const uint8_t* payload;
   const uint16_t* scales;
   uint16_t* k_cache;
   uint16_t* v_cache;
   int64_t layer_elems;  // elements of one layer of a cache: pool_pages * P * H * D, twice that when paired
-  int32_t H, D, log2P, cols, tpp;
-  int32_t cols_shift, dq_shift;  // log2 of cols and of D/16 when they are powers of two, else -1
-  int32_t R;            // rotary channels per head
-  int32_t page_shift;   // slot rows from a layer's start to page p: p << page_shift
+  int32_t H, D, cols, tpp;
+  int32_t R;                    // rotary channels per head
+  int8_t cols_shift, dq_shift;  // log2 of cols and of D/16 when they are powers of two, else -1
+  int8_t page_shift;            // slot rows from a layer's start to page p: p << page_shift
   // Units whose K rows start outside [win_lo, win_hi) payload bytes are
   // skipped (the staged restore runs a request's layer in payload windows);
   // [0, 2^64) everywhere else.
   uint64_t win_lo, win_hi;
 };
+static_assert(sizeof(KernelArgs) == 128, "launch_args");
 
 __device__ __forceinline__ float half_bits_to_float(uint32_t h) {
   return static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(h)));
@@ -341,6 +345,14 @@ __device__ __forceinline__ void value_store(const Chunk8<VBITS>& lo, const Chunk
   store_row_piece<LATE>(dst, doff + D + 16 * j, soff, out_hi);
 }
 
+// A work item of the layer it is restored in.
+struct LayerUnit {
+  uint64_t k_off, v_off, scale_off;
+  int64_t page;     // elements from a cache's start to the unit's page
+  uint32_t slot0;
+  int32_t n_valid;
+};
+
 // What a thread needs for every token of its unit.
 struct Piece {
   int head, j;
@@ -403,7 +415,7 @@ __device__ __forceinline__ void finish_stage(Stage& st, Piece& q, double2* cs) {
 // late order only the first `valid` tokens are real: the accesses of the
 // others get offsets past their buffers, which the hardware drops.
 template <int NK, int TAG, bool ROT, int STYLE, bool BF16, bool LATE>
-__device__ __forceinline__ void restore_tokens(const KernelArgs& a, const Unit& u, int t, Piece& q,
+__device__ __forceinline__ void restore_tokens(const KernelArgs& a, const LayerUnit& u, int t, Piece& q,
                                                double2* __restrict__ cs, Stage& st, int valid) {
   constexpr int KB = kKeyBits[TAG];
   constexpr int VB = kValueBits[TAG];
@@ -437,7 +449,7 @@ __device__ __forceinline__ void restore_tokens(const KernelArgs& a, const Unit& 
 }
 
 template <int TAG, bool ROT, int STYLE, bool BF16, bool LATE>
-__device__ __forceinline__ void restore_unit(const KernelArgs& a, const Unit& u, const double* __restrict__ s_tab,
+__device__ __forceinline__ void restore_unit(const KernelArgs& a, const LayerUnit& u, const double* __restrict__ s_tab,
                                              Stage& st, int t0, int head, int j) {
   Piece q;
   q.head = head;
@@ -452,10 +464,9 @@ __device__ __forceinline__ void restore_unit(const KernelArgs& a, const Unit& u,
     q.vz = half_bits_to_float(sw.y >> 16);
   }
   // A unit's rows share one page, carried in its work item.
-  const int64_t page = int64_t(u.layer) * a.layer_elems + (int64_t(u.page1) << a.page_shift) * (int64_t(a.H) * a.D);
-  q.kdst = raw_rsrc(a.k_cache + page, LATE ? kOutside : kWholeRange);
-  q.vdst = raw_rsrc(a.v_cache + page, LATE ? kOutside : kWholeRange);
-  q.doff = (uint32_t(u.row0 & ((int64_t(1) << a.log2P) - 1)) * uint32_t(a.H) + uint32_t(head)) * uint32_t(a.D) * 2;
+  q.kdst = raw_rsrc(a.k_cache + u.page, LATE ? kOutside : kWholeRange);
+  q.vdst = raw_rsrc(a.v_cache + u.page, LATE ? kOutside : kWholeRange);
+  q.doff = (u.slot0 * uint32_t(a.H) + uint32_t(head)) * uint32_t(a.D) * 2;
   double2 cs[8];  // (cos, sin) of this thread's eight rotary pairs
   if constexpr (ROT && !LATE) {
 #pragma unroll
@@ -524,13 +535,24 @@ __device__ __forceinline__ void restore_unit(const KernelArgs& a, const Unit& u,
 }
 
 template <bool BF16, int STYLE, bool LATE>
-__global__ __launch_bounds__(kWorkgroup, kMinWavesPerEU) void restore_kernel(KernelArgs a) {
+__global__ __launch_bounds__(kWorkgroup, kMinWavesPerEU) void restore_kernel(KernelArgs) {
   __shared__ __attribute__((aligned(16))) double s_tab[kMaxHeadDim];
-  const Unit u = a.units[xcd_grouped(blockIdx.x, gridDim.x)];
+  const KernelArgs a = launch_args<KernelArgs>();
+  const uint32_t item = uint32_t(xcd_grouped(blockIdx.x, a.grid)), l = layer_of(a.items, item);
+  const uint32_t layer = a.items.first + l;
+  const Unit unit = load_unit(a.units + (item - l * a.items.count.d));
+  LayerUnit u;
+  u.k_off = unit_k_off(unit, layer);
   if (u.k_off < a.win_lo || u.k_off >= a.win_hi) return;  // uniform across the workgroup
+  u.v_off = unit_v_off(unit, layer);
+  u.scale_off = unit_scale_off(unit, layer);
+  u.page = int64_t(layer) * a.layer_elems + (int64_t(unit.page0) << a.page_shift) * (int64_t(a.H) * a.D);
+  u.slot0 = uint32_t(unit.slot0);
+  u.n_valid = unit_tokens_of(unit);
+  const double* table = a.tables + unit.ref;
   const int tid = threadIdx.x;
-  const int tag = u.tag & 0xFF;
-  const bool rot = (u.tag & kUnitRotate) != 0;
+  const int tag = unit_tag(unit);
+  const bool rot = unit_rotates(unit);
   // Thread -> (token, head, piece): shifts when the row's piece counts are
   // powers of two (uniform branches), divisions otherwise.
   const int t0 = a.cols_shift >= 0 ? tid >> a.cols_shift : tid / a.cols;
@@ -542,16 +564,16 @@ __global__ __launch_bounds__(kWorkgroup, kMinWavesPerEU) void restore_kernel(Ker
   if constexpr (LATE) {
     // Threads past tpp token rows have no tokens but take part in the barrier.
     st.s_tab = s_tab;
-    st.table = a.tables + u.table_off;
+    st.table = table;
     st.tid = tid;
     st.D = a.D;
-    st.threads = int(blockDim.x);
+    st.threads = a.threads;
     st.pending = true;
     st.tval = rot && tid < a.D ? st.table[tid] : 0.0;
     st.sw = tag != PKV_TAG_FP16 ? *reinterpret_cast<const uint2*>(a.scales + u.scale_off + 4 * head) : make_uint2(0, 0);
   } else {
     if (rot) {  // uniform across the workgroup
-      for (int i = tid; i < a.D; i += int(blockDim.x)) s_tab[i] = a.tables[u.table_off + i];
+      for (int i = tid; i < a.D; i += a.threads) s_tab[i] = table[i];
       __syncthreads();
     }
     if (t0 >= a.tpp) return;
@@ -720,13 +742,17 @@ pkv_status_t check_restore_buffers(const pkv_plan* plan, const void* payload, ui
 // Set only through the test hook pkv_internal_set_restore_order.
 std::atomic<int> g_restore_order{0};
 
-// Enqueue the restore kernel over units [u0, u0 + n) of the plan, those whose
-// K rows start in payload bytes [win_lo, win_hi).
+// Enqueue the restore kernel over units [u0, u1) of layers [layer0, layer1),
+// those whose K rows start in payload bytes [win_lo, win_hi).
 pkv_status_t launch_restore(const pkv_plan* plan, const void* payload, const void* scales, void* k_cache,
-                            void* v_cache, int64_t u0, int64_t n, hipStream_t stream, uint64_t win_lo = 0,
-                            uint64_t win_hi = ~uint64_t(0)) {
+                            void* v_cache, int64_t layer0, int64_t layer1, int64_t u0, int64_t u1, hipStream_t stream,
+                            uint64_t win_lo = 0, uint64_t win_hi = ~uint64_t(0)) {
   const pkv_model_t& m = plan->host.model;
+  const int64_t n = (layer1 - layer0) * (u1 - u0);
   KernelArgs a;
+  a.items = layer_items(layer0, layer1 - layer0, u1 - u0);
+  a.grid = uint32_t(n);
+  a.threads = plan->host.workgroup;
   a.win_lo = win_lo;
   a.win_hi = win_hi;
   a.units = plan->d_units + u0;
@@ -736,44 +762,28 @@ pkv_status_t launch_restore(const pkv_plan* plan, const void* payload, const voi
   a.k_cache = static_cast<uint16_t*>(k_cache);
   a.v_cache = static_cast<uint16_t*>(v_cache);
   a.layer_elems = layer_elems(m);
-  a.page_shift = page_shift(m);
+  a.page_shift = int8_t(page_shift(m));
   a.H = m.num_kv_heads;
   a.D = m.head_dim;
-  a.log2P = plan->host.log2_page;
   a.cols = m.num_kv_heads * m.head_dim / 16;
   a.tpp = plan->host.workgroup / a.cols;
   auto shift_of = [](int32_t x) {
     int32_t s = 0;
     while ((1 << s) < x) ++s;
-    return (1 << s) == x ? s : -1;
+    return int8_t((1 << s) == x ? s : -1);
   };
   a.cols_shift = shift_of(a.cols);
   a.dq_shift = shift_of(m.head_dim / 16);
   a.R = m.rotary_dim ? m.rotary_dim : m.head_dim;
-  const dim3 grid(static_cast<uint32_t>(n)), block(plan->host.workgroup);
   const bool bf16 = m.out_dtype == PKV_OUT_BF16, half = m.rope_style == PKV_ROPE_HALF;
   const int order = g_restore_order.load(std::memory_order_relaxed);
   const bool late = order == 2 || (order == 0 && n <= plan->restore_late_units);
-  const uint32_t lds = plan->cap_lds;
-  if (late) {
-    if (bf16 && half)
-      hipLaunchKernelGGL((restore_kernel<true, PKV_ROPE_HALF, true>), grid, block, lds, stream, a);
-    else if (bf16)
-      hipLaunchKernelGGL((restore_kernel<true, PKV_ROPE_INTERLEAVED, true>), grid, block, lds, stream, a);
-    else if (half)
-      hipLaunchKernelGGL((restore_kernel<false, PKV_ROPE_HALF, true>), grid, block, lds, stream, a);
-    else
-      hipLaunchKernelGGL((restore_kernel<false, PKV_ROPE_INTERLEAVED, true>), grid, block, lds, stream, a);
-  } else {
-    if (bf16 && half)
-      hipLaunchKernelGGL((restore_kernel<true, PKV_ROPE_HALF, false>), grid, block, lds, stream, a);
-    else if (bf16)
-      hipLaunchKernelGGL((restore_kernel<true, PKV_ROPE_INTERLEAVED, false>), grid, block, lds, stream, a);
-    else if (half)
-      hipLaunchKernelGGL((restore_kernel<false, PKV_ROPE_HALF, false>), grid, block, lds, stream, a);
-    else
-      hipLaunchKernelGGL((restore_kernel<false, PKV_ROPE_INTERLEAVED, false>), grid, block, lds, stream, a);
-  }
+  const auto kernel =
+      late ? bf16 ? half ? restore_kernel<true, PKV_ROPE_HALF, true> : restore_kernel<true, PKV_ROPE_INTERLEAVED, true>
+                  : half ? restore_kernel<false, PKV_ROPE_HALF, true> : restore_kernel<false, PKV_ROPE_INTERLEAVED, true>
+           : bf16 ? half ? restore_kernel<true, PKV_ROPE_HALF, false> : restore_kernel<true, PKV_ROPE_INTERLEAVED, false>
+                  : half ? restore_kernel<false, PKV_ROPE_HALF, false> : restore_kernel<false, PKV_ROPE_INTERLEAVED, false>;
+  hipLaunchKernelGGL(kernel, dim3(uint32_t(n)), dim3(plan->host.workgroup), plan->cap_lds, stream, a);
   return hipGetLastError() == hipSuccess ? PKV_OK : PKV_ERR_DEVICE;
 }
 
@@ -859,8 +869,8 @@ pkv_status_t pkv_restore(const pkv_plan_t* plan, const void* payload, uint64_t p
       (st = pkv::kernel_accessible(plan, scales, &s_dev)) != PKV_OK || (st = pkv::device_resident(plan, k_cache)) != PKV_OK ||
       (st = pkv::device_resident(plan, v_cache)) != PKV_OK)
     return st;
-  return pkv::launch_restore(plan, p_dev, s_dev, k_cache, v_cache, 0, info.num_units,
-                             static_cast<hipStream_t>(hip_stream));
+  return pkv::launch_restore(plan, p_dev, s_dev, k_cache, v_cache, 0, plan->host.model.num_layers, 0,
+                             plan->host.layer_units, static_cast<hipStream_t>(hip_stream));
 }
 
 pkv_status_t pkv_restore_from_host(const pkv_plan_t* plan, const void* host_payload, uint64_t host_payload_bytes,
@@ -932,12 +942,18 @@ pkv_status_t pkv_restore_from_host(const pkv_plan_t* plan, const void* host_payl
     }
     return true;
   };
+  std::vector<pkv::CopyRange> payload_copies, scale_copies;
   for (int64_t l = 0; l < L; ++l) {
     uint32_t used = 0;
-    for (int64_t i = h.payload_layer[l]; i < h.payload_layer[l + 1]; ++i)
-      if (!enqueue(dp_bytes, hp_bytes, h.payload_ranges[size_t(i)], used)) return PKV_ERR_DEVICE;
-    for (int64_t i = h.scale_layer[l]; i < h.scale_layer[l + 1]; ++i)
-      if (!enqueue(ds_bytes, hs_bytes, h.scale_ranges[size_t(i)], used)) return PKV_ERR_DEVICE;
+    try {
+      pkv::layer_copies(h, l, payload_copies, scale_copies);
+    } catch (const std::bad_alloc&) {
+      return PKV_ERR_OUT_OF_MEMORY;
+    }
+    for (const pkv::CopyRange& c : payload_copies)
+      if (!enqueue(dp_bytes, hp_bytes, c, used)) return PKV_ERR_DEVICE;
+    for (const pkv::CopyRange& c : scale_copies)
+      if (!enqueue(ds_bytes, hs_bytes, c, used)) return PKV_ERR_DEVICE;
     for (size_t k = 0; k < n_copy; ++k) {
       if (!(used & (1u << k))) continue;
       hipEvent_t e = ev(1 + l * int64_t(n_copy) + int64_t(k));
@@ -945,9 +961,7 @@ pkv_status_t pkv_restore_from_host(const pkv_plan_t* plan, const void* host_payl
           hipStreamWaitEvent(stream, e, 0) != hipSuccess)
         return PKV_ERR_DEVICE;
     }
-    const int64_t u0 = h.layer_units[l], n = h.layer_units[l + 1] - u0;
-    if (n == 0) continue;
-    st = pkv::launch_restore(plan, payload, scales, k_cache, v_cache, u0, n, stream);
+    st = pkv::launch_restore(plan, payload, scales, k_cache, v_cache, l, l + 1, 0, h.layer_units, stream);
     if (st != PKV_OK) return st;
   }
   return PKV_OK;
@@ -983,26 +997,30 @@ pkv_status_t pkv_restore_from_host_noalloc(const pkv_plan_t* plan, const void* h
   const uint8_t* hs = static_cast<const uint8_t*>(host_scales);
   // Every step goes on the caller's stream, so a step's copies wait for the
   // restore of the step before it, which still reads the stage.
-  for (const pkv::StageStep& step : h.stage_steps) {
-    if (step.scale_elems &&
-        hipMemcpyAsync(stage_scales, hs + step.scale0 * 2, step.scale_elems * 2, hipMemcpyHostToDevice, stream) !=
-            hipSuccess)
-      return PKV_ERR_DEVICE;
-    for (int64_t c = step.copy0; c < step.copy1; ++c) {
-      const pkv::StageCopy& cp = h.stage_copies[size_t(c)];
-      if (hipMemcpyAsync(stage + cp.dst, hp + cp.src, cp.len, hipMemcpyHostToDevice, stream) != hipSuccess)
-        return PKV_ERR_DEVICE;
-    }
-    // The kernel adds a unit's absolute checkpoint offsets to these bases:
-    // payload byte o of the window is stage byte o - win_lo, scale element e
-    // of the request-layer is stage element e - scale0.
-    const void* payload_base = reinterpret_cast<const void*>(reinterpret_cast<uintptr_t>(stage) - step.win_lo);
-    const void* scales_base =
-        reinterpret_cast<const void*>(reinterpret_cast<uintptr_t>(stage_scales) - step.scale0 * 2);
-    st = pkv::launch_restore(plan, payload_base, scales_base, k_cache, v_cache, step.u0, step.u1 - step.u0, stream,
-                             step.win_lo, step.win_hi);
-    if (st != PKV_OK) return st;
-  }
+  for (int64_t l = 0; l < h.model.num_layers; ++l)
+    for (const pkv::RequestCopies& rc : h.copies)
+      for (size_t w = 0; w < rc.windows.size(); ++w) {
+        const pkv::StageStep step = pkv::stage_step(rc, l, w);
+        if (step.scale_elems &&
+            hipMemcpyAsync(stage_scales, hs + step.scale0 * 2, step.scale_elems * 2, hipMemcpyHostToDevice, stream) !=
+                hipSuccess)
+          return PKV_ERR_DEVICE;
+        for (int64_t c = rc.windows[w].copy0; c < rc.windows[w].copy1; ++c) {
+          const pkv::StageCopy& cp = rc.stage_copies[size_t(c)];
+          if (hipMemcpyAsync(stage + cp.dst, hp + step.payload_base + cp.src, cp.len, hipMemcpyHostToDevice, stream) !=
+              hipSuccess)
+            return PKV_ERR_DEVICE;
+        }
+        // The kernel adds a unit's absolute checkpoint offsets to these bases:
+        // payload byte o of the window is stage byte o - win_lo, scale element e
+        // of the request-layer is stage element e - scale0.
+        const void* payload_base = reinterpret_cast<const void*>(reinterpret_cast<uintptr_t>(stage) - step.win_lo);
+        const void* scales_base =
+            reinterpret_cast<const void*>(reinterpret_cast<uintptr_t>(stage_scales) - step.scale0 * 2);
+        st = pkv::launch_restore(plan, payload_base, scales_base, k_cache, v_cache, l, l + 1, rc.unit0, rc.unit1,
+                                 stream, step.win_lo, step.win_hi);
+        if (st != PKV_OK) return st;
+      }
   return PKV_OK;
 }
 

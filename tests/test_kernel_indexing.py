@@ -268,3 +268,35 @@ def test_xcd_grouping_is_a_permutation(tmp_path):
                     os.path.join(root, "paper_2609_26219_amd", "csrc"), str(src), "-o", str(exe)], check=True)
     out = subprocess.run([str(exe)], capture_output=True, text=True)
     assert out.returncode == 0 and out.stdout.strip() == "ok", out.stdout + out.stderr
+
+
+_DIVIDE_PROGRAM = r"""
+#include <cstdio>
+#include "pkv_internal.h"
+int main() {
+  const unsigned ds[] = {1, 2, 3, 5, 7, 8, 20, 255, 256, 690, 65537, 4294967295u};
+  const unsigned xs[] = {0, 1, 2, 6, 7, 8, 689, 690, 691, 1u << 26, (1u << 31) - 1, 1u << 31, 4294967294u, 4294967295u};
+  for (unsigned d : ds)
+    for (unsigned x : xs)
+      if (pkv::divide(pkv::divider(d), x) != x / d) { printf("%u / %u\n", x, d); return 1; }
+  printf("ok\n");
+  return 0;
+}
+"""
+
+
+def test_division_by_a_plan_time_divisor(tmp_path):
+    """The kernels find a work item's layer by a multiplication in place of a
+    division: exact for every 32-bit dividend."""
+    import shutil
+    import subprocess
+    if shutil.which("g++") is None:
+        pytest.skip("no host C++ compiler")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    src = tmp_path / "divide.cpp"
+    src.write_text(_DIVIDE_PROGRAM)
+    exe = tmp_path / "divide"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", os.path.join(root, "include"), "-I",
+                    os.path.join(root, "paper_2609_26219_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert out.returncode == 0 and out.stdout.strip() == "ok", out.stdout + out.stderr
