@@ -232,7 +232,7 @@ void layer_copies(const HostPlan& hp, int64_t l, std::vector<CopyRange>& payload
 
 // Restore workgroups resident per compute unit, chosen per plan: 8 to 16
 // waves (for 4-wave workgroups two to four, one wave per SIMD each; 16 waves
-// is the register limit).  Measured on the 8B-shaped 32-layer restore,
+// is the register limit), 6 to 16 for narrow rows.  Measured on the 8B-shaped 32-layer restore,
 // destination rows 7 slots into a page (units of 9, 16 and 7 tokens), us at
 // 2 / 3 / 4 workgroups per CU, paired pages:
 //   FP16 (read:write 1.00)  1200-1208 / 1233-1248 / 1240-1250
@@ -246,10 +246,19 @@ void layer_copies(const HostPlan& hp, int64_t l, std::vector<CopyRange>& payload
 //   K4V4 895-896 / 851-856 / 896-899;
 // and with page-aligned rows (16-token units), paired: mixed 891-898 /
 // 952-961 / 965, K4V4 774-776 / 836-837 / 847: the best count falls as units
-// grow.  Unshifted plans (no rotation, no table) run best with fewer.  The
-// one-head-per-GPU share of the same workload restores in 139 us (16 one-wave
-// workgroups) whatever the target, the two-head share in 263 us at 8
-// one-wave workgroups and 243 at 12 or 16.
+// grow.  Unshifted plans (no rotation, no table) run best with fewer.
+// Rows narrow enough for workgroups under 256 threads, in either layout, want
+// three quarters as much in flight, and more of it the less they read; us at
+// 3 / 4 / 6 / 8 two-wave workgroups per CU (4 heads, units of 5.5K elements):
+//   mixed 479 / 481 / 498 / 497,  FP16 620 / 640 / 652 / 649,  K4V4 444 / 406 / 425 / 429;
+//   8 heads x 64, mixed 513 / 514 / 545 / 560;
+// at 6 / 8 / 9 / 12 / 16 one-wave workgroups (units of 2.7K elements, one head of
+// 128 on 32-token pages, 80 layers):
+//   mixed 651 / 611 / 616 / 635 / 645,  FP16 812 / 836 / 847 / 856 / 847,
+//   K4V4 656 / 551 / 531 / 523 / 537;
+// two heads on 16-token pages: mixed 245 / 235 / 235 / 237 / 242.  Units of 1.4K
+// elements and less (one head on 16-token pages, one-token pages) are fastest
+// at the 16 waves the registers allow.
 int restore_workgroups_per_cu(const HostPlan& hp);
 
 // The same for the checkpoint write, 0 for no cap: staged tiles of 8 loads per
@@ -307,6 +316,10 @@ struct pkv_plan {
   // LDS bytes a workgroup claims so that at most restore_workgroups_per_cu() or
   // gather_workgroups_per_cu() of them are resident on a compute unit (0: no cap).
   uint32_t cap_lds = 0;
+  // Restore launches of at most this many units are resident at once with this
+  // claim instead (kOneRound in restore.hip); none where the count is 0.
+  int64_t one_round_units = 0;
+  uint32_t one_round_lds = 0;
   // Restore launches of at most this many units (a few rounds of compute
   // units x restore_workgroups_per_cu() resident workgroups; every launch for
   // rows narrow enough for workgroups under kWorkgroup threads) take the late

@@ -46,6 +46,7 @@
 #include <atomic>
 #include <mutex>
 #include <new>
+#include <type_traits>
 
 #include "pkv.h"
 #include "pkv_internal.h"
@@ -61,6 +62,14 @@ constexpr int kMinWavesPerEU = 4;
 // Launches of at most this many rounds of resident workgroups take the late
 // start order of the restore kernel (see Stage).
 constexpr int64_t kLateRounds = 6;
+
+// Launches that fit on the device at this many 256-thread workgroups to a
+// compute unit are all resident at once, whatever cap the plan has for longer
+// ones: one layer of the 8B-shaped restore (690 workgroups on 256 compute
+// units) takes 10.5 us at three and 11.1 at two, which leaves 178 for a second
+// round.  At four to a compute unit 1012 workgroups were slower than at two
+// (14.3 against 13.7 us).
+constexpr int kOneRound = 3;
 
 struct KernelArgs {
   const Unit* units;  // of one layer
@@ -119,13 +128,14 @@ constexpr int kNonTemporal = 2;
 constexpr int kNonTemporalDevice = 18;
 
 // Restored rows are written once and not read again by this launch: store
-// them non-temporally (2% faster than the default policy), and in the early
-// order, which deep launches of wide rows take, at device scope too, so that a
-// line leaves its XCD's L2 as it is written and not when another one evicts
-// it.  The write stream bounds those launches: the 8B-shaped 32-layer restore
-// takes 847 us that way against 886 (5.34 GB, 6.3 against 6.0 TB/s).  Narrow
-// rows and shallow launches, which take the late order, gain nothing from it
-// (one head of 128, 80 layers: 643 us against 638).
+// them non-temporally (2% faster than the default policy), and at device scope
+// too where each store instruction writes whole 64-byte sectors (whole_sectors),
+// so that a line leaves its XCD's L2 as it is written and not when another one
+// evicts it.  The write stream bounds the kernel: the 8B-shaped 32-layer restore
+// takes 847 us that way against 886 (5.34 GB, 6.3 against 6.0 TB/s), one layer
+// of it 10.5 against 11.3.  Parts of sectors are another matter: written
+// through one by one they take twice as long (8 heads of 96, 16 layers: 1100 us
+// against 550), so those rows stay in the L2, which puts them together.
 //
 // The whole offset goes in the VGPR operand and the SGPR offset is 0.  A
 // 16-byte store reads its data registers after it issues, so an instruction
@@ -134,10 +144,10 @@ constexpr int kNonTemporalDevice = 18;
 // a register SGPR offset gfx950 was seen storing the next instruction's
 // result (a token's 16 outputs replaced, now and then, by an address or a
 // decoded value).
-template <bool LATE>
+template <bool DEVICE>
 __device__ __forceinline__ void store_row_piece(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, uint4 v) {
   __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, voff + soff, 0,
-                                         LATE ? kNonTemporal : kNonTemporalDevice);
+                                         DEVICE ? kNonTemporalDevice : kNonTemporal);
 }
 
 // Two floats to two bfloat16 / binary16 values, round to nearest even, in
@@ -278,7 +288,7 @@ __device__ __forceinline__ void decode_run(const Chunk8<KBITS>& c, float s, floa
 
 // Keys of one (token, head), piece p, from its two loaded runs: decode,
 // rotate, round, store.
-template <int KBITS, bool ROT, int STYLE, bool BF16, bool LATE>
+template <int KBITS, bool ROT, int STYLE, bool BF16, bool DEVICE>
 __device__ __forceinline__ void key_store(const Chunk8<KBITS>& lo, const Chunk8<KBITS>& hi, const KeyPiece& p, float ks,
                                           float kz, const double2* __restrict__ cs, __amdgpu_buffer_rsrc_t dst,
                                           uint32_t doff, uint32_t soff) {
@@ -319,12 +329,12 @@ __device__ __forceinline__ void key_store(const Chunk8<KBITS>& lo, const Chunk8<
     out_lo = pack8<BF16>(a);
     out_hi = pack8<BF16>(b);
   }
-  store_row_piece<LATE>(dst, doff + 2 * p.lo, soff, out_lo);
-  store_row_piece<LATE>(dst, doff + 2 * p.hi, soff, out_hi);
+  store_row_piece<DEVICE>(dst, doff + 2 * p.lo, soff, out_lo);
+  store_row_piece<DEVICE>(dst, doff + 2 * p.hi, soff, out_hi);
 }
 
 // Values of one (token, head), piece j (never rotated).
-template <int VBITS, bool BF16, bool LATE>
+template <int VBITS, bool BF16, bool DEVICE>
 __device__ __forceinline__ void value_store(const Chunk8<VBITS>& lo, const Chunk8<VBITS>& hi, int j, int D, float vs,
                                             float vz, __amdgpu_buffer_rsrc_t dst, uint32_t doff, uint32_t soff) {
   uint4 out_lo, out_hi;
@@ -341,8 +351,8 @@ __device__ __forceinline__ void value_store(const Chunk8<VBITS>& lo, const Chunk
     out_lo = pack8<BF16>(a);
     out_hi = pack8<BF16>(b);
   }
-  store_row_piece<LATE>(dst, doff + 16 * j, soff, out_lo);
-  store_row_piece<LATE>(dst, doff + D + 16 * j, soff, out_hi);
+  store_row_piece<DEVICE>(dst, doff + 16 * j, soff, out_lo);
+  store_row_piece<DEVICE>(dst, doff + D + 16 * j, soff, out_hi);
 }
 
 // A work item of the layer it is restored in.
@@ -414,7 +424,7 @@ __device__ __forceinline__ void finish_stage(Stage& st, Piece& q, double2* cs) {
 // the thread is k * tpp rows further in the payload and in the page.  In the
 // late order only the first `valid` tokens are real: the accesses of the
 // others get offsets past their buffers, which the hardware drops.
-template <int NK, int TAG, bool ROT, int STYLE, bool BF16, bool LATE>
+template <int NK, int TAG, bool ROT, int STYLE, bool BF16, bool LATE, bool DEVICE>
 __device__ __forceinline__ void restore_tokens(const KernelArgs& a, const LayerUnit& u, int t, Piece& q,
                                                double2* __restrict__ cs, Stage& st, int valid) {
   constexpr int KB = kKeyBits[TAG];
@@ -443,12 +453,12 @@ __device__ __forceinline__ void restore_tokens(const KernelArgs& a, const LayerU
 #pragma unroll
   for (int k = 0; k < NK; ++k) {
     const uint32_t d = !LATE || k < valid ? doff : kOutside;
-    key_store<KB, ROT, STYLE, BF16, LATE>(klo[k], khi[k], q.kp, q.ks, q.kz, cs, q.kdst, d, k * tpp * H * D * 2);
-    value_store<VB, BF16, LATE>(vlo[k], vhi[k], q.j, D, q.vs, q.vz, q.vdst, d, k * tpp * H * D * 2);
+    key_store<KB, ROT, STYLE, BF16, DEVICE>(klo[k], khi[k], q.kp, q.ks, q.kz, cs, q.kdst, d, k * tpp * H * D * 2);
+    value_store<VB, BF16, DEVICE>(vlo[k], vhi[k], q.j, D, q.vs, q.vz, q.vdst, d, k * tpp * H * D * 2);
   }
 }
 
-template <int TAG, bool ROT, int STYLE, bool BF16, bool LATE>
+template <int TAG, bool ROT, int STYLE, bool BF16, bool LATE, bool DEVICE>
 __device__ __forceinline__ void restore_unit(const KernelArgs& a, const LayerUnit& u, const double* __restrict__ s_tab,
                                              Stage& st, int t0, int head, int j) {
   Piece q;
@@ -480,22 +490,22 @@ __device__ __forceinline__ void restore_unit(const KernelArgs& a, const LayerUni
     if constexpr (TAG != PKV_TAG_FP16) {
       switch (nk) {
         case 0: return;
-        case 1: restore_tokens<1, TAG, ROT, STYLE, BF16, false>(a, u, t0, q, cs, st, 1); return;
-        case 2: restore_tokens<2, TAG, ROT, STYLE, BF16, false>(a, u, t0, q, cs, st, 2); return;
-        case 3: restore_tokens<3, TAG, ROT, STYLE, BF16, false>(a, u, t0, q, cs, st, 3); return;
-        case 4: restore_tokens<4, TAG, ROT, STYLE, BF16, false>(a, u, t0, q, cs, st, 4); return;
+        case 1: restore_tokens<1, TAG, ROT, STYLE, BF16, false, DEVICE>(a, u, t0, q, cs, st, 1); return;
+        case 2: restore_tokens<2, TAG, ROT, STYLE, BF16, false, DEVICE>(a, u, t0, q, cs, st, 2); return;
+        case 3: restore_tokens<3, TAG, ROT, STYLE, BF16, false, DEVICE>(a, u, t0, q, cs, st, 3); return;
+        case 4: restore_tokens<4, TAG, ROT, STYLE, BF16, false, DEVICE>(a, u, t0, q, cs, st, 4); return;
         default: break;
       }
     } else if (nk <= 4) {
       for (int k = nk, t = t0; k > 0; k -= 2, t += 2 * a.tpp) {
         if (k >= 2)
-          restore_tokens<2, TAG, ROT, STYLE, BF16, false>(a, u, t, q, cs, st, 2);
+          restore_tokens<2, TAG, ROT, STYLE, BF16, false, DEVICE>(a, u, t, q, cs, st, 2);
         else
-          restore_tokens<1, TAG, ROT, STYLE, BF16, false>(a, u, t, q, cs, st, 1);
+          restore_tokens<1, TAG, ROT, STYLE, BF16, false, DEVICE>(a, u, t, q, cs, st, 1);
       }
       return;
     }
-    for (int t = t0; t < u.n_valid; t += a.tpp) restore_tokens<1, TAG, ROT, STYLE, BF16, false>(a, u, t, q, cs, st, 1);
+    for (int t = t0; t < u.n_valid; t += a.tpp) restore_tokens<1, TAG, ROT, STYLE, BF16, false, DEVICE>(a, u, t, q, cs, st, 1);
   } else {
     // Late order: the switch takes lane 0's count, the largest in its wave
     // (lanes are in token order; threads past tpp rows count 0), so each
@@ -505,36 +515,36 @@ __device__ __forceinline__ void restore_unit(const KernelArgs& a, const LayerUni
     if constexpr (TAG != PKV_TAG_FP16) {
       switch (nk) {
         case 0: finish_stage<TAG, ROT>(st, q, cs); return;
-        case 1: restore_tokens<1, TAG, ROT, STYLE, BF16, true>(a, u, t0, q, cs, st, nk_t); return;
-        case 2: restore_tokens<2, TAG, ROT, STYLE, BF16, true>(a, u, t0, q, cs, st, nk_t); return;
-        case 3: restore_tokens<3, TAG, ROT, STYLE, BF16, true>(a, u, t0, q, cs, st, nk_t); return;
-        case 4: restore_tokens<4, TAG, ROT, STYLE, BF16, true>(a, u, t0, q, cs, st, nk_t); return;
+        case 1: restore_tokens<1, TAG, ROT, STYLE, BF16, true, DEVICE>(a, u, t0, q, cs, st, nk_t); return;
+        case 2: restore_tokens<2, TAG, ROT, STYLE, BF16, true, DEVICE>(a, u, t0, q, cs, st, nk_t); return;
+        case 3: restore_tokens<3, TAG, ROT, STYLE, BF16, true, DEVICE>(a, u, t0, q, cs, st, nk_t); return;
+        case 4: restore_tokens<4, TAG, ROT, STYLE, BF16, true, DEVICE>(a, u, t0, q, cs, st, nk_t); return;
         default: break;
       }
     } else {
       const int t2 = t0 + 2 * a.tpp;
       switch (nk) {
         case 0: finish_stage<TAG, ROT>(st, q, cs); return;
-        case 1: restore_tokens<1, TAG, ROT, STYLE, BF16, true>(a, u, t0, q, cs, st, nk_t); return;
-        case 2: restore_tokens<2, TAG, ROT, STYLE, BF16, true>(a, u, t0, q, cs, st, nk_t); return;
+        case 1: restore_tokens<1, TAG, ROT, STYLE, BF16, true, DEVICE>(a, u, t0, q, cs, st, nk_t); return;
+        case 2: restore_tokens<2, TAG, ROT, STYLE, BF16, true, DEVICE>(a, u, t0, q, cs, st, nk_t); return;
         case 3:
-          restore_tokens<2, TAG, ROT, STYLE, BF16, true>(a, u, t0, q, cs, st, nk_t);
-          restore_tokens<1, TAG, ROT, STYLE, BF16, true>(a, u, t2, q, cs, st, nk_t - 2);
+          restore_tokens<2, TAG, ROT, STYLE, BF16, true, DEVICE>(a, u, t0, q, cs, st, nk_t);
+          restore_tokens<1, TAG, ROT, STYLE, BF16, true, DEVICE>(a, u, t2, q, cs, st, nk_t - 2);
           return;
         case 4:
-          restore_tokens<2, TAG, ROT, STYLE, BF16, true>(a, u, t0, q, cs, st, nk_t);
-          restore_tokens<2, TAG, ROT, STYLE, BF16, true>(a, u, t2, q, cs, st, nk_t - 2);
+          restore_tokens<2, TAG, ROT, STYLE, BF16, true, DEVICE>(a, u, t0, q, cs, st, nk_t);
+          restore_tokens<2, TAG, ROT, STYLE, BF16, true, DEVICE>(a, u, t2, q, cs, st, nk_t - 2);
           return;
         default: break;
       }
     }
     finish_stage<TAG, ROT>(st, q, cs);
     if (t0 < a.tpp)
-      for (int t = t0; t < u.n_valid; t += a.tpp) restore_tokens<1, TAG, ROT, STYLE, BF16, true>(a, u, t, q, cs, st, 1);
+      for (int t = t0; t < u.n_valid; t += a.tpp) restore_tokens<1, TAG, ROT, STYLE, BF16, true, DEVICE>(a, u, t, q, cs, st, 1);
   }
 }
 
-template <bool BF16, int STYLE, bool LATE>
+template <bool BF16, int STYLE, bool LATE, bool DEVICE>
 __global__ __launch_bounds__(kWorkgroup, kMinWavesPerEU) void restore_kernel(KernelArgs) {
   __shared__ __attribute__((aligned(16))) double s_tab[kMaxHeadDim];
   const KernelArgs a = launch_args<KernelArgs>();
@@ -579,14 +589,14 @@ __global__ __launch_bounds__(kWorkgroup, kMinWavesPerEU) void restore_kernel(Ker
     if (t0 >= a.tpp) return;
   }
   switch (tag * 2 + (rot ? 1 : 0)) {
-    case 0: restore_unit<PKV_TAG_FP16, false, STYLE, BF16, LATE>(a, u, s_tab, st, t0, head, j); break;
-    case 1: restore_unit<PKV_TAG_FP16, true, STYLE, BF16, LATE>(a, u, s_tab, st, t0, head, j); break;
-    case 2: restore_unit<PKV_TAG_K8V8, false, STYLE, BF16, LATE>(a, u, s_tab, st, t0, head, j); break;
-    case 3: restore_unit<PKV_TAG_K8V8, true, STYLE, BF16, LATE>(a, u, s_tab, st, t0, head, j); break;
-    case 4: restore_unit<PKV_TAG_K8V4, false, STYLE, BF16, LATE>(a, u, s_tab, st, t0, head, j); break;
-    case 5: restore_unit<PKV_TAG_K8V4, true, STYLE, BF16, LATE>(a, u, s_tab, st, t0, head, j); break;
-    case 6: restore_unit<PKV_TAG_K4V4, false, STYLE, BF16, LATE>(a, u, s_tab, st, t0, head, j); break;
-    default: restore_unit<PKV_TAG_K4V4, true, STYLE, BF16, LATE>(a, u, s_tab, st, t0, head, j); break;
+    case 0: restore_unit<PKV_TAG_FP16, false, STYLE, BF16, LATE, DEVICE>(a, u, s_tab, st, t0, head, j); break;
+    case 1: restore_unit<PKV_TAG_FP16, true, STYLE, BF16, LATE, DEVICE>(a, u, s_tab, st, t0, head, j); break;
+    case 2: restore_unit<PKV_TAG_K8V8, false, STYLE, BF16, LATE, DEVICE>(a, u, s_tab, st, t0, head, j); break;
+    case 3: restore_unit<PKV_TAG_K8V8, true, STYLE, BF16, LATE, DEVICE>(a, u, s_tab, st, t0, head, j); break;
+    case 4: restore_unit<PKV_TAG_K8V4, false, STYLE, BF16, LATE, DEVICE>(a, u, s_tab, st, t0, head, j); break;
+    case 5: restore_unit<PKV_TAG_K8V4, true, STYLE, BF16, LATE, DEVICE>(a, u, s_tab, st, t0, head, j); break;
+    case 6: restore_unit<PKV_TAG_K4V4, false, STYLE, BF16, LATE, DEVICE>(a, u, s_tab, st, t0, head, j); break;
+    default: restore_unit<PKV_TAG_K4V4, true, STYLE, BF16, LATE, DEVICE>(a, u, s_tab, st, t0, head, j); break;
   }
 }
 
@@ -622,16 +632,25 @@ pkv_status_t upload_plan(HostPlan&& hp, pkv_plan** out) {
   // Residency cap through LDS: each workgroup claims a share of the compute
   // unit's LDS (it needs only its table, or its tile's image) so that no more
   // than restore_workgroups_per_cu() or gather_workgroups_per_cu() fit.
-  int lds_cu = 0, lds_wg = 0;
+  int lds_cu = 0, lds_wg = 0, cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+    (void)hipGetLastError();
+    cus = 0;
+  }
   if (hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) == hipSuccess &&
       hipDeviceGetAttribute(&lds_wg, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && lds_cu > 0) {
     const bool write = plan->host.kind == 1;
     const int64_t fixed = write ? 0 : int64_t(kMaxHeadDim) * int64_t(sizeof(double));
     const int64_t n = write ? gather_workgroups_per_cu(plan->host) : restore_workgroups_per_cu(plan->host);
-    if (n > 0 && n < 16 / std::max(1, plan->host.workgroup / 64) + (write ? 1 : 0)) {
-      const int64_t share = (int64_t(lds_cu) / n + int64_t(lds_cu) / (n + 1)) / 2;
+    const auto claim = [&](int64_t per_cu) {
+      const int64_t share = (int64_t(lds_cu) / per_cu + int64_t(lds_cu) / (per_cu + 1)) / 2;
       const int64_t dyn = std::min<int64_t>((share - fixed) & ~int64_t(255), int64_t(lds_wg) - fixed);
-      plan->cap_lds = dyn > 0 ? uint32_t(dyn) : 0;
+      return dyn > 0 ? uint32_t(dyn) : 0;
+    };
+    if (n > 0 && n < 16 / std::max(1, plan->host.workgroup / 64) + (write ? 1 : 0)) plan->cap_lds = claim(n);
+    if (!write && plan->host.workgroup == kWorkgroup && n < kOneRound) {
+      plan->one_round_units = kOneRound * int64_t(cus);
+      plan->one_round_lds = claim(kOneRound);
     }
   } else {
     (void)hipGetLastError();
@@ -644,13 +663,10 @@ pkv_status_t upload_plan(HostPlan&& hp, pkv_plan** out) {
   // 8B-shaped workload's share of one KV head per GPU (one-wave workgroups of
   // two tokens per thread) it measured 102-112 us against 127-135 us, and
   // within 1% of the early order at two and four heads.
-  int cus = 0;
   if (plan->host.workgroup < kWorkgroup)
     plan->restore_late_units = INT64_MAX;
-  else if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
-    plan->restore_late_units = kLateRounds * int64_t(cus) * restore_workgroups_per_cu(plan->host);
   else
-    (void)hipGetLastError();
+    plan->restore_late_units = kLateRounds * int64_t(cus) * restore_workgroups_per_cu(plan->host);
   if (total > 0) {
     hipError_t e = hipMalloc(&plan->device_mem, total);
     if (e != hipSuccess) {
@@ -742,6 +758,14 @@ pkv_status_t check_restore_buffers(const pkv_plan* plan, const void* payload, ui
 // Set only through the test hook pkv_internal_set_restore_order.
 std::atomic<int> g_restore_order{0};
 
+// Whether the pieces that a store instruction writes next to each other make
+// whole 64-byte sectors (of a cache that starts on one): they fill half a
+// head's row, or half its rotary channels and half the others where
+// rotate-half pairs stop short of the row.
+bool whole_sectors(const pkv_model_t& m) {
+  return m.head_dim % 64 == 0 && (m.rope_style == PKV_ROPE_INTERLEAVED || m.rotary_dim % 64 == 0);
+}
+
 // Enqueue the restore kernel over units [u0, u1) of layers [layer0, layer1),
 // those whose K rows start in payload bytes [win_lo, win_hi).
 pkv_status_t launch_restore(const pkv_plan* plan, const void* payload, const void* scales, void* k_cache,
@@ -778,12 +802,19 @@ pkv_status_t launch_restore(const pkv_plan* plan, const void* payload, const voi
   const bool bf16 = m.out_dtype == PKV_OUT_BF16, half = m.rope_style == PKV_ROPE_HALF;
   const int order = g_restore_order.load(std::memory_order_relaxed);
   const bool late = order == 2 || (order == 0 && n <= plan->restore_late_units);
-  const auto kernel =
-      late ? bf16 ? half ? restore_kernel<true, PKV_ROPE_HALF, true> : restore_kernel<true, PKV_ROPE_INTERLEAVED, true>
-                  : half ? restore_kernel<false, PKV_ROPE_HALF, true> : restore_kernel<false, PKV_ROPE_INTERLEAVED, true>
-           : bf16 ? half ? restore_kernel<true, PKV_ROPE_HALF, false> : restore_kernel<true, PKV_ROPE_INTERLEAVED, false>
-                  : half ? restore_kernel<false, PKV_ROPE_HALF, false> : restore_kernel<false, PKV_ROPE_INTERLEAVED, false>;
-  hipLaunchKernelGGL(kernel, dim3(uint32_t(n)), dim3(plan->host.workgroup), plan->cap_lds, stream, a);
+  const bool device = whole_sectors(m);
+  const auto pick = [&](auto f16, auto style) {
+    constexpr bool B = decltype(f16)::value;
+    constexpr int S = decltype(style)::value;
+    return late ? device ? restore_kernel<B, S, true, true> : restore_kernel<B, S, true, false>
+                : device ? restore_kernel<B, S, false, true> : restore_kernel<B, S, false, false>;
+  };
+  using Half = std::integral_constant<int, PKV_ROPE_HALF>;
+  using Pairs = std::integral_constant<int, PKV_ROPE_INTERLEAVED>;
+  const auto kernel = bf16 ? half ? pick(std::true_type(), Half()) : pick(std::true_type(), Pairs())
+                           : half ? pick(std::false_type(), Half()) : pick(std::false_type(), Pairs());
+  const uint32_t lds = n <= plan->one_round_units ? plan->one_round_lds : plan->cap_lds;
+  hipLaunchKernelGGL(kernel, dim3(uint32_t(n)), dim3(plan->host.workgroup), lds, stream, a);
   return hipGetLastError() == hipSuccess ? PKV_OK : PKV_ERR_DEVICE;
 }
 

@@ -300,3 +300,20 @@ def test_plan_payload_bytes_per_request(torch):
             assert pb.pkv_plan_payload_bytes_status(plan.handle, bad, ctypes.byref(out)) == pb.PKV_ERR_INVALID_ARGUMENT
         assert pb.pkv_plan_payload_bytes_status(plan.handle, 0, None) == pb.PKV_ERR_INVALID_ARGUMENT
         assert out.value == 7
+
+
+@pytest.mark.parametrize("heads,dim,style,rotary", [
+    (2, 64, wl.ROPE_HALF, 0),            # half a row is one 64-byte sector: stored at device scope
+    (1, 128, wl.ROPE_HALF, 64),          # rotary and pass-through runs of one sector each
+    (2, 128, wl.ROPE_INTERLEAVED, 32),   # whole half rows whatever the rotary dimension
+    (1, 128, wl.ROPE_HALF, 32),          # runs of half a sector: kept in the L2
+    (3, 96, wl.ROPE_HALF, 0),            # one and a half
+    (8, 80, wl.ROPE_INTERLEAVED, 48),
+])
+def test_both_store_scopes(heads, dim, style, rotary, torch):
+    """Rows stored at device scope and rows that stay in the L2, at the edges of the rule between them."""
+    import dataclasses
+    case = wl.make_custom(51, L=2, H=heads, D=dim, B=16, P=8, n_tokens=(70, 9), deltas=(-300, 7), rho0s=(305, 2),
+                          tag_set=(0, 1, 2, 3), mix=(1, 1, 1, 1), out_dtype=wl.OUT_BF16, outlier_pairs=1)
+    case.shape = dataclasses.replace(case.shape, rope_style=style, rotary_dim=rotary)
+    check_both_orders(case)
