@@ -200,6 +200,7 @@ struct RequestCopies {
   uint64_t payload_offset, layer_bytes;  // bytes
   uint64_t scale_offset, layer_scales;   // binary16 elements
   bool scales_needed;                    // some reused block is quantized
+  uint64_t fp16_bytes;                   // bytes of the reused FP16 blocks of a layer
   int64_t unit0, unit1;                  // the request's units of a layer
   std::vector<CopyRange> ranges;         // merged payload copies, from the layer's start, ascending
   std::vector<StageWindow> windows;

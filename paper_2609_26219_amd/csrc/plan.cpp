@@ -356,6 +356,7 @@ pkv_status_t build_host_plan(const pkv_model_t* model, const pkv_request_t* requ
       rc.layer_scales = uint64_t(nb) * H * 4;
       rc.layer_bytes = 0;
       rc.scales_needed = false;
+      rc.fp16_bytes = 0;
       // Block offsets inside one layer (runs by tag, ascending blocks) and the
       // reused ones' ranges in that order, so that neighbours merge into one
       // copy; merging stays inside this request's layer, so copies never overlap.
@@ -370,6 +371,7 @@ pkv_status_t build_host_plan(const pkv_model_t* model, const pkv_request_t* requ
             reused.push_back(CopyRange{rc.layer_bytes, len});
             add_range(rc.ranges, 0, rc.layer_bytes, len, kHostGapBytes);
             rc.scales_needed |= tag != PKV_TAG_FP16;
+            rc.fp16_bytes += tag == PKV_TAG_FP16 ? len : 0;
           }
           rc.layer_bytes += len;
         }

@@ -101,3 +101,27 @@ def test_noalloc_rejects_pageable_and_oversized(torch):
     after = dr.host_caches()
     assert np.array_equal(before[0], after[0]) and np.array_equal(before[1], after[1])
     assert int(k.abs().sum()) == 0 and int(v.abs().sum()) == 0
+
+
+@pytest.mark.parametrize("offset", [0, 16, 4], ids=["base", "inside", "unaligned"])
+def test_noalloc_host_buffer_placement(offset, torch):
+    """A checkpoint at the start of a pinned allocation or 16 bytes into it is read in place; one that a kernel
+    cannot address in whole loads is staged.  Both restore what the oracle does."""
+    from paper_2609_26219_amd.device import DeviceRestore
+
+    case = wl.make_custom(33, L=3, H=2, D=64, B=16, P=16, n_tokens=(137, 16, 50), deltas=(3, 0, -7), rho0s=(3, 6, 13),
+                          tag_set=(0, 1, 2, 3), mix=(1, 1, 1, 1), repair_frac=0.3, out_dtype=wl.OUT_BF16)
+    ckpt = oracle_checkpoint(case)
+    raw_p, raw_s = ckpt[0].view(np.uint8), ckpt[1].view(np.uint8)
+    hp = torch.zeros(raw_p.size + 64, dtype=torch.uint8).pin_memory()
+    hs = torch.zeros(raw_s.size + 64, dtype=torch.uint8).pin_memory()
+    hp[offset:offset + raw_p.size] = torch.from_numpy(raw_p)
+    hs[offset:offset + raw_s.size] = torch.from_numpy(raw_s)
+    blank = (np.full(ckpt[0].shape, FILL, np.uint8), np.full(ckpt[1].shape, FILL * 0x101, np.uint16))
+    dr = DeviceRestore(case, checkpoint=blank)
+    st = pb.pkv_restore_from_host_noalloc_status(
+        dr.plan, hp.data_ptr() + offset, raw_p.size, hs.data_ptr() + offset, raw_s.size, dr.k_cache.data_ptr(),
+        dr.v_cache.data_ptr(), pb.cache_nbytes(dr.k_cache, dr.v_cache), torch.cuda.current_stream().cuda_stream)
+    assert st == pb.PKV_OK, pb.pkv_status_string(st)
+    torch.cuda.synchronize()
+    check_full(dr, ckpt)
