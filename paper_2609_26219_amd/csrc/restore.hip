@@ -44,6 +44,8 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cstddef>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <type_traits>
@@ -610,6 +612,110 @@ bool ranges_overlap(const void* a, uint64_t na, const void* b, uint64_t nb) {
 
 namespace pkv {
 
+namespace {
+
+constexpr int kMaxDevices = 64;
+
+// Device memory of plans, cut from slabs: a resume's plan is 0.1-0.3 MB and
+// lives for one restore, and an allocation of its own costs a hipMalloc and,
+// when it is freed, a wait for everything the device still runs (hipFree).
+// Plans of more than a quarter slab keep an allocation of their own.  A slab
+// hands out each byte once; its memory is used again only after a device
+// synchronisation that follows the release of every plan in it, so a plan
+// that is freed while a launch still reads it stays readable, as with hipFree.
+// Slabs behind the current one are freed with their last plan, and all are
+// when no plan of the device is left.
+class PlanMemory {
+ public:
+  static constexpr size_t kSlab = size_t(4) << 20;
+
+  hipError_t allocate(size_t bytes, void** out) {
+    std::lock_guard<std::mutex> lock(mu_);
+    hipError_t e = hipSuccess;
+    if (bytes > kSlab / 4) {
+      e = hipMalloc(out, bytes);
+    } else {
+      if (slabs_.empty() || slabs_.back().used + bytes > kSlab) {
+        if (!slabs_.empty() && slabs_.back().plans == 0) {
+          if ((e = hipDeviceSynchronize()) != hipSuccess) return e;
+          slabs_.back().used = 0;
+        } else {
+          void* p = nullptr;
+          if ((e = hipMalloc(&p, kSlab)) != hipSuccess) return e;
+          try {
+            slabs_.push_back(Slab{static_cast<char*>(p), 0, 0});
+          } catch (const std::bad_alloc&) {
+            (void)hipFree(p);
+            return hipErrorOutOfMemory;
+          }
+        }
+      }
+      Slab& s = slabs_.back();
+      *out = s.base + s.used;
+      s.used += (bytes + 255) & ~size_t(255);
+      ++s.plans;
+    }
+    if (e == hipSuccess) ++plans_;
+    return e;
+  }
+
+  void release(void* p) {
+    std::lock_guard<std::mutex> lock(mu_);
+    --plans_;
+    size_t i = 0;
+    while (i < slabs_.size() && !(p >= slabs_[i].base && p < slabs_[i].base + kSlab)) ++i;
+    if (i == slabs_.size()) {
+      (void)hipFree(p);
+    } else if (--slabs_[i].plans == 0 && i + 1 < slabs_.size()) {
+      (void)hipFree(slabs_[i].base);
+      slabs_.erase(slabs_.begin() + std::ptrdiff_t(i));
+    }
+    if (plans_ > 0) return;
+    for (const Slab& s : slabs_) (void)hipFree(s.base);
+    slabs_.clear();
+  }
+
+  // Copy `bytes` of host memory to the device and wait for it, on a stream of
+  // the library's own: the copy does not queue behind the restores that the
+  // caller's streams still run.
+  hipError_t upload(void* dst, const void* src, size_t bytes) {
+    std::lock_guard<std::mutex> lock(mu_);
+    if (!stream_) {
+      const hipError_t e = hipStreamCreateWithFlags(&stream_, hipStreamNonBlocking);
+      if (e != hipSuccess) {
+        stream_ = nullptr;
+        return e;
+      }
+    }
+    const hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, stream_);
+    return e == hipSuccess ? hipStreamSynchronize(stream_) : e;
+  }
+
+ private:
+  struct Slab {
+    char* base;
+    size_t used;
+    int64_t plans;
+  };
+  std::mutex mu_;
+  std::vector<Slab> slabs_;  // the last one is cut from
+  int64_t plans_ = 0;        // plans that hold device memory
+  hipStream_t stream_ = nullptr;
+};
+
+// One per device, never destroyed: plans may outlive static destructors.
+PlanMemory& plan_memory(int dev) {
+  alignas(PlanMemory) static char room[kMaxDevices][sizeof(PlanMemory)];
+  static const bool made = [] {
+    for (auto& r : room) new (r) PlanMemory();
+    return true;
+  }();
+  (void)made;
+  return *std::launder(reinterpret_cast<PlanMemory*>(room[dev]));
+}
+
+}  // namespace
+
 pkv_status_t upload_plan(HostPlan&& hp, pkv_plan** out) {
   *out = nullptr;
   pkv_plan* plan = new (std::nothrow) pkv_plan();
@@ -623,7 +729,7 @@ pkv_status_t upload_plan(HostPlan&& hp, pkv_plan** out) {
   const size_t n_pt = plan->host.kind == 1 ? plan->host.page_tables.size() * sizeof(int32_t) : 0;
   const size_t total = al(n_units) + al(n_tab) + al(n_pt);
   int dev = -1;
-  if (hipGetDevice(&dev) != hipSuccess) {
+  if (hipGetDevice(&dev) != hipSuccess || dev >= kMaxDevices) {
     delete plan;
     return PKV_ERR_DEVICE;
   }
@@ -668,25 +774,24 @@ pkv_status_t upload_plan(HostPlan&& hp, pkv_plan** out) {
   else
     plan->restore_late_units = kLateRounds * int64_t(cus) * restore_workgroups_per_cu(plan->host);
   if (total > 0) {
-    hipError_t e = hipMalloc(&plan->device_mem, total);
+    std::unique_ptr<char[]> image(new (std::nothrow) char[total]);
+    hipError_t e = image ? plan_memory(dev).allocate(total, &plan->device_mem) : hipErrorOutOfMemory;
     if (e != hipSuccess) {
       plan->device_mem = nullptr;
       delete plan;
       return e == hipErrorOutOfMemory ? PKV_ERR_OUT_OF_MEMORY : PKV_ERR_DEVICE;
     }
+    const size_t at_tab = al(n_units), at_pt = at_tab + al(n_tab);
     char* p = static_cast<char*>(plan->device_mem);
     plan->d_units = reinterpret_cast<Unit*>(p);
-    p += al(n_units);
-    plan->d_tables = reinterpret_cast<double*>(p);
-    p += al(n_tab);
-    plan->d_page_tables = reinterpret_cast<int32_t*>(p);
-    bool ok = true;
-    if (n_units) ok = ok && hipMemcpy(plan->d_units, plan->host.units.data(), n_units, hipMemcpyHostToDevice) == hipSuccess;
-    if (n_tab) ok = ok && hipMemcpy(plan->d_tables, plan->host.tables.data(), n_tab, hipMemcpyHostToDevice) == hipSuccess;
-    if (n_pt)
-      ok = ok && hipMemcpy(plan->d_page_tables, plan->host.page_tables.data(), n_pt, hipMemcpyHostToDevice) == hipSuccess;
-    if (!ok) {
-      (void)hipFree(plan->device_mem);
+    plan->d_tables = reinterpret_cast<double*>(p + at_tab);
+    plan->d_page_tables = reinterpret_cast<int32_t*>(p + at_pt);
+    if (n_units) memcpy(image.get(), plan->host.units.data(), n_units);
+    if (n_tab) memcpy(image.get() + at_tab, plan->host.tables.data(), n_tab);
+    if (n_pt) memcpy(image.get() + at_pt, plan->host.page_tables.data(), n_pt);
+    e = plan_memory(dev).upload(plan->device_mem, image.get(), total);
+    if (e != hipSuccess) {
+      plan_memory(dev).release(plan->device_mem);
       delete plan;
       return PKV_ERR_DEVICE;
     }
@@ -830,7 +935,6 @@ static __device__ __align__(256) unsigned char scratch[pkv::kStagePayloadBytes +
 namespace pkv {
 namespace {
 
-constexpr int kMaxDevices = 64;
 std::mutex g_stage_mu;
 void* g_stage[kMaxDevices] = {};
 
@@ -1091,7 +1195,7 @@ void pkv_free(pkv_plan_t* plan) {
     for (void* e : plan->events)
       if (e) (void)hipEventDestroy(static_cast<hipEvent_t>(e));
     for (void* cs : plan->copy_streams) (void)hipStreamDestroy(static_cast<hipStream_t>(cs));
-    if (plan->device_mem) (void)hipFree(plan->device_mem);
+    if (plan->device_mem) pkv::plan_memory(plan->device).release(plan->device_mem);
     if (switched) (void)hipSetDevice(cur);
   }
   delete plan;
