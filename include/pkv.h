@@ -202,7 +202,11 @@ pkv_status_t pkv_restore(const pkv_plan_t* plan, const void* payload, uint64_t p
  * entries are copied host -> device, into `payload` / `scales` at the
  * checkpoint's own offsets, on copy streams owned by the plan; the layer's
  * restore is then enqueued on `hip_stream` behind those copies.  Copies of
- * layer l + 1 therefore overlap the restore of layer l.  Repair-block
+ * layer l + 1 therefore overlap the restore of layer l.  Plans whose copies
+ * average under 4 MiB are copied by a kernel instead of DMA copies (from pinned
+ * memory that the device can read in place), several layers at a time; a
+ * checkpoint of up to about 16 MiB then goes in one copy launch and one restore
+ * launch on `hip_stream`.  Repair-block
  * payload bytes cross the host link only where a repair block sits between
  * two reused ones closer than 512 KiB apart (one copy then covers all three:
  * cheaper than a second copy's setup); a layer's scale entries, 8 bytes per
@@ -360,7 +364,7 @@ typedef struct {
   int32_t device;             /* HIP device the plan lives on */
   int32_t kind;               /* 0 = restore plan, 1 = checkpoint plan */
   uint64_t host_copy_bytes;   /* restore plans: bytes pkv_restore_from_host copies (F-block ranges + scales) */
-  int64_t host_copies;        /* restore plans: number of host -> device copies it issues (after chunking) */
+  int64_t host_copies;        /* restore plans: number of those copies, as DMA copies are cut */
 } pkv_plan_info_t;
 
 pkv_status_t pkv_plan_query(const pkv_plan_t* plan, pkv_plan_info_t* info);

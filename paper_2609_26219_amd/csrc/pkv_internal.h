@@ -163,6 +163,16 @@ static_assert(kHostCopyStreams >= 1 && kHostCopyStreams <= 32, "copy streams are
 #endif
 constexpr uint64_t kHostChunkBytes = PKV_HOST_CHUNK_BYTES;
 
+// Streamed restore from host memory that the device can read in place: pieces
+// of at most this many bytes, copied by a kernel (pull_kernel), each the same
+// distance apart from layer to layer.
+constexpr uint64_t kPullBytes = 64u << 10;
+struct PullPiece {
+  uint64_t off, stride;  // bytes into the payload or the scales: layer 0, and from layer to layer
+  uint32_t len;
+  uint32_t scales;       // 1: of the scales
+};
+
 // The allocation-free streamed restore stages the checkpoint through a
 // static device buffer: payload windows in its first kStagePayloadBytes, one
 // request-layer's scales in the kStageScaleBytes after them.
@@ -331,6 +341,10 @@ struct pkv_plan {
   // events[1 + l * n + k] the end of layer l's chunks on copy stream k.
   std::vector<void*> copy_streams;
   std::vector<void*> events;
+  // Pieces of one layer for pull_kernel, made on first use.
+  void* pull_mem = nullptr;
+  int64_t pull_pieces = 0;
+  uint64_t pull_layer_bytes = 0;
 };
 namespace pkv {
 // Copy a built host plan to device memory on the current device and wrap it.

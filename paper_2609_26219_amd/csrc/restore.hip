@@ -967,6 +967,99 @@ bool pinned_host(const void* p, const void** mapped) {
   return a.type == hipMemoryTypeHost;
 }
 
+// Copies pieces of the checkpoint from host memory to the device, over the
+// link: kPullGroups workgroups take the pieces of a launch's layers in turn.
+// Few workgroups, so that the restore of the layers before, and whatever else
+// runs, finds room beside them: 16 of 256 threads keep 256 KB of reads in
+// flight, which fills the link (54 GB/s; 32, 64 and 128 are no faster).
+struct PullArgs {
+  const PullPiece* pieces;  // of one layer
+  LayerItems items;
+  uint32_t total;           // pieces of the launch
+  const uint8_t* host_payload;
+  const uint8_t* host_scales;
+  uint8_t* payload;
+  uint8_t* scales;
+};
+constexpr uint32_t kPullGroups = 16;
+
+template <typename T>
+__device__ __forceinline__ void pull_piece(uint8_t* dst, const uint8_t* src, uint32_t len) {
+  constexpr int kDepth = 4;
+  const uint32_t n = len / sizeof(T);
+  const T* from = reinterpret_cast<const T*>(src);
+  T* to = reinterpret_cast<T*>(dst);
+  for (uint32_t i = threadIdx.x; i < n; i += kDepth * kWorkgroup) {
+    T v[kDepth];
+#pragma unroll
+    for (int k = 0; k < kDepth; ++k)
+      if (i + k * kWorkgroup < n) v[k] = __builtin_nontemporal_load(from + i + k * kWorkgroup);
+#pragma unroll
+    for (int k = 0; k < kDepth; ++k)
+      if (i + k * kWorkgroup < n) to[i + k * kWorkgroup] = v[k];
+  }
+}
+
+__global__ __launch_bounds__(kWorkgroup) void pull_kernel(PullArgs a) {
+  for (uint32_t w = blockIdx.x; w < a.total; w += gridDim.x) {
+    const uint32_t l = layer_of(a.items, w);
+    const PullPiece p = a.pieces[w - l * a.items.count.d];
+    const uint64_t off = p.off + uint64_t(a.items.first + l) * p.stride;
+    if (p.scales)
+      pull_piece<u32x2>(a.scales + off, a.host_scales + off, p.len);
+    else
+      pull_piece<u32x4>(a.payload + off, a.host_payload + off, p.len);
+  }
+}
+
+// The pieces of one layer: the copies of layer_copies(), cut.
+pkv_status_t make_pull_pieces(pkv_plan* plan) {
+  std::vector<PullPiece> pieces;
+  uint64_t bytes = 0;
+  try {
+    const auto cut = [&](uint64_t off, uint64_t stride, uint64_t len, uint32_t scales) {
+      for (uint64_t o = 0; o < len; o += kPullBytes)
+        pieces.push_back(PullPiece{off + o, stride, uint32_t(std::min(len - o, kPullBytes)), scales});
+      bytes += len;
+    };
+    for (const RequestCopies& rc : plan->host.copies) {
+      for (const CopyRange& c : rc.ranges) cut(rc.payload_offset + c.off, rc.layer_bytes, c.len, 0);
+      if (rc.scales_needed) cut(rc.scale_offset * 2, rc.layer_scales * 2, rc.layer_scales * 2, 1);
+    }
+  } catch (const std::bad_alloc&) {
+    return PKV_ERR_OUT_OF_MEMORY;
+  }
+  void* mem = nullptr;
+  PlanMemory& memory = plan_memory(plan->device);
+  const hipError_t e = memory.allocate(pieces.size() * sizeof(PullPiece), &mem);
+  if (e != hipSuccess) return e == hipErrorOutOfMemory ? PKV_ERR_OUT_OF_MEMORY : PKV_ERR_DEVICE;
+  if (memory.upload(mem, pieces.data(), pieces.size() * sizeof(PullPiece)) != hipSuccess) {
+    memory.release(mem);
+    return PKV_ERR_DEVICE;
+  }
+  plan->pull_mem = mem;
+  plan->pull_pieces = int64_t(pieces.size());
+  plan->pull_layer_bytes = bytes;
+  return PKV_OK;
+}
+
+// Whether the streamed restore pulls its copies with a kernel instead of
+// enqueueing them on DMA streams.  A DMA copy takes about 16 us of its stream
+// beyond its transfer, and a layer's events and launch some more, while two
+// streams move 57 GB/s and the kernel 54, so the kernel is ahead while copies
+// are small.  us by kernel / by DMA, 8 heads and 32 layers: 300 tokens 383 /
+// 1354, 1024 tokens (1 MB a copy) 1157 / 1540, 3000 tokens (2.6 MB) 3330 / 3617,
+// 8192 tokens (4.7 MB) 8336 / 8239; two heads (1.2 MB) 2258 / 2977.
+bool pulls(const HostPlan& h) {
+  const uint64_t copies = uint64_t(h.info.host_copies);
+  return h.info.host_copy_bytes < copies * (4ull << 20) &&
+         h.info.host_copy_bytes / kPullBytes < (uint64_t(1) << 28);
+}
+// Layers that the pulling kernel and the restore take together: about this
+// many bytes, so that the launches and the event between them are a few
+// percent of a transfer and the last restore, which nothing hides, is short.
+constexpr uint64_t kPullGroupBytes = 16ull << 20;
+
 // Whether the allocation-free restore copies windows of the checkpoint into the
 // stage, instead of reading it over the host link in one launch.  A window
 // costs about 50 us beyond its transfer (its copies' setup, the wait for its
@@ -1070,6 +1163,48 @@ pkv_status_t pkv_restore_from_host(const pkv_plan_t* plan, const void* host_payl
     p->events = std::move(events);
   }
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+  const void *p_mapped = nullptr, *s_mapped = nullptr;
+  bool pull = pkv::pulls(plan->host);
+  if (pull && !p->pull_mem) {  // its pieces cannot be made while the stream is captured
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
+      (void)hipGetLastError();
+      pull = false;
+    }
+    pull = pull && capture == hipStreamCaptureStatusNone;
+  }
+  if (pull && pkv::pinned_host(host_payload, &p_mapped) && pkv::pinned_host(host_scales, &s_mapped) &&
+      p_mapped && s_mapped && reinterpret_cast<uintptr_t>(p_mapped) % 16 == 0 &&
+      reinterpret_cast<uintptr_t>(s_mapped) % 8 == 0) {
+    if (!p->pull_mem && (st = pkv::make_pull_pieces(p)) != PKV_OK) return st;
+    const int64_t group = int64_t(std::max<uint64_t>(1, pkv::kPullGroupBytes / p->pull_layer_bytes));
+    // One group needs no second stream: its restore follows its copies.
+    hipStream_t copies = group >= L ? stream : static_cast<hipStream_t>(p->copy_streams[0]);
+    if (copies != stream && (hipEventRecord(static_cast<hipEvent_t>(p->events[0]), stream) != hipSuccess ||
+                             hipStreamWaitEvent(copies, static_cast<hipEvent_t>(p->events[0]), 0) != hipSuccess))
+      return PKV_ERR_DEVICE;
+    for (int64_t l = 0; l < L; l += group) {
+      const int64_t end = std::min(L, l + group);
+      pkv::PullArgs a;
+      a.pieces = static_cast<const pkv::PullPiece*>(p->pull_mem);
+      a.items = pkv::layer_items(l, end - l, p->pull_pieces);
+      a.total = uint32_t((end - l) * p->pull_pieces);
+      a.host_payload = static_cast<const uint8_t*>(p_mapped);
+      a.host_scales = static_cast<const uint8_t*>(s_mapped);
+      a.payload = static_cast<uint8_t*>(payload);
+      a.scales = static_cast<uint8_t*>(scales);
+      hipLaunchKernelGGL(pkv::pull_kernel, dim3(std::min(a.total, pkv::kPullGroups)), dim3(pkv::kWorkgroup), 0, copies, a);
+      if (hipGetLastError() != hipSuccess) return PKV_ERR_DEVICE;
+      if (copies != stream) {
+        hipEvent_t done = static_cast<hipEvent_t>(p->events[size_t(1 + l)]);
+        if (hipEventRecord(done, copies) != hipSuccess || hipStreamWaitEvent(stream, done, 0) != hipSuccess)
+          return PKV_ERR_DEVICE;
+      }
+      st = pkv::launch_restore(plan, payload, scales, k_cache, v_cache, l, end, 0, plan->host.layer_units, stream);
+      if (st != PKV_OK) return st;
+    }
+    return PKV_OK;
+  }
   const size_t n_copy = p->copy_streams.size();
   auto ev = [&](int64_t i) { return static_cast<hipEvent_t>(p->events[size_t(i)]); };
   // Earlier work on the caller's stream may still read `payload`.
@@ -1082,15 +1217,23 @@ pkv_status_t pkv_restore_from_host(const pkv_plan_t* plan, const void* host_payl
   uint8_t* dp_bytes = static_cast<uint8_t*>(payload);
   uint8_t* ds_bytes = static_cast<uint8_t*>(scales);
   const pkv::HostPlan& h = plan->host;
-  // Copies are cut into chunks of at most kHostChunkBytes and dealt to the
-  // copy streams in turn, so every stream (each feeding its own DMA engine)
-  // stays busy within a layer; layer l's restore waits on every stream that
-  // carried one of its chunks.
-  size_t next = 0;
+  // Copies are cut into chunks of at most kHostChunkBytes, each dealt to the
+  // copy stream with the fewest bytes so far, so every stream (each feeding its
+  // own DMA engine) has the same work; layer l's restore waits on every stream
+  // that carried one of its chunks.  (Dealt in turn, a layer's payload went to
+  // one stream and its scales to the other: 3356 us against 2977 for two heads and 8192 tokens of 32 layers,
+  // 8310 against 8239 for eight heads.)
+  std::vector<uint64_t> queued;
+  try {
+    queued.assign(n_copy, 0);
+  } catch (const std::bad_alloc&) {
+    return PKV_ERR_OUT_OF_MEMORY;
+  }
   auto enqueue = [&](uint8_t* dst, const uint8_t* src, const pkv::CopyRange& c, uint32_t& used) {
     for (uint64_t o = 0; o < c.len; o += pkv::kHostChunkBytes) {
       const uint64_t n = c.len - o < pkv::kHostChunkBytes ? c.len - o : pkv::kHostChunkBytes;
-      const size_t k = next++ % n_copy;
+      const size_t k = size_t(std::min_element(queued.begin(), queued.end()) - queued.begin());
+      queued[k] += n;
       if (hipMemcpyAsync(dst + c.off + o, src + c.off + o, n, hipMemcpyHostToDevice,
                          static_cast<hipStream_t>(p->copy_streams[k])) != hipSuccess)
         return false;
@@ -1188,13 +1331,14 @@ pkv_status_t pkv_restore_from_host_noalloc(const pkv_plan_t* plan, const void* h
 
 void pkv_free(pkv_plan_t* plan) {
   if (!plan) return;
-  if (plan->device_mem || !plan->copy_streams.empty()) {
+  if (plan->device_mem || plan->pull_mem || !plan->copy_streams.empty()) {
     int cur = -1;
     const bool switched = hipGetDevice(&cur) == hipSuccess && cur != plan->device &&
                           hipSetDevice(plan->device) == hipSuccess;
     for (void* e : plan->events)
       if (e) (void)hipEventDestroy(static_cast<hipEvent_t>(e));
     for (void* cs : plan->copy_streams) (void)hipStreamDestroy(static_cast<hipStream_t>(cs));
+    if (plan->pull_mem) pkv::plan_memory(plan->device).release(plan->pull_mem);
     if (plan->device_mem) pkv::plan_memory(plan->device).release(plan->device_mem);
     if (switched) (void)hipSetDevice(cur);
   }

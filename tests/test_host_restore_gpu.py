@@ -181,3 +181,34 @@ def test_pageable_and_foreign_inputs_rejected(torch):
     torch.cuda.synchronize()
     after = dr.host_caches()
     assert np.array_equal(before[0], after[0]) and np.array_equal(before[1], after[1])
+
+
+@pytest.mark.parametrize("params,offset", [
+    # About 4 MB a layer: layers in groups of three, the second beside the first one's restore.
+    (dict(L=5, H=8, D=128, B=32, P=16, n_tokens=(2300, 40), deltas=(-3, 0), rho0s=(7, 11)), 0),
+    # Pieces of 64 KiB and what remains; a request whose only reused blocks are FP16.
+    (dict(L=2, H=5, D=64, B=16, P=8, n_tokens=(700,), deltas=(9,), rho0s=(3,)), 0),
+    # Host buffers that a kernel cannot read in whole loads are copied by DMA.
+    (dict(L=2, H=5, D=64, B=16, P=8, n_tokens=(700,), deltas=(9,), rho0s=(3,)), 4),
+], ids=["two_groups", "piece_tails", "unaligned"])
+def test_streamed_restore_copy_ways(params, offset, torch):
+    from paper_2609_26219_amd.device import DeviceRestore
+
+    case = wl.make_custom(41, tag_set=(0, 1, 2, 3), mix=(1, 1, 1, 1), repair_frac=0.2, out_dtype=wl.OUT_BF16, **params)
+    ckpt = oracle_checkpoint(case)
+    dr = DeviceRestore(case, checkpoint=(np.full(ckpt[0].shape, FILL, np.uint8),
+                                         np.full(ckpt[1].shape, FILL * 0x101, np.uint16)))
+    raw = [ckpt[0].view(np.uint8), ckpt[1].view(np.uint8)]
+    host = [torch.zeros(r.size + 64, dtype=torch.uint8).pin_memory() for r in raw]
+    for h, r in zip(host, raw):
+        h[offset:offset + r.size] = torch.from_numpy(r)
+    nb = lambda t: t.numel() * t.element_size()
+    for _ in range(2):  # the second call finds the plan's pieces made
+        dr.prefill()
+        pb.pkv_restore_from_host(dr.plan, host[0].data_ptr() + offset, raw[0].size, host[1].data_ptr() + offset,
+                                 raw[1].size, dr.payload.data_ptr(), nb(dr.payload), dr.scales.data_ptr(),
+                                 nb(dr.scales), dr.k_cache.data_ptr(), dr.v_cache.data_ptr(),
+                                 pb.cache_nbytes(dr.k_cache, dr.v_cache), torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+    check_full(dr, ckpt)
+    _check_copied_only_reused(case, dr, ckpt)
