@@ -153,7 +153,7 @@ constexpr uint64_t kHostGapBytes = PKV_HOST_GAP_BYTES;
 constexpr int kHostCopyStreams = PKV_HOST_COPY_STREAMS;
 static_assert(kHostCopyStreams >= 1 && kHostCopyStreams <= 32, "copy streams are tracked in a 32-bit mask");
 // Streamed restore: copies are cut into chunks of at most this many bytes,
-// dealt to the copy streams in turn.  One DMA stream alone moves ~40 GB/s;
+// dealt to the copy streams by load.  One DMA stream alone moves ~40 GB/s;
 // two busy together fill the host link (~57 GB/s).  Measured on the
 // 8B-shaped 32-layer checkpoint: 16 MiB chunks on two streams 16.8 ms
 // (uniform 4-bit) and 31.7 ms (mixed tags), against 33.2 / 33.0 ms with one
