@@ -62,7 +62,13 @@ namespace {
 constexpr int kMinWavesPerEU = 4;
 
 // Launches of at most this many rounds of resident workgroups take the late
-// start order of the restore kernel (see Stage).
+// start order of the restore kernel (see Stage).  Separate caches run fewer
+// workgroups at a time and gain from it longer: us late / early, 690
+// workgroups a layer, separate (512 resident) and paired (768): 4 layers 30.0 /
+// 30.8 and 29.6 / 30.0, 8 layers (10.8 and 7.2 rounds) 59.1 / 61.2 and 55.8 /
+// 54.8, 16 layers 124.2 / 124.3 and 116.8 / 114.3, 32 layers 244.8 / 242.9 and
+// 230.9 / 222.4.
+constexpr int64_t kLateRoundsSeparate = 12;
 constexpr int64_t kLateRounds = 6;
 
 // Launches that fit on the device at this many 256-thread workgroups to a
@@ -761,18 +767,17 @@ pkv_status_t upload_plan(HostPlan&& hp, pkv_plan** out) {
   } else {
     (void)hipGetLastError();
   }
-  // Late start order up to kLateRounds rounds of resident workgroups: with
-  // 8B-shaped rows (690 units per layer of an 8K-token suffix, 512 resident)
-  // it measured faster up to 4 layers (5.4 rounds), warm and cold, and
-  // slower cold from 6 layers (8 rounds) on.  Rows narrow enough for
-  // workgroups under kWorkgroup threads take it at any depth: on the 32-layer
-  // 8B-shaped workload's share of one KV head per GPU (one-wave workgroups of
-  // two tokens per thread) it measured 102-112 us against 127-135 us, and
-  // within 1% of the early order at two and four heads.
+  // Late start order up to kLateRounds (separate caches kLateRoundsSeparate)
+  // rounds of resident workgroups.  Rows narrow enough for workgroups under
+  // kWorkgroup threads take it at any depth: on the 32-layer 8B-shaped
+  // workload's share of one KV head per GPU (one-wave workgroups of two tokens
+  // per thread) it measured 102-112 us against 127-135 us, and within 1% of the
+  // early order at two and four heads.
   if (plan->host.workgroup < kWorkgroup)
     plan->restore_late_units = INT64_MAX;
   else
-    plan->restore_late_units = kLateRounds * int64_t(cus) * restore_workgroups_per_cu(plan->host);
+    plan->restore_late_units = (plan->host.model.kv_layout == PKV_KV_SEPARATE ? kLateRoundsSeparate : kLateRounds) *
+                               int64_t(cus) * restore_workgroups_per_cu(plan->host);
   if (total > 0) {
     std::unique_ptr<char[]> image(new (std::nothrow) char[total]);
     hipError_t e = image ? plan_memory(dev).allocate(total, &plan->device_mem) : hipErrorOutOfMemory;
