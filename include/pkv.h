@@ -204,7 +204,8 @@ pkv_status_t pkv_restore(const pkv_plan_t* plan, const void* payload, uint64_t p
  * restore is then enqueued on `hip_stream` behind those copies.  Copies of
  * layer l + 1 therefore overlap the restore of layer l.  Plans whose copies
  * average under 4 MiB are copied by a kernel instead of DMA copies (from pinned
- * memory that the device can read in place), several layers at a time; a
+ * memory that the device can read in place; the kernel's list of copies is part
+ * of the plan), several layers at a time; a
  * checkpoint of up to about 16 MiB then goes in one copy launch and one restore
  * launch on `hip_stream`.  Repair-block
  * payload bytes cross the host link only where a repair block sits between
@@ -226,7 +227,9 @@ pkv_status_t pkv_restore(const pkv_plan_t* plan, const void* payload, uint64_t p
  * must wait until the earlier call's work has finished (successive calls on
  * one stream are ordered by it).  The plan must be a restore plan.  The
  * streams and events are created on the first call and released by
- * pkv_free.  Errors: PKV_ERR_INVALID_ARGUMENT,
+ * pkv_free; apart from those, no call allocates device memory or waits for the
+ * device, so the first one too may be captured in a HIP graph.  Errors:
+ * PKV_ERR_INVALID_ARGUMENT, PKV_ERR_OUT_OF_MEMORY (host memory),
  * PKV_ERR_DEVICE. */
 pkv_status_t pkv_restore_from_host(const pkv_plan_t* plan, const void* host_payload, uint64_t host_payload_bytes,
                                    const void* host_scales, uint64_t host_scale_bytes, void* payload,

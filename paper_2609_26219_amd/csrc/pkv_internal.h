@@ -229,6 +229,8 @@ struct HostPlan {
   int32_t log2_page;
   int64_t layer_units = 0;                  // units.size(), kept when the list itself is dropped
   std::vector<RequestCopies> copies;        // restore plans, per request
+  std::vector<PullPiece> pieces;            // restore plans that pull their copies (pulls()): those of one layer
+  uint64_t pull_layer_bytes = 0;            // bytes of `pieces`
   int64_t rotated_rows = 0;  // restore plans: restored rows whose keys rotate (shift != 0)
   std::vector<uint64_t> req_payload_bytes;  // per request: bytes of its checkpoint payload, all layers
   // Restore plans: whether every request-layer's scales fit the staged restore's static buffer.
@@ -236,6 +238,9 @@ struct HostPlan {
   bool keep_rows = false;  // test hooks: fill `rows`, one entry per unit
   std::vector<UnitRows> rows;
 };
+
+// Whether the streamed restore of a plan copies with a kernel (plan.cpp).
+bool pulls(const HostPlan& hp);
 
 // Copies of layer l of a streamed restore, in order: payload byte ranges and
 // scale byte ranges (neighbouring requests' scales as one).
@@ -318,7 +323,7 @@ uint32_t gather_image(const pkv_model_t& m);
 // The plan object behind pkv_plan_t (host metadata + one device allocation).
 }  // namespace pkv
 struct pkv_plan {
-  pkv::HostPlan host;  // units, tables and page tables are dropped after upload
+  pkv::HostPlan host;  // units, tables, page tables and pieces are dropped after upload
   void* device_mem = nullptr;
   pkv::Unit* d_units = nullptr;
   double* d_tables = nullptr;
@@ -341,10 +346,9 @@ struct pkv_plan {
   // events[1 + l * n + k] the end of layer l's chunks on copy stream k.
   std::vector<void*> copy_streams;
   std::vector<void*> events;
-  // Pieces of one layer for pull_kernel, made on first use.
-  void* pull_mem = nullptr;
+  // Pieces of one layer for pull_kernel (HostPlan::pieces), part of device_mem.
+  pkv::PullPiece* d_pieces = nullptr;
   int64_t pull_pieces = 0;
-  uint64_t pull_layer_bytes = 0;
 };
 namespace pkv {
 // Copy a built host plan to device memory on the current device and wrap it.

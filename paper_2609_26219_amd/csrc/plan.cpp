@@ -272,6 +272,37 @@ StageStep stage_step(const RequestCopies& rc, int64_t l, size_t window) {
   return st;
 }
 
+// Whether the streamed restore pulls its copies with a kernel instead of
+// enqueueing them on DMA streams.  A DMA copy takes about 16 us of its stream
+// beyond its transfer, and a layer's events and launch some more, while two
+// streams move 57 GB/s and the kernel 54, so the kernel is ahead while copies
+// are small.  us by kernel / by DMA, 8 heads and 32 layers: 300 tokens 383 /
+// 1354, 1024 tokens (1 MB a copy) 1157 / 1540, 3000 tokens (2.6 MB) 3330 / 3617,
+// 8192 tokens (4.7 MB) 8336 / 8239; two heads (1.2 MB) 2258 / 2977.
+bool pulls(const HostPlan& h) {
+  const uint64_t copies = uint64_t(h.info.host_copies);
+  return h.info.host_copy_bytes < copies * (4ull << 20) &&
+         h.info.host_copy_bytes / kPullBytes < (uint64_t(1) << 28);
+}
+namespace {
+
+// The pieces of one layer: the copies of layer_copies(), cut.
+void cut_pieces(HostPlan& hp) {
+  hp.pieces.clear();
+  hp.pull_layer_bytes = 0;
+  const auto cut = [&](uint64_t off, uint64_t stride, uint64_t len, uint32_t scales) {
+    for (uint64_t o = 0; o < len; o += kPullBytes)
+      hp.pieces.push_back(PullPiece{off + o, stride, uint32_t(std::min(len - o, kPullBytes)), scales});
+    hp.pull_layer_bytes += len;
+  };
+  for (const RequestCopies& rc : hp.copies) {
+    for (const CopyRange& c : rc.ranges) cut(rc.payload_offset + c.off, rc.layer_bytes, c.len, 0);
+    if (rc.scales_needed) cut(rc.scale_offset * 2, rc.layer_scales * 2, rc.layer_scales * 2, 1);
+  }
+}
+
+}  // namespace
+
 pkv_status_t build_host_plan(const pkv_model_t* model, const pkv_request_t* requests, int32_t num_requests,
                              HostPlan* out) {
   pkv_status_t st = check_model(model);
@@ -438,6 +469,7 @@ pkv_status_t build_host_plan(const pkv_model_t* model, const pkv_request_t* requ
         hp.info.host_copies += int64_t((c.len + kHostChunkBytes - 1) / kHostChunkBytes);
       }
     }
+    if (pulls(hp)) cut_pieces(hp);
   } catch (const std::bad_alloc&) {
     return PKV_ERR_OUT_OF_MEMORY;
   }
@@ -736,6 +768,25 @@ pkv_status_t pkv_internal_stream_schedule(const pkv_model_t* model, const pkv_re
         ++k;
       }
   }
+  return PKV_OK;
+}
+
+// Internal test hook (not part of pkv.h): the pieces of one layer that the
+// streamed restore's copy kernel takes, 4 uint64 each (byte offset, bytes from
+// layer to layer, length, 1 for the scales); none where DMA copies are used.
+pkv_status_t pkv_internal_pull_pieces(const pkv_model_t* model, const pkv_request_t* requests, int32_t num_requests,
+                                      uint64_t* out, int64_t capacity, int64_t* count) {
+  if (!count) return PKV_ERR_INVALID_ARGUMENT;
+  pkv::HostPlan hp;
+  pkv_status_t st = pkv::build_host_plan(model, requests, num_requests, &hp);
+  if (st != PKV_OK) return st;
+  *count = int64_t(hp.pieces.size());
+  if (out && capacity >= *count)
+    for (const pkv::PullPiece& p : hp.pieces) {
+      const uint64_t v[4] = {p.off, p.stride, p.len, p.scales};
+      memcpy(out, v, sizeof(v));
+      out += 4;
+    }
   return PKV_OK;
 }
 

@@ -733,7 +733,8 @@ pkv_status_t upload_plan(HostPlan&& hp, pkv_plan** out) {
   const size_t n_tab = plan->host.tables.size() * sizeof(double);
   // Restore work items carry their page; only checkpoint plans read page tables on the device.
   const size_t n_pt = plan->host.kind == 1 ? plan->host.page_tables.size() * sizeof(int32_t) : 0;
-  const size_t total = al(n_units) + al(n_tab) + al(n_pt);
+  const size_t n_pull = plan->host.pieces.size() * sizeof(PullPiece);
+  const size_t total = al(n_units) + al(n_tab) + al(n_pt) + al(n_pull);
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev >= kMaxDevices) {
     delete plan;
@@ -786,14 +787,17 @@ pkv_status_t upload_plan(HostPlan&& hp, pkv_plan** out) {
       delete plan;
       return e == hipErrorOutOfMemory ? PKV_ERR_OUT_OF_MEMORY : PKV_ERR_DEVICE;
     }
-    const size_t at_tab = al(n_units), at_pt = at_tab + al(n_tab);
+    const size_t at_tab = al(n_units), at_pt = at_tab + al(n_tab), at_pull = at_pt + al(n_pt);
     char* p = static_cast<char*>(plan->device_mem);
     plan->d_units = reinterpret_cast<Unit*>(p);
     plan->d_tables = reinterpret_cast<double*>(p + at_tab);
     plan->d_page_tables = reinterpret_cast<int32_t*>(p + at_pt);
+    plan->d_pieces = reinterpret_cast<PullPiece*>(p + at_pull);
+    plan->pull_pieces = int64_t(plan->host.pieces.size());
     if (n_units) memcpy(image.get(), plan->host.units.data(), n_units);
     if (n_tab) memcpy(image.get() + at_tab, plan->host.tables.data(), n_tab);
     if (n_pt) memcpy(image.get() + at_pt, plan->host.page_tables.data(), n_pt);
+    if (n_pull) memcpy(image.get() + at_pull, plan->host.pieces.data(), n_pull);
     e = plan_memory(dev).upload(plan->device_mem, image.get(), total);
     if (e != hipSuccess) {
       plan_memory(dev).release(plan->device_mem);
@@ -805,6 +809,7 @@ pkv_status_t upload_plan(HostPlan&& hp, pkv_plan** out) {
   std::vector<Unit>().swap(plan->host.units);
   std::vector<double>().swap(plan->host.tables);
   std::vector<int32_t>().swap(plan->host.page_tables);
+  std::vector<PullPiece>().swap(plan->host.pieces);
   *out = plan;
   return PKV_OK;
 }
@@ -1017,49 +1022,6 @@ __global__ __launch_bounds__(kWorkgroup) void pull_kernel(PullArgs a) {
   }
 }
 
-// The pieces of one layer: the copies of layer_copies(), cut.
-pkv_status_t make_pull_pieces(pkv_plan* plan) {
-  std::vector<PullPiece> pieces;
-  uint64_t bytes = 0;
-  try {
-    const auto cut = [&](uint64_t off, uint64_t stride, uint64_t len, uint32_t scales) {
-      for (uint64_t o = 0; o < len; o += kPullBytes)
-        pieces.push_back(PullPiece{off + o, stride, uint32_t(std::min(len - o, kPullBytes)), scales});
-      bytes += len;
-    };
-    for (const RequestCopies& rc : plan->host.copies) {
-      for (const CopyRange& c : rc.ranges) cut(rc.payload_offset + c.off, rc.layer_bytes, c.len, 0);
-      if (rc.scales_needed) cut(rc.scale_offset * 2, rc.layer_scales * 2, rc.layer_scales * 2, 1);
-    }
-  } catch (const std::bad_alloc&) {
-    return PKV_ERR_OUT_OF_MEMORY;
-  }
-  void* mem = nullptr;
-  PlanMemory& memory = plan_memory(plan->device);
-  const hipError_t e = memory.allocate(pieces.size() * sizeof(PullPiece), &mem);
-  if (e != hipSuccess) return e == hipErrorOutOfMemory ? PKV_ERR_OUT_OF_MEMORY : PKV_ERR_DEVICE;
-  if (memory.upload(mem, pieces.data(), pieces.size() * sizeof(PullPiece)) != hipSuccess) {
-    memory.release(mem);
-    return PKV_ERR_DEVICE;
-  }
-  plan->pull_mem = mem;
-  plan->pull_pieces = int64_t(pieces.size());
-  plan->pull_layer_bytes = bytes;
-  return PKV_OK;
-}
-
-// Whether the streamed restore pulls its copies with a kernel instead of
-// enqueueing them on DMA streams.  A DMA copy takes about 16 us of its stream
-// beyond its transfer, and a layer's events and launch some more, while two
-// streams move 57 GB/s and the kernel 54, so the kernel is ahead while copies
-// are small.  us by kernel / by DMA, 8 heads and 32 layers: 300 tokens 383 /
-// 1354, 1024 tokens (1 MB a copy) 1157 / 1540, 3000 tokens (2.6 MB) 3330 / 3617,
-// 8192 tokens (4.7 MB) 8336 / 8239; two heads (1.2 MB) 2258 / 2977.
-bool pulls(const HostPlan& h) {
-  const uint64_t copies = uint64_t(h.info.host_copies);
-  return h.info.host_copy_bytes < copies * (4ull << 20) &&
-         h.info.host_copy_bytes / kPullBytes < (uint64_t(1) << 28);
-}
 // Layers that the pulling kernel and the restore take together: about this
 // many bytes, so that the launches and the event between them are a few
 // percent of a transfer and the last restore, which nothing hides, is short.
@@ -1169,20 +1131,10 @@ pkv_status_t pkv_restore_from_host(const pkv_plan_t* plan, const void* host_payl
   }
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const void *p_mapped = nullptr, *s_mapped = nullptr;
-  bool pull = pkv::pulls(plan->host);
-  if (pull && !p->pull_mem) {  // its pieces cannot be made while the stream is captured
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
-      (void)hipGetLastError();
-      pull = false;
-    }
-    pull = pull && capture == hipStreamCaptureStatusNone;
-  }
-  if (pull && pkv::pinned_host(host_payload, &p_mapped) && pkv::pinned_host(host_scales, &s_mapped) &&
+  if (plan->pull_pieces > 0 && pkv::pinned_host(host_payload, &p_mapped) && pkv::pinned_host(host_scales, &s_mapped) &&
       p_mapped && s_mapped && reinterpret_cast<uintptr_t>(p_mapped) % 16 == 0 &&
       reinterpret_cast<uintptr_t>(s_mapped) % 8 == 0) {
-    if (!p->pull_mem && (st = pkv::make_pull_pieces(p)) != PKV_OK) return st;
-    const int64_t group = int64_t(std::max<uint64_t>(1, pkv::kPullGroupBytes / p->pull_layer_bytes));
+    const int64_t group = int64_t(std::max<uint64_t>(1, pkv::kPullGroupBytes / plan->host.pull_layer_bytes));
     // One group needs no second stream: its restore follows its copies.
     hipStream_t copies = group >= L ? stream : static_cast<hipStream_t>(p->copy_streams[0]);
     if (copies != stream && (hipEventRecord(static_cast<hipEvent_t>(p->events[0]), stream) != hipSuccess ||
@@ -1191,9 +1143,9 @@ pkv_status_t pkv_restore_from_host(const pkv_plan_t* plan, const void* host_payl
     for (int64_t l = 0; l < L; l += group) {
       const int64_t end = std::min(L, l + group);
       pkv::PullArgs a;
-      a.pieces = static_cast<const pkv::PullPiece*>(p->pull_mem);
-      a.items = pkv::layer_items(l, end - l, p->pull_pieces);
-      a.total = uint32_t((end - l) * p->pull_pieces);
+      a.pieces = plan->d_pieces;
+      a.items = pkv::layer_items(l, end - l, plan->pull_pieces);
+      a.total = uint32_t((end - l) * plan->pull_pieces);
       a.host_payload = static_cast<const uint8_t*>(p_mapped);
       a.host_scales = static_cast<const uint8_t*>(s_mapped);
       a.payload = static_cast<uint8_t*>(payload);
@@ -1336,14 +1288,13 @@ pkv_status_t pkv_restore_from_host_noalloc(const pkv_plan_t* plan, const void* h
 
 void pkv_free(pkv_plan_t* plan) {
   if (!plan) return;
-  if (plan->device_mem || plan->pull_mem || !plan->copy_streams.empty()) {
+  if (plan->device_mem || !plan->copy_streams.empty()) {
     int cur = -1;
     const bool switched = hipGetDevice(&cur) == hipSuccess && cur != plan->device &&
                           hipSetDevice(plan->device) == hipSuccess;
     for (void* e : plan->events)
       if (e) (void)hipEventDestroy(static_cast<hipEvent_t>(e));
     for (void* cs : plan->copy_streams) (void)hipStreamDestroy(static_cast<hipStream_t>(cs));
-    if (plan->pull_mem) pkv::plan_memory(plan->device).release(plan->pull_mem);
     if (plan->device_mem) pkv::plan_memory(plan->device).release(plan->device_mem);
     if (switched) (void)hipSetDevice(cur);
   }

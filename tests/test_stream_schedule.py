@@ -95,3 +95,51 @@ def test_stream_schedule(maker):
             else:
                 merged.append((o, n))
         assert got_s == merged, l
+
+
+def pull_pieces(shape, requests):
+    fn = pb.load().pkv_internal_pull_pieces
+    fn.argtypes = [ctypes.POINTER(pb.PkvModel), ctypes.POINTER(pb.PkvRequest), ctypes.c_int32, ctypes.c_void_p,
+                   ctypes.c_int64, ctypes.POINTER(ctypes.c_int64)]
+    fn.restype = ctypes.c_int32
+    m, reqs, n = pb.make_model(shape), pb._Requests(requests), ctypes.c_int64()
+    assert fn(ctypes.byref(m), reqs.array, reqs.count, None, 0, ctypes.byref(n)) == 0
+    out = np.zeros((n.value, 4), np.uint64)
+    assert fn(ctypes.byref(m), reqs.array, reqs.count, out.ctypes.data, len(out), ctypes.byref(n)) == 0
+    return out.astype(np.int64)
+
+
+def _bytes_of(ranges):
+    """Merged byte ranges."""
+    out = []
+    for o, n in sorted((int(o), int(n)) for o, n in ranges):
+        if out and out[-1][0] + out[-1][1] >= o:
+            out[-1][1] = max(out[-1][1], o + n - out[-1][0])
+        else:
+            out.append([o, n])
+    return out
+
+
+@pytest.mark.parametrize("maker", CASES, ids=["three_requests_3l", "tiny", "three_requests", "no_repair", "all_repair", "fp16_only"])
+def test_pull_pieces_are_the_plans(maker):
+    """The copy kernel's pieces are part of the host plan (so a call needs no memory for them): layer by layer they
+    are the scheduled copies, whole 16-byte (payload) and 8-byte (scales) loads, none longer than 64 KiB."""
+    case = maker()
+    pay, sc, layers = schedule(case.shape, case.requests)
+    pieces = pull_pieces(case.shape, case.requests)
+    assert (len(pieces) > 0) == (len(pay) > 0)
+    for which, copies, first in ((0, pay, layers[1]), (1, sc, layers[2])):
+        mine = pieces[pieces[:, 3] == which]
+        unit = 8 if which else 16
+        assert (mine[:, :3] % unit == 0).all() and (mine[:, 2] > 0).all() and (mine[:, 2] <= 65536).all()
+        for l in range(case.shape.num_layers):
+            got = [(o + l * stride, n) for o, stride, n, _ in mine]
+            assert _bytes_of(got) == _bytes_of(copies[first[l]:first[l + 1]])
+            assert sum(n for _, n in got) == int(copies[first[l]:first[l + 1], 1].sum())
+
+
+def test_large_copies_have_no_pieces():
+    """Copies of 4 MiB and more go to DMA streams: their plans hold no pieces."""
+    case = wl.make_custom(8, L=1, H=8, D=128, B=32, P=16, n_tokens=(8192,), deltas=(5,), tag_set=(0,), mix=(1,),
+                          repair_frac=0.0)
+    assert len(pull_pieces(case.shape, case.requests)) == 0
