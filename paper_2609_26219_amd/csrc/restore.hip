@@ -52,6 +52,7 @@
 
 #include "pkv.h"
 #include "pkv_internal.h"
+#include "plan_memory.h"
 
 namespace pkv {
 namespace {
@@ -622,102 +623,32 @@ namespace {
 
 constexpr int kMaxDevices = 64;
 
-// Device memory of plans, cut from slabs: a resume's plan is 0.1-0.3 MB and
-// lives for one restore, and an allocation of its own costs a hipMalloc and,
-// when it is freed, a wait for everything the device still runs (hipFree).
-// Plans of more than a quarter slab keep an allocation of their own.  A slab
-// hands out each byte once; its memory is used again only after a device
-// synchronisation that follows the release of every plan in it, so a plan
-// that is freed while a launch still reads it stays readable, as with hipFree.
-// Slabs behind the current one are freed with their last plan, and all are
-// when no plan of the device is left.
-class PlanMemory {
- public:
-  static constexpr size_t kSlab = size_t(4) << 20;
-
-  hipError_t allocate(size_t bytes, void** out) {
-    std::lock_guard<std::mutex> lock(mu_);
-    hipError_t e = hipSuccess;
-    if (bytes > kSlab / 4) {
-      e = hipMalloc(out, bytes);
-    } else {
-      if (slabs_.empty() || slabs_.back().used + bytes > kSlab) {
-        if (!slabs_.empty() && slabs_.back().plans == 0) {
-          if ((e = hipDeviceSynchronize()) != hipSuccess) return e;
-          slabs_.back().used = 0;
-        } else {
-          void* p = nullptr;
-          if ((e = hipMalloc(&p, kSlab)) != hipSuccess) return e;
-          try {
-            slabs_.push_back(Slab{static_cast<char*>(p), 0, 0});
-          } catch (const std::bad_alloc&) {
-            (void)hipFree(p);
-            return hipErrorOutOfMemory;
-          }
-        }
-      }
-      Slab& s = slabs_.back();
-      *out = s.base + s.used;
-      s.used += (bytes + 255) & ~size_t(255);
-      ++s.plans;
-    }
-    if (e == hipSuccess) ++plans_;
-    return e;
+// The runtime calls that PlanMemory makes.
+struct HipRuntime {
+  using Error = hipError_t;
+  using Stream = hipStream_t;
+  static constexpr Error kSuccess = hipSuccess, kOutOfMemory = hipErrorOutOfMemory;
+  static Error malloc(void** p, size_t bytes) { return hipMalloc(p, bytes); }
+  static void free(void* p) { (void)hipFree(p); }
+  static Error device_synchronize() { return hipDeviceSynchronize(); }
+  static void clear_error() { (void)hipGetLastError(); }
+  static Error stream_create(Stream* s) { return hipStreamCreateWithFlags(s, hipStreamNonBlocking); }
+  static Error copy(void* dst, const void* src, size_t bytes, Stream s) {
+    return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
   }
-
-  void release(void* p) {
-    std::lock_guard<std::mutex> lock(mu_);
-    --plans_;
-    size_t i = 0;
-    while (i < slabs_.size() && !(p >= slabs_[i].base && p < slabs_[i].base + kSlab)) ++i;
-    if (i == slabs_.size()) {
-      (void)hipFree(p);
-    } else if (--slabs_[i].plans == 0 && i + 1 < slabs_.size()) {
-      (void)hipFree(slabs_[i].base);
-      slabs_.erase(slabs_.begin() + std::ptrdiff_t(i));
-    }
-    if (plans_ > 0) return;
-    for (const Slab& s : slabs_) (void)hipFree(s.base);
-    slabs_.clear();
-  }
-
-  // Copy `bytes` of host memory to the device and wait for it, on a stream of
-  // the library's own: the copy does not queue behind the restores that the
-  // caller's streams still run.
-  hipError_t upload(void* dst, const void* src, size_t bytes) {
-    std::lock_guard<std::mutex> lock(mu_);
-    if (!stream_) {
-      const hipError_t e = hipStreamCreateWithFlags(&stream_, hipStreamNonBlocking);
-      if (e != hipSuccess) {
-        stream_ = nullptr;
-        return e;
-      }
-    }
-    const hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, stream_);
-    return e == hipSuccess ? hipStreamSynchronize(stream_) : e;
-  }
-
- private:
-  struct Slab {
-    char* base;
-    size_t used;
-    int64_t plans;
-  };
-  std::mutex mu_;
-  std::vector<Slab> slabs_;  // the last one is cut from
-  int64_t plans_ = 0;        // plans that hold device memory
-  hipStream_t stream_ = nullptr;
+  static Error stream_synchronize(Stream s) { return hipStreamSynchronize(s); }
 };
+using DevicePlans = PlanMemory<HipRuntime>;
 
 // One per device, never destroyed: plans may outlive static destructors.
-PlanMemory& plan_memory(int dev) {
-  alignas(PlanMemory) static char room[kMaxDevices][sizeof(PlanMemory)];
+DevicePlans& plan_memory(int dev) {
+  alignas(DevicePlans) static char room[kMaxDevices][sizeof(DevicePlans)];
   static const bool made = [] {
-    for (auto& r : room) new (r) PlanMemory();
+    for (auto& r : room) new (r) DevicePlans();
     return true;
   }();
   (void)made;
-  return *std::launder(reinterpret_cast<PlanMemory*>(room[dev]));
+  return *std::launder(reinterpret_cast<DevicePlans*>(room[dev]));
 }
 
 }  // namespace

@@ -1,7 +1,7 @@
 """Plans share slabs of device memory: work lists of many plans alive at once,
 freed in any order and made again keep their contents, from several threads
 too, and a plan freed right behind its launch stays readable until the launch
-is done."""
+is done, also where a slab is filled again."""
 import threading
 
 import numpy as np
@@ -84,6 +84,36 @@ def test_plan_freed_behind_its_launch(torch):
     torch.cuda.synchronize()
     check_full(dr, ckpt)
     del new
+
+
+def test_slab_is_reused_behind_launches(torch):
+    """Work lists of 250 KB, each freed right behind a launch that still waits on its stream: 40 of them use a 4 MiB slab
+    more than twice, and every launch finds its own list."""
+    from paper_2609_26219_amd.device import DeviceRestore
+
+    keep = wl.make_custom(100, L=1, H=1, D=16, B=2, P=2, n_tokens=(60000,), deltas=(1,), rho0s=(0,), repair_frac=0.0)
+    kept = pb.pkv_restore_plan(keep.shape, keep.requests)  # an allocation of its own; with it the slab outlives the others
+    cases = [wl.make_custom(101 + i, L=1, H=1, D=16, B=2, P=2, n_tokens=(7000 + 100 * (i % 7),), deltas=(5 - 3 * i,), rho0s=(i,),
+                            tag_set=(0, 1, 2, 3), mix=(1, 1, 1, 1), repair_frac=0.1, out_dtype=wl.OUT_BF16) for i in range(10)]
+    ckpts = [oracle_checkpoint(c) for c in cases]
+    drs = [DeviceRestore(c, checkpoint=k) for c, k in zip(cases, ckpts)]
+    side = torch.cuda.Stream()
+    for turn in range(4):
+        for dr in drs:
+            dr.prefill()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            busy = torch.randn(4096, 4096, device="cuda")
+            for _ in range(20):
+                busy = torch.tanh(busy @ busy)
+            for dr, case in zip(drs, cases):
+                plan = pb.pkv_restore_plan(case.shape, case.requests)
+                pb.restore_tensors(plan, dr.payload, dr.scales, dr.k_cache, dr.v_cache)
+                pb.pkv_free(plan)
+        torch.cuda.synchronize()
+        for dr, ckpt in zip(drs, ckpts):
+            check_full(dr, ckpt)
+    pb.pkv_free(kept)
 
 
 def test_plans_from_several_threads(torch):
