@@ -20,7 +20,8 @@
 // first load each row's page from the page table, all of them at once, and
 // then the rows through 64-bit addresses.  The general kernel remains for
 // tiles of more than 128 loads per lane (it reads a tile twice: range pass,
-// then encode pass).  In all, the waves of one workgroup encode
+// then encode pass) and for writes of more tiles than one launch of the others
+// can hold (gather_launch).  In all, the waves of one workgroup encode
 // neighbouring tiles, so they write neighbouring pieces of the same rows into
 // one L2.
 //
@@ -626,9 +627,6 @@ __global__ __launch_bounds__(kGatherMaxWaves * 64) void gather_tile_kernel(TileA
 // measured 6.6% faster on the 70B-shaped write (5488-5494 against 5880-5889
 // us).  Every wave passes the barrier exactly once, FP16 tiles and waves past
 // the last tile included.
-constexpr int kSplitLoads = 8;
-constexpr int kSplitWaves = 8;
-
 template <bool BF16, bool WIDE>
 __global__ __launch_bounds__(kGatherMaxWaves * 64) void gather_split_kernel(TileArgs s, const Unit* __restrict__ units) {
   __shared__ float s_rng[kGatherMaxWaves][2];
@@ -673,26 +671,27 @@ __global__ __launch_bounds__(kGatherMaxWaves * 64) void gather_split_kernel(Tile
 }
 
 template <bool BF16, bool WIDE, int NL>
-void launch_tile(const TileArgs& s, const Unit* units, int wg, uint32_t image, uint32_t cap, hipStream_t stream) {
-  const uint32_t waves = uint32_t(wg) / 64;
-  const dim3 grid((s.num_tiles + waves - 1) / waves);
+void launch_tile(const GatherLaunch& l, const TileArgs& s, const Unit* units, uint32_t image, uint32_t cap,
+                 hipStream_t stream) {
   if (image)
-    hipLaunchKernelGGL((gather_tile_kernel<BF16, NL, true, WIDE>), grid, dim3(wg), std::max(image, cap), stream, s,
-                       units);
+    hipLaunchKernelGGL((gather_tile_kernel<BF16, NL, true, WIDE>), dim3(l.grid), dim3(l.threads), std::max(image, cap),
+                       stream, s, units);
   else
-    hipLaunchKernelGGL((gather_tile_kernel<BF16, NL, false, WIDE>), grid, dim3(wg), 0, stream, s, units);
+    hipLaunchKernelGGL((gather_tile_kernel<BF16, NL, false, WIDE>), dim3(l.grid), dim3(l.threads), 0, stream, s, units);
 }
 
 template <bool BF16, bool WIDE>
-void launch_tiles(TileArgs s, const Unit* units, int nload, int wg, uint32_t image, uint32_t cap,
+void launch_tiles(const GatherLaunch& l, const TileArgs& s, const Unit* units, uint32_t image, uint32_t cap,
                   hipStream_t stream) {
-  if (nload <= 2) return launch_tile<BF16, WIDE, 2>(s, units, wg, image, cap, stream);
-  if (nload <= 4) return launch_tile<BF16, WIDE, 4>(s, units, wg, image, cap, stream);
-  if (nload <= 8) return launch_tile<BF16, WIDE, 8>(s, units, wg, image, cap, stream);
-  s.split = (nload + kSplitLoads - 1) / kSplitLoads;
-  s.group = s.split < kSplitWaves ? kSplitWaves / s.split : 1;
-  const dim3 grid((s.num_tiles + s.group - 1) / s.group), block(64 * s.split * s.group);
-  hipLaunchKernelGGL((gather_split_kernel<BF16, WIDE>), grid, block, 0, stream, s, units);
+  if (l.kernel == GatherLaunch::kSplit) {
+    hipLaunchKernelGGL((gather_split_kernel<BF16, WIDE>), dim3(l.grid), dim3(l.threads), 0, stream, s, units);
+    return;
+  }
+  switch (l.loads) {
+    case 2: return launch_tile<BF16, WIDE, 2>(l, s, units, image, cap, stream);
+    case 4: return launch_tile<BF16, WIDE, 4>(l, s, units, image, cap, stream);
+    default: return launch_tile<BF16, WIDE, 8>(l, s, units, image, cap, stream);
+  }
 }
 
 bool overlap(const void* a, uint64_t na, const void* b, uint64_t nb) {
@@ -769,25 +768,22 @@ pkv_status_t pkv_quantize_gather(const pkv_plan_t* plan, const void* k_cache, co
   a.nchunk = (nload + pkv::kGeneralLoads - 1) / pkv::kGeneralLoads;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const bool bf16 = m.out_dtype == PKV_OUT_BF16;
-  if (nload <= pkv::kSplitLoads * pkv::kGatherMaxWaves) {
-    const int64_t tiles = info.num_units * 2 * m.num_kv_heads;
-    if (tiles * 64 >= (int64_t(1) << 32)) return PKV_ERR_DEVICE;  // no grid holds them
+  const pkv::GatherLaunch l = pkv::gather_launch(m, info.num_units);
+  if (l.kernel == pkv::GatherLaunch::kNone) return PKV_ERR_DEVICE;
+  if (l.kernel == pkv::GatherLaunch::kGeneral) {
+    if (bf16)
+      hipLaunchKernelGGL((pkv::gather_kernel<true, pkv::kGeneralLoads>), dim3(l.grid), dim3(l.threads), 0, stream, a);
+    else
+      hipLaunchKernelGGL((pkv::gather_kernel<false, pkv::kGeneralLoads>), dim3(l.grid), dim3(l.threads), 0, stream, a);
+  } else {
     pkv::TileArgs sa;
     sa.g = a;
-    sa.num_tiles = uint32_t(tiles);
-    sa.split = sa.group = 1;
-    // Blocks on more than kUnitPages pages, and layer slices whose rows are
-    // out of a 32-bit offset's reach, look their pages up (load_tile).
-    const bool wide = m.block_tokens > 2 * m.page_size + 1 || a.layer_elems * 2 >= (int64_t(1) << 32);
-    const auto launch = bf16 ? wide ? pkv::launch_tiles<true, true> : pkv::launch_tiles<true, false>
-                             : wide ? pkv::launch_tiles<false, true> : pkv::launch_tiles<false, false>;
-    launch(sa, plan->d_units, nload, plan->host.workgroup, pkv::gather_image(m), plan->cap_lds, stream);
-  } else {
-    const dim3 grid(static_cast<uint32_t>(2 * info.num_units)), block(plan->host.workgroup);
-    if (bf16)
-      hipLaunchKernelGGL((pkv::gather_kernel<true, pkv::kGeneralLoads>), grid, block, 0, stream, a);
-    else
-      hipLaunchKernelGGL((pkv::gather_kernel<false, pkv::kGeneralLoads>), grid, block, 0, stream, a);
+    sa.num_tiles = uint32_t(info.num_units * 2 * m.num_kv_heads);
+    sa.split = l.split;
+    sa.group = l.group;
+    const auto launch = bf16 ? l.wide ? pkv::launch_tiles<true, true> : pkv::launch_tiles<true, false>
+                             : l.wide ? pkv::launch_tiles<false, true> : pkv::launch_tiles<false, false>;
+    launch(l, sa, plan->d_units, pkv::gather_image(m), plan->cap_lds, stream);
   }
   return hipGetLastError() == hipSuccess ? PKV_OK : PKV_ERR_DEVICE;
 }

@@ -320,6 +320,26 @@ int32_t gather_loads(const pkv_model_t& m);
 constexpr uint32_t kTileImageMax = 64u << 10;
 uint32_t gather_image(const pkv_model_t& m);
 
+// Which kernel a checkpoint write of `units` work items (all layers) takes, and its launch.
+//   kTile   one wave per tile of at most 8 loads per lane, `loads` of them in registers (2, 4 or 8);
+//   kSplit  tiles of 9 to 128 loads on `split` waves of kSplitLoads each, `group` tiles to a workgroup of about
+//           kSplitWaves waves;
+//   kGeneral  larger tiles, and writes whose tiles are more than one launch of the other two can hold (it takes
+//           at most kGatherMaxWaves waves per block and cache, each looping over its heads, where those take one per
+//           tile and more: with 256 heads of 16 they reach the limit 16 times sooner);
+//   kNone   a launch is limited to 2^32 - 1 threads.
+// `wide`: blocks on more than kUnitPages pages, and layer slices whose rows are out of a 32-bit offset's reach, look
+// their pages up (load_tile).
+constexpr int kSplitLoads = 8;
+constexpr int kSplitWaves = 8;
+struct GatherLaunch {
+  enum Kernel : int32_t { kNone, kTile, kSplit, kGeneral } kernel;
+  int32_t loads, split, group, threads;
+  bool wide;
+  uint32_t grid;
+};
+GatherLaunch gather_launch(const pkv_model_t& m, int64_t units);
+
 // The plan object behind pkv_plan_t (host metadata + one device allocation).
 }  // namespace pkv
 struct pkv_plan {

@@ -493,6 +493,33 @@ uint32_t gather_image(const pkv_model_t& m) {
   return gather_loads(m) <= 8 && m.num_kv_heads <= kGatherMaxWaves && image <= kTileImageMax ? uint32_t(image) : 0;
 }
 
+GatherLaunch gather_launch(const pkv_model_t& m, int64_t units) {
+  GatherLaunch g;
+  const int32_t nload = gather_loads(m);
+  const int64_t tiles = units * 2 * m.num_kv_heads;
+  g.loads = nload <= 2 ? 2 : nload <= 4 ? 4 : 8;
+  g.split = g.group = 1;
+  g.wide = m.block_tokens > 2 * m.page_size + 1 || layer_elems(m) * 2 >= (int64_t(1) << 32);
+  g.grid = 0;
+  const auto fits = [&](GatherLaunch::Kernel kernel, int64_t grid, int32_t threads) {
+    if (grid * threads >= (int64_t(1) << 32)) return false;
+    g.kernel = kernel;
+    g.grid = uint32_t(grid);
+    g.threads = threads;
+    return true;
+  };
+  const int32_t wg = gather_workgroup(m);
+  if (nload <= 8) {
+    if (fits(GatherLaunch::kTile, ceil_div(tiles, wg / 64), wg)) return g;
+  } else if (nload <= kSplitLoads * kGatherMaxWaves) {
+    g.split = int32_t(ceil_div(nload, kSplitLoads));
+    g.group = g.split < kSplitWaves ? kSplitWaves / g.split : 1;
+    if (fits(GatherLaunch::kSplit, ceil_div(tiles, g.group), 64 * g.split * g.group)) return g;
+  }
+  if (!fits(GatherLaunch::kGeneral, 2 * units, wg)) g.kernel = GatherLaunch::kNone;
+  return g;
+}
+
 int gather_workgroups_per_cu(const HostPlan& hp) {
   const pkv_plan_info_t& info = hp.info;
   const int waves = hp.workgroup / 64;
@@ -824,6 +851,17 @@ pkv_status_t pkv_internal_stage_schedule(const pkv_model_t* model, const pkv_req
         }
         ++*n_steps;
       }
+  return PKV_OK;
+}
+
+// Internal test hook (not part of pkv.h): gather_launch() as 7 int64: kernel,
+// loads, split, group, threads, wide, grid.
+pkv_status_t pkv_internal_gather_launch(const pkv_model_t* model, int64_t units, int64_t* out) {
+  pkv_status_t st = pkv::check_model(model);
+  if (st != PKV_OK || units < 1 || !out) return PKV_ERR_INVALID_ARGUMENT;
+  const pkv::GatherLaunch g = pkv::gather_launch(*model, units);
+  const int64_t v[7] = {g.kernel, g.loads, g.split, g.group, g.threads, g.wide, g.grid};
+  memcpy(out, v, sizeof(v));
   return PKV_OK;
 }
 

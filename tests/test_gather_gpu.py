@@ -246,3 +246,31 @@ def test_checkpoint_into_pinned_host_memory(name, torch):
     assert pb.pkv_plan_payload_bytes(plan, 0) == oracle.request_payload_bytes(case.shape, case.requests[0])
     assert np.array_equal(hp.numpy(), ref_p)
     assert np.array_equal(hs.numpy().view(np.uint16), ref_s)
+
+
+def test_write_past_the_tile_grid(torch):
+    """One block more than a launch with a wave per tile can hold (256 heads of 16, one-token pages, 131072 blocks): the
+    general kernel writes it.  The source rows repeat every 64 tokens, so the checkpoint repeats that of 16 blocks."""
+    H, D, B, blocks, few = 256, 16, 4, 1 << 17, 16
+    shape = wl.Shape(1, H, D, B, 1, 64, 1e4, wl.OUT_BF16)
+
+    def request(nb):
+        table = (np.arange(nb * B) % 64).astype(np.int32)
+        return wl.Request(nb * B, 0, 0, np.full(nb, wl.TAG_K4V4, np.uint8), np.zeros(nb, np.uint8), table, 0, 0,
+                          src_row0=0, src_page_table=table)
+
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    k = torch.randn((64, H, D), device="cuda", generator=gen).bfloat16()
+    v = torch.randn((64, H, D), device="cuda", generator=gen).bfloat16()
+    out = []
+    for nb in (few, blocks):
+        plan = pb.pkv_checkpoint_plan(shape, [request(nb)])
+        payload = torch.zeros(nb * B * H * D, dtype=torch.uint8, device="cuda")
+        scales = torch.zeros(nb * H * 4, dtype=torch.int16, device="cuda")
+        pb.quantize_gather_tensors(plan, k, v, payload, scales)
+        torch.cuda.synchronize()
+        pb.pkv_free(plan)
+        out.append((payload, scales))
+    (p0, s0), (p1, s1) = out
+    assert int(p0.count_nonzero()) > 0 and int(s0.count_nonzero()) > 0
+    assert bool((p1.view(blocks // few, -1) == p0).all()) and bool((s1.view(blocks // few, -1) == s0).all())

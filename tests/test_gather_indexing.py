@@ -221,53 +221,19 @@ def test_tile_kernel_tiles_and_pages(maker):
             assert 0 <= pages[k] < s.pool_pages
 
 
-HALF_WAVES = 8  # waves per workgroup of the half-tile kernel
+KERNELS = {0: "none", 1: "tile", 2: "split", 3: "general"}
 
 
-@pytest.mark.parametrize("maker", [
-    lambda: wl.make_custom(13, L=1, H=8, D=128, B=64, P=32, n_tokens=(150, 64), deltas=(4096, 0), rho0s=(31, 96),
-                           tag_set=(0, 1, 2, 3), mix=(1, 1, 1, 1)),
-    # 12 loads per lane (a 16-load chunk), three heads: tiles of different (unit, K|V) share workgroups
-    lambda: wl.make_custom(14, L=2, H=3, D=128, B=48, P=32, n_tokens=(100,), deltas=(7,), rho0s=(5,),
-                           tag_set=(0, 1, 2, 3), mix=(1, 1, 1, 1)),
-], ids=["h8_d128_b64_p32", "h3_d128_b48"])
-def test_half_tile_kernel_mapping(maker):
-    """Half-tile kernel (9 to 16 loads per lane): wave w of workgroup b is
-    half-tile W = 8b + w, tile W >> 1, half W & 1, so both halves of a tile sit
-    in one workgroup (the range exchange), every tile is covered exactly once
-    by its two halves' rows, and each tile's scale word is written once."""
-    case = maker()
-    s = case.src_shape
-    H, D, B = s.num_kv_heads, s.head_dim, s.block_tokens
-    units, _ = checkpoint_units(s, case.requests)
-    lpr = D // 8
-    rpl = 64 // lpr
-    nload = -(-B // rpl)
-    assert 8 < nload <= 16 and loads_per_chunk(nload) == 16
-    ntiles = len(units) * 2 * H
-    grid = -(-2 * ntiles // HALF_WAVES)
-    lane = np.arange(64)
-    r, c = lane // lpr, lane % lpr
-    on = r < rpl
-    rows_of = np.zeros((ntiles, B, lpr), dtype=np.int32)  # (tile, row, channel piece) writes
-    scale_writes = np.zeros(ntiles, dtype=np.int32)
-    for b in range(grid):
-        for w in range(HALF_WAVES):
-            W = b * HALF_WAVES + w
-            T, half = W >> 1, W & 1
-            assert (W ^ 1) // HALF_WAVES == b  # the partner half is in the same workgroup
-            if T >= ntiles:
-                continue  # such waves read tile 0, store nothing, and still pass the barrier
-            for i in range(8):
-                t = half * 8 * rpl + i * rpl + r
-                st = on & (t < B)
-                np.add.at(rows_of[T], (t[st], c[st]), 1)
-            if half == 0:
-                scale_writes[T] += 1
-    assert (rows_of == 1).all() and (scale_writes == 1).all()
-
-
-SPLIT_LOADS, SPLIT_WAVES = 8, 8  # loads per lane of one wave; waves per workgroup where the tiles' waves fit
+def gather_launch(units, **model):
+    """The library's kernel choice and launch for a write of ``units`` work items."""
+    fn = pb.load().pkv_internal_gather_launch
+    fn.argtypes = [ctypes.POINTER(pb.PkvModel), ctypes.c_int64, ctypes.c_void_p]
+    fn.restype = ctypes.c_int32
+    out = np.zeros(7, np.int64)
+    m = pb.make_model(wl.Shape(1, model["H"], model["D"], model["B"], model["P"], model.get("pool", 64), 1e4, wl.OUT_FP16))
+    assert fn(ctypes.byref(m), units, out.ctypes.data) == 0
+    return dict(zip(("kernel", "loads", "split", "group", "threads", "wide", "grid"), out.tolist()),
+                kernel=KERNELS[int(out[0])])
 
 
 @pytest.mark.parametrize("B,D,H,split,group", [
@@ -280,16 +246,17 @@ SPLIT_LOADS, SPLIT_WAVES = 8, 8  # loads per lane of one wave; waves per workgro
     (512, 128, 1, 16, 1),  # 128 loads: the largest
 ])
 def test_split_kernel_mapping(B, D, H, split, group):
-    """Split kernel (9 to 128 loads per lane): `split` waves of a workgroup hold
-    one tile, `group` tiles to a workgroup; every row of every tile belongs to
-    one wave of its workgroup, and workgroups stay within 16 waves."""
+    """Split kernel (9 to 128 loads per lane), as the library launches it: `split` waves of a workgroup hold one tile,
+    `group` tiles to a workgroup; every row of every tile belongs to one wave of its workgroup, and workgroups stay
+    within 16 waves."""
     lpr = D // 8
     rpl = 64 // lpr
-    nload = -(-B // rpl)
-    assert split == -(-nload // SPLIT_LOADS) and group == max(1, SPLIT_WAVES // split)
-    assert 1 < split * group <= MAX_WAVES
-    ntiles = 2 * H * 3
-    grid = -(-ntiles // group)
+    units = 3
+    got = gather_launch(units, H=H, D=D, B=B, P=16)
+    assert (got["kernel"], got["split"], got["group"], got["loads"]) == ("split", split, group, 8)
+    loads, grid = got["loads"], got["grid"]
+    ntiles = 2 * H * units
+    assert got["threads"] == 64 * split * group <= 64 * MAX_WAVES
     lane = np.arange(64)
     r, c = lane // lpr, lane % lpr
     on = r < rpl
@@ -302,9 +269,42 @@ def test_split_kernel_mapping(B, D, H, split, group):
             assert local < group and local * split + part == w  # the range exchange reads waves of this workgroup
             if T >= ntiles:
                 continue
-            for i in range(SPLIT_LOADS):
-                t = part * SPLIT_LOADS * rpl + i * rpl + r
+            for i in range(loads):
+                t = part * loads * rpl + i * rpl + r
                 st = on & (t < B)
                 np.add.at(rows_of[T], (t[st], c[st]), 1)
             leads[T] += part == 0
     assert (rows_of == 1).all() and (leads == 1).all()
+
+
+@pytest.mark.parametrize("model,units,kernel", [
+    (dict(H=8, D=128, B=32, P=16), 1, "tile"),
+    (dict(H=8, D=128, B=33, P=32), 1, "split"),
+    (dict(H=1, D=128, B=512, P=512), 1, "split"),
+    (dict(H=1, D=128, B=513, P=512), 1, "general"),
+    # One wave per tile is one thread too many; the general kernel's 16 waves per (block, cache) are not.
+    (dict(H=256, D=16, B=4, P=1), 131071, "tile"),
+    (dict(H=256, D=16, B=4, P=1), 131072, "general"),
+    (dict(H=256, D=16, B=4, P=1), (1 << 21) - 1, "general"),
+    (dict(H=256, D=16, B=4, P=1), 1 << 21, "none"),
+    # Blocks of 128 loads: 16 waves to a tile.
+    (dict(H=8, D=128, B=512, P=512), 262143, "split"),
+    (dict(H=8, D=128, B=512, P=512), 262144, "general"),
+])
+def test_kernel_choice_and_grid_limits(model, units, kernel):
+    """A launch holds fewer than 2^32 threads: writes whose tiles do not fit go to the general kernel, which refuses
+    only what its own grid cannot hold."""
+    got = gather_launch(units, **model)
+    assert got["kernel"] == kernel
+    if kernel != "none":
+        assert 0 < got["grid"] * got["threads"] < 1 << 32
+    if kernel == "general":
+        assert got["grid"] == 2 * units and got["threads"] == 64 * min(model["H"], MAX_WAVES)
+
+
+@pytest.mark.parametrize("model,wide", [(dict(H=8, D=128, B=33, P=16), False), (dict(H=8, D=128, B=34, P=16), True),
+                                        (dict(H=8, D=128, B=32, P=16, pool=(1 << 17) - 1), False),
+                                        (dict(H=8, D=128, B=32, P=16, pool=1 << 17), True)])
+def test_wide_blocks(model, wide):
+    """Blocks on more than three pages, and layer slices of 4 GiB and more, look their pages up."""
+    assert gather_launch(1, **model)["wide"] == wide
