@@ -231,6 +231,8 @@ struct HostPlan {
   std::vector<RequestCopies> copies;        // restore plans, per request
   std::vector<PullPiece> pieces;            // restore plans that pull their copies (pulls()): those of one layer
   uint64_t pull_layer_bytes = 0;            // bytes of `pieces`
+  int32_t cus = 0;     // compute units of the plan's device; 0 when it could not be queried
+  int32_t per_cu = 0;  // restore plans: restore_workgroups_per_cu()
   int64_t rotated_rows = 0;  // restore plans: restored rows whose keys rotate (shift != 0)
   std::vector<uint64_t> req_payload_bytes;  // per request: bytes of its checkpoint payload, all layers
   // Restore plans: whether every request-layer's scales fit the staged restore's static buffer.
@@ -276,6 +278,22 @@ void layer_copies(const HostPlan& hp, int64_t l, std::vector<CopyRange>& payload
 // elements and less (one head on 16-token pages, one-token pages) are fastest
 // at the 16 waves the registers allow.
 int restore_workgroups_per_cu(const HostPlan& hp);
+
+// Launches that fit on the device at this many 256-thread workgroups to a
+// compute unit are all resident at once, whatever cap the plan has for longer
+// ones: one layer of the 8B-shaped restore (690 workgroups on 256 compute
+// units) takes 10.5 us at three and 11.1 at two, which leaves 178 for a second
+// round.  At four to a compute unit 1012 workgroups were slower than at two
+// (14.3 against 13.7 us).
+constexpr int kOneRound = 3;
+
+// How a launch of `units` restore work items into these caches runs.
+struct RestoreLaunch {
+  bool late;       // the late start order (Stage in restore.hip)
+  bool one_round;  // kOneRound workgroups to a compute unit instead of HostPlan::per_cu
+  bool device;     // stores at device scope
+};
+RestoreLaunch restore_launch(const HostPlan& hp, int64_t units, uintptr_t k_cache, uintptr_t v_cache);
 
 // The same for the checkpoint write, 0 for no cap: staged tiles of 8 loads per
 // lane (32-token blocks at head_dim 128) run best with 16 waves, 128 KB of
@@ -352,15 +370,8 @@ struct pkv_plan {
   // LDS bytes a workgroup claims so that at most restore_workgroups_per_cu() or
   // gather_workgroups_per_cu() of them are resident on a compute unit (0: no cap).
   uint32_t cap_lds = 0;
-  // Restore launches of at most this many units are resident at once with this
-  // claim instead (kOneRound in restore.hip); none where the count is 0.
-  int64_t one_round_units = 0;
+  // The same for restore launches in one round (RestoreLaunch::one_round).
   uint32_t one_round_lds = 0;
-  // Restore launches of at most this many units (a few rounds of compute
-  // units x restore_workgroups_per_cu() resident workgroups; every launch for
-  // rows narrow enough for workgroups under kWorkgroup threads) take the late
-  // start order of the restore kernel; 0 when the device could not be queried.
-  int64_t restore_late_units = 0;
   // Streamed restore: copy streams and events (hipStream_t / hipEvent_t),
   // created on first use.  events[0] marks the caller's stream at entry;
   // events[1 + l * n + k] the end of layer l's chunks on copy stream k.

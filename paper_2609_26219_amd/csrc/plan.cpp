@@ -218,6 +218,50 @@ int restore_workgroups_per_cu(const HostPlan& hp) {
   return n < lo ? lo : n > hi ? hi : int(n);
 }
 
+namespace {
+
+// Whether the pieces that a store instruction writes next to each other make
+// whole pieces of `bytes` bytes (of a cache that starts on one): they fill half
+// a head's row, or half its rotary channels and half the others where
+// rotate-half pairs stop short of the row.
+bool stores_whole(const pkv_model_t& m, int32_t bytes) {
+  return m.head_dim % bytes == 0 && (m.rope_style == PKV_ROPE_INTERLEAVED || m.rotary_dim % bytes == 0);
+}
+
+// Rows stored at device scope.  The write stream bounds the kernel, and the
+// 8B-shaped 32-layer restore takes 847 us that way against 886 (5.34 GB, 6.3
+// against 6.0 TB/s), one layer of it 10.5 against 11.3.  It needs
+//   whole 64-byte sectors, by the rows and by the caches' addresses: parts of
+//     sectors are written through one by one (8 heads of 96, 16 layers: 1100 us
+//     against 550), where the L2 puts them together.
+bool device_stores(const HostPlan& hp, uintptr_t k_cache, uintptr_t v_cache) {
+  return stores_whole(hp.model, 64) && (k_cache | v_cache) % 64 == 0;
+}
+
+// Launches of at most this many rounds of resident workgroups take the late
+// start order of the restore kernel.  Separate caches run fewer
+// workgroups at a time and gain from it longer: us late / early, 690
+// workgroups a layer, separate (512 resident) and paired (768): 4 layers 30.0 /
+// 30.8 and 29.6 / 30.0, 8 layers (10.8 and 7.2 rounds) 59.1 / 61.2 and 55.8 /
+// 54.8, 16 layers 124.2 / 124.3 and 116.8 / 114.3, 32 layers 244.8 / 242.9 and
+// 230.9 / 222.4.  Rows narrow enough for workgroups under kWorkgroup threads take
+// it at any depth: on the 32-layer 8B-shaped workload's share of one KV head per
+// GPU (one-wave workgroups of two tokens per thread) it measured 102-112 us
+// against 127-135 us, and within 1% of the early order at two and four heads.
+constexpr int64_t kLateRoundsSeparate = 12;
+constexpr int64_t kLateRounds = 6;
+
+}  // namespace
+
+RestoreLaunch restore_launch(const HostPlan& hp, int64_t units, uintptr_t k_cache, uintptr_t v_cache) {
+  RestoreLaunch r;
+  const int64_t rounds = hp.model.kv_layout == PKV_KV_SEPARATE ? kLateRoundsSeparate : kLateRounds;
+  r.late = hp.workgroup < kWorkgroup || units <= rounds * hp.cus * hp.per_cu;
+  r.one_round = hp.workgroup == kWorkgroup && hp.per_cu < kOneRound && units <= kOneRound * int64_t(hp.cus);
+  r.device = device_stores(hp, k_cache, v_cache);
+  return r;
+}
+
 // Threads of a restore workgroup: enough that each thread owns at most four
 // tokens of the largest unit (units stop at page ends), in whole waves, at
 // most kWorkgroup.  Rows of 8 heads x 128 keep 256; a one-head row of 128
@@ -700,6 +744,24 @@ pkv_status_t pkv_internal_host_units(const pkv_model_t* model, const pkv_request
   if (st != PKV_OK) return st;
   *count = hp.info.num_units;
   if (units_out && capacity >= *count) unit_views(hp, units_out);
+  return PKV_OK;
+}
+
+// Internal test hook (not part of pkv.h): how launches of a plan run on a
+// device of 256 compute units, as 4 int64: workgroups to a compute unit, late,
+// one_round, device.  `layers` of the plan's layers at a time (0: all of them).
+pkv_status_t pkv_internal_restore_launch(const pkv_model_t* model, const pkv_request_t* requests, int32_t num_requests,
+                                         int64_t layers, uint64_t k_cache, uint64_t v_cache, int64_t* out) {
+  if (!out) return PKV_ERR_INVALID_ARGUMENT;
+  pkv::HostPlan hp;
+  pkv_status_t st = pkv::build_host_plan(model, requests, num_requests, &hp);
+  if (st != PKV_OK) return st;
+  hp.cus = 256;
+  hp.per_cu = pkv::restore_workgroups_per_cu(hp);
+  const pkv::RestoreLaunch r = pkv::restore_launch(hp, layers ? layers * hp.layer_units : hp.info.num_units,
+                                                   uintptr_t(k_cache), uintptr_t(v_cache));
+  const int64_t v[4] = {hp.per_cu, r.late, r.one_round, r.device};
+  memcpy(out, v, sizeof(v));
   return PKV_OK;
 }
 

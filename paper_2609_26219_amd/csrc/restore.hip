@@ -62,24 +62,6 @@ namespace {
 // keeps two to four).
 constexpr int kMinWavesPerEU = 4;
 
-// Launches of at most this many rounds of resident workgroups take the late
-// start order of the restore kernel (see Stage).  Separate caches run fewer
-// workgroups at a time and gain from it longer: us late / early, 690
-// workgroups a layer, separate (512 resident) and paired (768): 4 layers 30.0 /
-// 30.8 and 29.6 / 30.0, 8 layers (10.8 and 7.2 rounds) 59.1 / 61.2 and 55.8 /
-// 54.8, 16 layers 124.2 / 124.3 and 116.8 / 114.3, 32 layers 244.8 / 242.9 and
-// 230.9 / 222.4.
-constexpr int64_t kLateRoundsSeparate = 12;
-constexpr int64_t kLateRounds = 6;
-
-// Launches that fit on the device at this many 256-thread workgroups to a
-// compute unit are all resident at once, whatever cap the plan has for longer
-// ones: one layer of the 8B-shaped restore (690 workgroups on 256 compute
-// units) takes 10.5 us at three and 11.1 at two, which leaves 178 for a second
-// round.  At four to a compute unit 1012 workgroups were slower than at two
-// (14.3 against 13.7 us).
-constexpr int kOneRound = 3;
-
 struct KernelArgs {
   const Unit* units;  // of one layer
   LayerItems items;
@@ -138,13 +120,8 @@ constexpr int kNonTemporalDevice = 18;
 
 // Restored rows are written once and not read again by this launch: store
 // them non-temporally (2% faster than the default policy), and at device scope
-// too where each store instruction writes whole 64-byte sectors (whole_sectors),
-// so that a line leaves its XCD's L2 as it is written and not when another one
-// evicts it.  The write stream bounds the kernel: the 8B-shaped 32-layer restore
-// takes 847 us that way against 886 (5.34 GB, 6.3 against 6.0 TB/s), one layer
-// of it 10.5 against 11.3.  Parts of sectors are another matter: written
-// through one by one they take twice as long (8 heads of 96, 16 layers: 1100 us
-// against 550), so those rows stay in the L2, which puts them together.
+// too where device_stores() says so: a line then leaves its XCD's L2 as it is
+// written and not when another one evicts it.
 //
 // The whole offset goes in the VGPR operand and the SGPR offset is 0.  A
 // 16-byte store reads its data registers after it issues, so an instruction
@@ -681,35 +658,23 @@ pkv_status_t upload_plan(HostPlan&& hp, pkv_plan** out) {
     (void)hipGetLastError();
     cus = 0;
   }
+  plan->host.cus = cus;
+  if (plan->host.kind == 0) plan->host.per_cu = restore_workgroups_per_cu(plan->host);
   if (hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) == hipSuccess &&
       hipDeviceGetAttribute(&lds_wg, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && lds_cu > 0) {
     const bool write = plan->host.kind == 1;
     const int64_t fixed = write ? 0 : int64_t(kMaxHeadDim) * int64_t(sizeof(double));
-    const int64_t n = write ? gather_workgroups_per_cu(plan->host) : restore_workgroups_per_cu(plan->host);
+    const int64_t n = write ? gather_workgroups_per_cu(plan->host) : plan->host.per_cu;
     const auto claim = [&](int64_t per_cu) {
       const int64_t share = (int64_t(lds_cu) / per_cu + int64_t(lds_cu) / (per_cu + 1)) / 2;
       const int64_t dyn = std::min<int64_t>((share - fixed) & ~int64_t(255), int64_t(lds_wg) - fixed);
       return dyn > 0 ? uint32_t(dyn) : 0;
     };
     if (n > 0 && n < 16 / std::max(1, plan->host.workgroup / 64) + (write ? 1 : 0)) plan->cap_lds = claim(n);
-    if (!write && plan->host.workgroup == kWorkgroup && n < kOneRound) {
-      plan->one_round_units = kOneRound * int64_t(cus);
-      plan->one_round_lds = claim(kOneRound);
-    }
+    if (!write) plan->one_round_lds = claim(kOneRound);
   } else {
     (void)hipGetLastError();
   }
-  // Late start order up to kLateRounds (separate caches kLateRoundsSeparate)
-  // rounds of resident workgroups.  Rows narrow enough for workgroups under
-  // kWorkgroup threads take it at any depth: on the 32-layer 8B-shaped
-  // workload's share of one KV head per GPU (one-wave workgroups of two tokens
-  // per thread) it measured 102-112 us against 127-135 us, and within 1% of the
-  // early order at two and four heads.
-  if (plan->host.workgroup < kWorkgroup)
-    plan->restore_late_units = INT64_MAX;
-  else
-    plan->restore_late_units = (plan->host.model.kv_layout == PKV_KV_SEPARATE ? kLateRoundsSeparate : kLateRounds) *
-                               int64_t(cus) * restore_workgroups_per_cu(plan->host);
   if (total > 0) {
     std::unique_ptr<char[]> image(new (std::nothrow) char[total]);
     hipError_t e = image ? plan_memory(dev).allocate(total, &plan->device_mem) : hipErrorOutOfMemory;
@@ -798,19 +763,10 @@ pkv_status_t check_restore_buffers(const pkv_plan* plan, const void* payload, ui
   return PKV_OK;
 }
 
-// Start order of the restore kernel: 0 by plan and launch size (late for
-// narrow rows and for launches of at most kLateRounds rounds of resident
-// workgroups), 1 early, 2 late.
+// Start order of the restore kernel: 0 by plan and launch size
+// (restore_launch), 1 early, 2 late.
 // Set only through the test hook pkv_internal_set_restore_order.
 std::atomic<int> g_restore_order{0};
-
-// Whether the pieces that a store instruction writes next to each other make
-// whole 64-byte sectors (of a cache that starts on one): they fill half a
-// head's row, or half its rotary channels and half the others where
-// rotate-half pairs stop short of the row.
-bool whole_sectors(const pkv_model_t& m) {
-  return m.head_dim % 64 == 0 && (m.rope_style == PKV_ROPE_INTERLEAVED || m.rotary_dim % 64 == 0);
-}
 
 // Enqueue the restore kernel over units [u0, u1) of layers [layer0, layer1),
 // those whose K rows start in payload bytes [win_lo, win_hi).
@@ -847,8 +803,9 @@ pkv_status_t launch_restore(const pkv_plan* plan, const void* payload, const voi
   a.R = m.rotary_dim ? m.rotary_dim : m.head_dim;
   const bool bf16 = m.out_dtype == PKV_OUT_BF16, half = m.rope_style == PKV_ROPE_HALF;
   const int order = g_restore_order.load(std::memory_order_relaxed);
-  const bool late = order == 2 || (order == 0 && n <= plan->restore_late_units);
-  const bool device = whole_sectors(m);
+  const RestoreLaunch launch = restore_launch(plan->host, n, reinterpret_cast<uintptr_t>(k_cache),
+                                              reinterpret_cast<uintptr_t>(v_cache));
+  const bool late = order == 2 || (order == 0 && launch.late), device = launch.device;
   const auto pick = [&](auto f16, auto style) {
     constexpr bool B = decltype(f16)::value;
     constexpr int S = decltype(style)::value;
@@ -859,7 +816,7 @@ pkv_status_t launch_restore(const pkv_plan* plan, const void* payload, const voi
   using Pairs = std::integral_constant<int, PKV_ROPE_INTERLEAVED>;
   const auto kernel = bf16 ? half ? pick(std::true_type(), Half()) : pick(std::true_type(), Pairs())
                            : half ? pick(std::false_type(), Half()) : pick(std::false_type(), Pairs());
-  const uint32_t lds = n <= plan->one_round_units ? plan->one_round_lds : plan->cap_lds;
+  const uint32_t lds = launch.one_round ? plan->one_round_lds : plan->cap_lds;
   hipLaunchKernelGGL(kernel, dim3(uint32_t(n)), dim3(plan->host.workgroup), lds, stream, a);
   return hipGetLastError() == hipSuccess ? PKV_OK : PKV_ERR_DEVICE;
 }

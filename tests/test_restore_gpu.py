@@ -317,3 +317,26 @@ def test_both_store_scopes(heads, dim, style, rotary, torch):
                           tag_set=(0, 1, 2, 3), mix=(1, 1, 1, 1), out_dtype=wl.OUT_BF16, outlier_pairs=1)
     case.shape = dataclasses.replace(case.shape, rope_style=style, rotary_dim=rotary)
     check_both_orders(case)
+
+
+@pytest.mark.parametrize("offset", [16, 32, 48, 64])
+def test_store_scopes_by_cache_address(offset, torch):
+    """Caches that start inside a 64-byte sector, as the contract allows, and on one."""
+    from paper_2609_26219_amd.device import DeviceRestore
+
+    case = wl.make_custom(52, L=2, H=2, D=128, B=16, P=8, n_tokens=(70, 9), deltas=(-300, 7), rho0s=(305, 2),
+                          tag_set=(0, 1, 2, 3), mix=(1, 1, 1, 1), out_dtype=wl.OUT_BF16, outlier_pairs=1)
+    ckpt = oracle_checkpoint(case)
+    dr = DeviceRestore(case, checkpoint=ckpt)
+    for name in ("k_cache", "v_cache"):
+        cache = getattr(dr, name)
+        flat = torch.empty(cache.numel() + 64, dtype=cache.dtype, device=cache.device)
+        skip = (offset - flat.data_ptr() % 64) % 64 // 2
+        setattr(dr, name, flat[skip:skip + cache.numel()].view(cache.shape))
+        assert getattr(dr, name).data_ptr() % 64 == offset % 64
+    for order in ("early", "late"):
+        dr.prefill()
+        with restore_order(order):
+            dr.run()
+        torch.cuda.synchronize()
+        check_full(dr, ckpt)

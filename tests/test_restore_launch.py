@@ -1,0 +1,46 @@
+"""How a restore is launched (restore_launch in plan.cpp): which rows are stored at device scope, in which start order and
+at what residency, by the plan's sizes and the caches' addresses."""
+import ctypes
+import dataclasses
+
+import numpy as np
+import pytest
+
+from paper_2609_26219_amd import binding as pb
+from paper_2609_26219_amd import workloads as wl
+
+MIXED, K8V4, K4V4 = (1, 2, 7, 0), (0, 0, 1, 0), (0, 0, 0, 1)
+
+
+def restore_launch(case, layers=0, k=0, v=0):
+    fn = pb.load().pkv_internal_restore_launch
+    fn.argtypes = [ctypes.POINTER(pb.PkvModel), ctypes.POINTER(pb.PkvRequest), ctypes.c_int32, ctypes.c_int64,
+                   ctypes.c_uint64, ctypes.c_uint64, ctypes.c_void_p]
+    fn.restype = ctypes.c_int32
+    m, reqs, out = pb.make_model(case.shape), pb._Requests(case.requests), np.zeros(4, np.int64)
+    assert fn(ctypes.byref(m), reqs.array, reqs.count, layers, k, v, out.ctypes.data) == 0
+    return dict(zip(("per_cu", "late", "one_round", "device"), out.tolist()))
+
+
+def make(H, D, B=32, P=16, tokens=4096, L=1, mix=MIXED, delta=-700, paired=False, style=wl.ROPE_HALF, rotary=0):
+    case = wl.make_custom(5, L=L, H=H, D=D, B=B, P=P, n_tokens=(tokens,), deltas=(delta,), rho0s=(max(0, 2000 - delta),),
+                          tag_set=(0, 1, 2, 3), mix=mix, repair_frac=0.1, out_dtype=wl.OUT_BF16)
+    case.shape = dataclasses.replace(case.shape, rope_style=style, rotary_dim=rotary,
+                                     kv_layout=wl.KV_PAIRED if paired else wl.KV_SEPARATE)
+    return case
+
+
+@pytest.mark.parametrize("offset,device", [(0, 1), (16, 0), (32, 0), (48, 0), (64, 1)])
+def test_device_scope_by_address(offset, device):
+    """Either cache inside a 64-byte sector would be written through in parts of sectors."""
+    case = make(8, 128)
+    assert restore_launch(case, k=1 << 20, v=(1 << 21) + offset)["device"] == device
+    assert restore_launch(case, k=(1 << 20) + offset, v=1 << 21)["device"] == device
+
+
+@pytest.mark.parametrize("args,device", [
+    (dict(H=8, D=96), 0), (dict(H=8, D=80), 0), (dict(H=1, D=256), 1), (dict(H=8, D=64), 1),
+    (dict(H=2, D=128, rotary=32), 0), (dict(H=2, D=128, rotary=32, style=wl.ROPE_INTERLEAVED), 1),
+])
+def test_device_scope_by_rows(args, device):
+    assert restore_launch(make(**args))["device"] == device
