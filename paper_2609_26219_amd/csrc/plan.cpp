@@ -233,9 +233,23 @@ bool stores_whole(const pkv_model_t& m, int32_t bytes) {
 // against 6.0 TB/s), one layer of it 10.5 against 11.3.  It needs
 //   whole 64-byte sectors, by the rows and by the caches' addresses: parts of
 //     sectors are written through one by one (8 heads of 96, 16 layers: 1100 us
-//     against 550), where the L2 puts them together.
-bool device_stores(const HostPlan& hp, uintptr_t k_cache, uintptr_t v_cache) {
-  return stores_whole(hp.model, 64) && (k_cache | v_cache) % 64 == 0;
+//     against 550), where the L2 puts them together;
+//   units of 2 KB and more: single rows below that (one-token pages) are 1-9%
+//     slower with it (2 heads of 128: mixed tags 1.02x, 4-bit 1.06x), larger ones
+//     level or up to 16% faster (4 heads of 256, 48 MB: 0.84x; 8 heads of 128, 360
+//     MB: mixed 1.01x, FP16 1.00x, 4-bit 1.07x);
+//   and for pieces of half a 128-byte line (heads of 64): little read beside
+//     the writes (below 0.42 bytes per byte written: 10-40% faster, 8 heads, K8V4
+//     and 4-bit), keys that do not rotate, or a launch that writes up to 64 MB
+//     (5-29% faster); above, mixed tags are 4-6% slower with it.
+bool device_stores(const HostPlan& hp, int64_t units, uintptr_t k_cache, uintptr_t v_cache) {
+  const pkv_model_t& m = hp.model;
+  if (!stores_whole(m, 64) || (k_cache | v_cache) % 64 != 0) return false;
+  if (std::min(unit_tokens(m), m.page_size) == 1 && m.num_kv_heads * m.head_dim < 1024) return false;
+  if (stores_whole(m, 128)) return true;
+  const pkv_plan_info_t& info = hp.info;
+  return double(info.bytes_read) < 0.42 * double(info.bytes_written) || 2 * hp.rotated_rows < info.restored_rows ||
+         double(info.bytes_written) * double(units) <= 64e6 * double(info.num_units);
 }
 
 // Launches of at most this many rounds of resident workgroups take the late
@@ -258,7 +272,7 @@ RestoreLaunch restore_launch(const HostPlan& hp, int64_t units, uintptr_t k_cach
   const int64_t rounds = hp.model.kv_layout == PKV_KV_SEPARATE ? kLateRoundsSeparate : kLateRounds;
   r.late = hp.workgroup < kWorkgroup || units <= rounds * hp.cus * hp.per_cu;
   r.one_round = hp.workgroup == kWorkgroup && hp.per_cu < kOneRound && units <= kOneRound * int64_t(hp.cus);
-  r.device = device_stores(hp, k_cache, v_cache);
+  r.device = device_stores(hp, units, k_cache, v_cache);
   return r;
 }
 

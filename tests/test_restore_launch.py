@@ -39,8 +39,20 @@ def test_device_scope_by_address(offset, device):
 
 
 @pytest.mark.parametrize("args,device", [
-    (dict(H=8, D=96), 0), (dict(H=8, D=80), 0), (dict(H=1, D=256), 1), (dict(H=8, D=64), 1),
+    (dict(H=8, D=96), 0), (dict(H=8, D=80), 0), (dict(H=1, D=256), 1),
+    # one-row units, below 2 KB and from there on
+    (dict(H=7, D=128, P=1), 0), (dict(H=7, D=128, P=2), 1), (dict(H=7, D=128, B=1, tokens=256), 0), (dict(H=8, D=128, P=1), 1),
     (dict(H=2, D=128, rotary=32), 0), (dict(H=2, D=128, rotary=32, style=wl.ROPE_INTERLEAVED), 1),
+    # pieces of half a line: 8 x 64, 26 layers of 4096 tokens write 196 MB
+    (dict(H=8, D=64, L=26), 0), (dict(H=8, D=64, L=26, mix=K8V4), 1), (dict(H=8, D=64, L=26, mix=K4V4), 1),
+    (dict(H=8, D=64, L=26, delta=0), 1), (dict(H=8, D=64, L=8), 1), (dict(H=8, D=64, L=26, paired=True), 0),
+    (dict(H=4, D=128, rotary=64, L=26), 0), (dict(H=4, D=128, rotary=64, L=26, style=wl.ROPE_INTERLEAVED), 1),
 ])
 def test_device_scope_by_rows(args, device):
     assert restore_launch(make(**args))["device"] == device
+
+
+def test_device_scope_by_launch_size():
+    """The streamed restore launches a layer at a time: what counts is the launch."""
+    case = make(8, 64, L=26)
+    assert restore_launch(case)["device"] == 0 and restore_launch(case, layers=1)["device"] == 1
