@@ -292,6 +292,7 @@ struct RestoreLaunch {
   bool late;       // the late start order (Stage in restore.hip)
   bool one_round;  // kOneRound workgroups to a compute unit instead of HostPlan::per_cu
   bool device;     // stores at device scope
+  bool single;     // work items of one row
 };
 RestoreLaunch restore_launch(const HostPlan& hp, int64_t units, uintptr_t k_cache, uintptr_t v_cache);
 

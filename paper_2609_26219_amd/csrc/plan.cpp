@@ -228,6 +228,9 @@ bool stores_whole(const pkv_model_t& m, int32_t bytes) {
   return m.head_dim % bytes == 0 && (m.rope_style == PKV_ROPE_INTERLEAVED || m.rotary_dim % bytes == 0);
 }
 
+// Whether every work item is one row.
+bool single_rows(const pkv_model_t& m) { return std::min(unit_tokens(m), m.page_size) == 1; }
+
 // Rows stored at device scope.  The write stream bounds the kernel, and the
 // 8B-shaped 32-layer restore takes 847 us that way against 886 (5.34 GB, 6.3
 // against 6.0 TB/s), one layer of it 10.5 against 11.3.  It needs
@@ -245,7 +248,7 @@ bool stores_whole(const pkv_model_t& m, int32_t bytes) {
 bool device_stores(const HostPlan& hp, int64_t units, uintptr_t k_cache, uintptr_t v_cache) {
   const pkv_model_t& m = hp.model;
   if (!stores_whole(m, 64) || (k_cache | v_cache) % 64 != 0) return false;
-  if (std::min(unit_tokens(m), m.page_size) == 1 && m.num_kv_heads * m.head_dim < 1024) return false;
+  if (single_rows(m) && m.num_kv_heads * m.head_dim < 1024) return false;
   if (stores_whole(m, 128)) return true;
   const pkv_plan_info_t& info = hp.info;
   return double(info.bytes_read) < 0.42 * double(info.bytes_written) || 2 * hp.rotated_rows < info.restored_rows ||
@@ -273,6 +276,7 @@ RestoreLaunch restore_launch(const HostPlan& hp, int64_t units, uintptr_t k_cach
   r.late = hp.workgroup < kWorkgroup || units <= rounds * hp.cus * hp.per_cu;
   r.one_round = hp.workgroup == kWorkgroup && hp.per_cu < kOneRound && units <= kOneRound * int64_t(hp.cus);
   r.device = device_stores(hp, units, k_cache, v_cache);
+  r.single = single_rows(hp.model);
   return r;
 }
 
@@ -762,8 +766,8 @@ pkv_status_t pkv_internal_host_units(const pkv_model_t* model, const pkv_request
 }
 
 // Internal test hook (not part of pkv.h): how launches of a plan run on a
-// device of 256 compute units, as 4 int64: workgroups to a compute unit, late,
-// one_round, device.  `layers` of the plan's layers at a time (0: all of them).
+// device of 256 compute units, as 5 int64: workgroups to a compute unit, late,
+// one_round, device, single.  `layers` of the plan's layers at a time (0: all of them).
 pkv_status_t pkv_internal_restore_launch(const pkv_model_t* model, const pkv_request_t* requests, int32_t num_requests,
                                          int64_t layers, uint64_t k_cache, uint64_t v_cache, int64_t* out) {
   if (!out) return PKV_ERR_INVALID_ARGUMENT;
@@ -774,7 +778,7 @@ pkv_status_t pkv_internal_restore_launch(const pkv_model_t* model, const pkv_req
   hp.per_cu = pkv::restore_workgroups_per_cu(hp);
   const pkv::RestoreLaunch r = pkv::restore_launch(hp, layers ? layers * hp.layer_units : hp.info.num_units,
                                                    uintptr_t(k_cache), uintptr_t(v_cache));
-  const int64_t v[4] = {hp.per_cu, r.late, r.one_round, r.device};
+  const int64_t v[5] = {hp.per_cu, r.late, r.one_round, r.device, r.single};
   memcpy(out, v, sizeof(v));
   return PKV_OK;
 }

@@ -530,13 +530,30 @@ __device__ __forceinline__ void restore_unit(const KernelArgs& a, const LayerUni
   }
 }
 
-template <bool BF16, int STYLE, bool LATE, bool DEVICE>
-__global__ __launch_bounds__(kWorkgroup, kMinWavesPerEU) void restore_kernel(KernelArgs) {
+// SINGLE: work items of one row (one-token pages) leave the loads of the
+// launch arguments and of the item to the compiler, which takes them piece by
+// piece.  One-go loads (load_scalars) are 3-8% slower there (2 heads of 128, 8 of
+// 128 and 1 of 256, all four mixes: 1.079, 1.045 and 1.079 of the time of an
+// earlier kernel, 1.018, 1.005 and 1.012 piece by piece); with several rows an
+// item, they are 0-7% faster.
+template <bool BF16, int STYLE, bool LATE, bool DEVICE, bool SINGLE>
+__global__ __launch_bounds__(kWorkgroup, kMinWavesPerEU) void restore_kernel(KernelArgs args) {
   __shared__ __attribute__((aligned(16))) double s_tab[kMaxHeadDim];
-  const KernelArgs a = launch_args<KernelArgs>();
+  const KernelArgs a = [&] {
+    if constexpr (SINGLE)
+      return args;
+    else
+      return launch_args<KernelArgs>();
+  }();
   const uint32_t item = uint32_t(xcd_grouped(blockIdx.x, a.grid)), l = layer_of(a.items, item);
   const uint32_t layer = a.items.first + l;
-  const Unit unit = load_unit(a.units + (item - l * a.items.count.d));
+  const Unit* const at = a.units + (item - l * a.items.count.d);
+  const Unit unit = [&] {
+    if constexpr (SINGLE)
+      return *at;
+    else
+      return load_unit(at);
+  }();
   LayerUnit u;
   u.k_off = unit_k_off(unit, layer);
   if (u.k_off < a.win_lo || u.k_off >= a.win_hi) return;  // uniform across the workgroup
@@ -809,8 +826,10 @@ pkv_status_t launch_restore(const pkv_plan* plan, const void* payload, const voi
   const auto pick = [&](auto f16, auto style) {
     constexpr bool B = decltype(f16)::value;
     constexpr int S = decltype(style)::value;
-    return late ? device ? restore_kernel<B, S, true, true> : restore_kernel<B, S, true, false>
-                : device ? restore_kernel<B, S, false, true> : restore_kernel<B, S, false, false>;
+    if (late && launch.single)
+      return device ? restore_kernel<B, S, true, true, true> : restore_kernel<B, S, true, false, true>;
+    return late ? device ? restore_kernel<B, S, true, true, false> : restore_kernel<B, S, true, false, false>
+                : device ? restore_kernel<B, S, false, true, false> : restore_kernel<B, S, false, false, false>;
   };
   using Half = std::integral_constant<int, PKV_ROPE_HALF>;
   using Pairs = std::integral_constant<int, PKV_ROPE_INTERLEAVED>;

@@ -340,3 +340,13 @@ def test_store_scopes_by_cache_address(offset, torch):
             dr.run()
         torch.cuda.synchronize()
         check_full(dr, ckpt)
+
+
+@pytest.mark.parametrize("heads,dim,paired", [(1, 16, False), (2, 128, True), (5, 80, False), (8, 128, False), (32, 128, True)])
+def test_one_row_units(heads, dim, paired, torch):
+    """One-token pages: work items of a row each, narrow and 2 KB and more, in both start orders."""
+    case = wl.make_custom(53, L=3, H=heads, D=dim, B=32, P=1, n_tokens=(75, 1, 32), deltas=(-300, 7, 0), rho0s=(305, 2, 90),
+                          tag_set=(0, 1, 2, 3), mix=(1, 1, 1, 1), out_dtype=wl.OUT_BF16, outlier_pairs=1)
+    if paired:
+        case = _paired(case)
+    check_both_orders(case)

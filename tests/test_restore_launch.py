@@ -17,9 +17,9 @@ def restore_launch(case, layers=0, k=0, v=0):
     fn.argtypes = [ctypes.POINTER(pb.PkvModel), ctypes.POINTER(pb.PkvRequest), ctypes.c_int32, ctypes.c_int64,
                    ctypes.c_uint64, ctypes.c_uint64, ctypes.c_void_p]
     fn.restype = ctypes.c_int32
-    m, reqs, out = pb.make_model(case.shape), pb._Requests(case.requests), np.zeros(4, np.int64)
+    m, reqs, out = pb.make_model(case.shape), pb._Requests(case.requests), np.zeros(5, np.int64)
     assert fn(ctypes.byref(m), reqs.array, reqs.count, layers, k, v, out.ctypes.data) == 0
-    return dict(zip(("per_cu", "late", "one_round", "device"), out.tolist()))
+    return dict(zip(("per_cu", "late", "one_round", "device", "single"), out.tolist()))
 
 
 def make(H, D, B=32, P=16, tokens=4096, L=1, mix=MIXED, delta=-700, paired=False, style=wl.ROPE_HALF, rotary=0):
@@ -56,3 +56,10 @@ def test_device_scope_by_launch_size():
     """The streamed restore launches a layer at a time: what counts is the launch."""
     case = make(8, 64, L=26)
     assert restore_launch(case)["device"] == 0 and restore_launch(case, layers=1)["device"] == 1
+
+
+@pytest.mark.parametrize("args,single", [(dict(H=8, D=128, P=1), 1), (dict(H=8, D=128, B=1, tokens=64), 1),
+                                         (dict(H=8, D=128, P=2), 0), (dict(H=32, D=128, B=64, P=1), 1)])
+def test_single_rows(args, single):
+    """Work items of one row, which load their launch arguments piece by piece."""
+    assert restore_launch(make(**args))["single"] == single
