@@ -265,6 +265,13 @@ bool device_stores(const HostPlan& hp, int64_t units, uintptr_t k_cache, uintptr
 // it at any depth: on the 32-layer 8B-shaped workload's share of one KV head per
 // GPU (one-wave workgroups of two tokens per thread) it measured 102-112 us
 // against 127-135 us, and within 1% of the early order at two and four heads.
+//
+// Rows of partial sectors (heads of 80 and 96) gain nothing past kLateRounds: late
+// / early at 8 to 11 rounds, separate caches, is 1.03-1.08 on average and up to
+// 1.44 (35 layers of 8 heads of 80, K8V4: 109 us against 83), where whole sectors
+// have 0.93-0.996.  Nor does one round at kOneRound workgroups suit them: 8 heads
+// of 96, 530 to 755 workgroups, five mixes, 1.06 of the time at two to a compute
+// unit, up to 1.22; whole sectors 0.96-0.98 (8, 16 and 32 heads of 128, 4 of 256).
 constexpr int64_t kLateRoundsSeparate = 12;
 constexpr int64_t kLateRounds = 6;
 
@@ -272,9 +279,11 @@ constexpr int64_t kLateRounds = 6;
 
 RestoreLaunch restore_launch(const HostPlan& hp, int64_t units, uintptr_t k_cache, uintptr_t v_cache) {
   RestoreLaunch r;
-  const int64_t rounds = hp.model.kv_layout == PKV_KV_SEPARATE ? kLateRoundsSeparate : kLateRounds;
+  const bool sectors = stores_whole(hp.model, 64);
+  const int64_t rounds = hp.model.kv_layout == PKV_KV_SEPARATE && sectors ? kLateRoundsSeparate : kLateRounds;
   r.late = hp.workgroup < kWorkgroup || units <= rounds * hp.cus * hp.per_cu;
-  r.one_round = hp.workgroup == kWorkgroup && hp.per_cu < kOneRound && units <= kOneRound * int64_t(hp.cus);
+  r.one_round =
+      hp.workgroup == kWorkgroup && sectors && hp.per_cu < kOneRound && units <= kOneRound * int64_t(hp.cus);
   r.device = device_stores(hp, units, k_cache, v_cache);
   r.single = single_rows(hp.model);
   return r;

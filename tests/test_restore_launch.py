@@ -63,3 +63,30 @@ def test_device_scope_by_launch_size():
 def test_single_rows(args, single):
     """Work items of one row, which load their launch arguments piece by piece."""
     assert restore_launch(make(**args))["single"] == single
+
+
+def _units(case):
+    lib, n = pb.load(), ctypes.c_int64()
+    m, reqs = pb.make_model(case.shape), pb._Requests(case.requests)
+    lib.pkv_internal_host_units.argtypes = [ctypes.POINTER(pb.PkvModel), ctypes.POINTER(pb.PkvRequest), ctypes.c_int32,
+                                            ctypes.c_void_p, ctypes.c_int64, ctypes.POINTER(ctypes.c_int64)]
+    assert lib.pkv_internal_host_units(ctypes.byref(m), reqs.array, reqs.count, None, 0, ctypes.byref(n)) == 0
+    return n.value
+
+
+@pytest.mark.parametrize("dim,paired,rounds", [(128, False, 12), (128, True, 6), (96, False, 6), (96, True, 6), (80, False, 6)])
+def test_late_order_by_rounds(dim, paired, rounds):
+    """The late start order up to `rounds` rounds of resident workgroups on 256 compute units."""
+    for tokens in (20000, 60000, 90000, 130000, 260000):
+        case = make(8, dim, B=64, P=64, tokens=tokens, paired=paired)
+        got, units = restore_launch(case), _units(case)
+        assert got["late"] == (units <= rounds * 256 * got["per_cu"]), (tokens, units, got)
+
+
+@pytest.mark.parametrize("dim", [128, 96])
+def test_one_round_for_whole_sectors(dim):
+    """Launches of up to three workgroups to a compute unit run in one round where rows are whole sectors."""
+    for tokens in (4000, 7000, 9000, 12000, 20000):
+        case = make(8, dim, B=64, P=64, tokens=tokens)
+        got, units = restore_launch(case), _units(case)
+        assert got["one_round"] == (dim == 128 and got["per_cu"] < 3 and units <= 768), (tokens, units, got)
