@@ -276,7 +276,13 @@ void layer_copies(const HostPlan& hp, int64_t l, std::vector<CopyRange>& payload
 //   K4V4 656 / 551 / 531 / 523 / 537;
 // two heads on 16-token pages: mixed 245 / 235 / 235 / 237 / 242.  Units of 1.4K
 // elements and less (one head on 16-token pages, one-token pages) are fastest
-// at the 16 waves the registers allow.
+// at the 16 waves the registers allow.  That count is too low for rotating rows
+// of whole lines that read a half to 0.8 of a byte per byte written, and below
+// that for launches that the 256 MB cache holds; mean of 19 to 54 drawn restores
+// of 1, 2 and 4 heads of 128 and one of 256 over the fastest count of each, this
+// rule / the one above:
+//   0.49-0.8, writing up to 100 MB 1.02 / 1.10, to 300 MB 1.005 / 1.07, over 700 MB 1.01 / 1.04;
+//   0.3-0.49, up to 100 MB 1.015 / 1.035, to 300 MB 1.01 / 1.03.
 int restore_workgroups_per_cu(const HostPlan& hp);
 
 // Launches that fit on the device at this many 256-thread workgroups to a

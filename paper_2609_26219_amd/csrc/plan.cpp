@@ -194,6 +194,21 @@ bool cache_ranges(const pkv_model_t& m, const void* k_cache, const void* v_cache
   return true;
 }
 
+namespace {
+
+// Whether the pieces that a store instruction writes next to each other make
+// whole pieces of `bytes` bytes (of a cache that starts on one): they fill half
+// a head's row, or half its rotary channels and half the others where
+// rotate-half pairs stop short of the row.
+bool stores_whole(const pkv_model_t& m, int32_t bytes) {
+  return m.head_dim % bytes == 0 && (m.rope_style == PKV_ROPE_INTERLEAVED || m.rotary_dim % bytes == 0);
+}
+
+// Whether every work item is one row.
+bool single_rows(const pkv_model_t& m) { return std::min(unit_tokens(m), m.page_size) == 1; }
+
+}  // namespace
+
 int restore_workgroups_per_cu(const HostPlan& hp) {
   // The memory system streams best with about 32K output elements of work in
   // flight per compute unit (two thirds of that for plans reading half a byte
@@ -214,22 +229,20 @@ int restore_workgroups_per_cu(const HostPlan& hp) {
       (narrow ? 0.72 : hp.model.kv_layout == PKV_KV_SEPARATE ? 0.75 : 1.0);
   const double unit_elems =
       double(info.restored_rows) * hp.model.num_kv_heads * hp.model.head_dim / double(info.num_units);
-  const double n = std::floor(target / unit_elems + 0.5);
+  double n = std::floor(target / unit_elems + 0.5);
+  // Narrow rows of whole 128-byte lines that rotate and read less than they
+  // write hold fewer tokens per thread, and want more waves the smaller the
+  // units, whatever the size of a workgroup: where units are 4096 elements, 10 of
+  // them while the restore writes no more than the 256 MB cache holds (10.5 below
+  // half a byte read per byte written), 8.5 above (as the target says below half).
+  const bool cached = info.bytes_written <= uint64_t(256) << 20;
+  if (narrow && stores_whole(hp.model, 128) && !single_rows(hp.model) && rotated >= 0.5 && ratio < 0.8 &&
+      (ratio >= 0.49 || (ratio >= 0.3 && cached)))
+    n = std::floor((ratio < 0.49 ? 10.5 : cached ? 10.0 : 8.5) * std::sqrt(4096.0 / unit_elems) / waves + 0.5);
   return n < lo ? lo : n > hi ? hi : int(n);
 }
 
 namespace {
-
-// Whether the pieces that a store instruction writes next to each other make
-// whole pieces of `bytes` bytes (of a cache that starts on one): they fill half
-// a head's row, or half its rotary channels and half the others where
-// rotate-half pairs stop short of the row.
-bool stores_whole(const pkv_model_t& m, int32_t bytes) {
-  return m.head_dim % bytes == 0 && (m.rope_style == PKV_ROPE_INTERLEAVED || m.rotary_dim % bytes == 0);
-}
-
-// Whether every work item is one row.
-bool single_rows(const pkv_model_t& m) { return std::min(unit_tokens(m), m.page_size) == 1; }
 
 // Rows stored at device scope.  The write stream bounds the kernel, and the
 // 8B-shaped 32-layer restore takes 847 us that way against 886 (5.34 GB, 6.3

@@ -90,3 +90,19 @@ def test_one_round_for_whole_sectors(dim):
         case = make(8, dim, B=64, P=64, tokens=tokens)
         got, units = restore_launch(case), _units(case)
         assert got["one_round"] == (dim == 128 and got["per_cu"] < 3 and units <= 768), (tokens, units, got)
+
+
+@pytest.mark.parametrize("args,per_cu", [
+    # 2 heads of 128: one wave, 2731 elements on average; 0.61 bytes read per byte written: 10 * sqrt(1.5) waves,
+    # and where 755 MB are written 8.5 * sqrt(1.5)
+    (dict(H=2, D=128, mix=(37, 25, 14, 24)), 12), (dict(H=2, D=128, mix=(37, 25, 14, 24), L=200), 10),
+    (dict(H=2, D=128), 13),          # 0.47: 10.5 * sqrt(1.5)
+    (dict(H=2, D=128, L=200), 9),    # the same, 755 MB: 23592 / 2731
+    (dict(H=2, D=128, mix=K4V4), 10), (dict(H=2, D=128, mix=(1, 0, 0, 0)), 6), (dict(H=2, D=128, delta=0), 6),
+    (dict(H=2, D=64), 16), (dict(H=2, D=64, mix=(37, 25, 14, 24)), 12),  # half lines: 23592 / 1365, 15729 / 1365
+    (dict(H=4, D=128, mix=(37, 25, 14, 24)), 4),  # two waves, 5461 elements: 10 * sqrt(0.75) / 2
+    (dict(H=4, D=128, P=1, mix=(37, 25, 14, 24)), 16),  # one-token pages
+])
+def test_residency_of_narrow_rows(args, per_cu):
+    """Destination rows start twelve slots into a 16-token page, so a block's units are 4, 16 and 12 tokens."""
+    assert restore_launch(make(**args))["per_cu"] == per_cu
