@@ -313,6 +313,9 @@ RestoreLaunch restore_launch(const HostPlan& hp, int64_t units, uintptr_t k_cach
 //   K8V4 (0.38)                     1019 / 1001    K8V4, K4V4 (0.31)        943 / 983
 //   FP16 (1.00)                     1447 / 1454    K4V4 (0.25)              908 / 983
 // four heads: mixed 551 / 525, K8V4 504 / 490, K4V4 452 / 474, FP16 707 / 743;
+// heads of 256 gain the same.  Not so tiles whose lanes are not all busy (8 heads of 80
+// and 96, 3 of 96, mixed tags: 1.03-1.12 of the uncapped time), heads of 64 (1.00-1.04),
+// nor launches of up to about eight rounds of 24 waves (8 heads of 128: 1.01-1.07);
 // one and two heads alike.  Tiles of 4 loads, and tiles split over several
 // waves, measured level or slower with a cap, and so did workgroups whose waves
 // do not make 16 (five heads: 647 at 24 waves, 755 at 15).

@@ -607,7 +607,11 @@ GatherLaunch gather_launch(const pkv_model_t& m, int64_t units) {
 int gather_workgroups_per_cu(const HostPlan& hp) {
   const pkv_plan_info_t& info = hp.info;
   const int waves = hp.workgroup / 64;
-  if (gather_image(hp.model) == 0 || gather_loads(hp.model) <= 4 || 16 % waves != 0 || info.bytes_read == 0) return 0;
+  if (gather_image(hp.model) == 0 || gather_loads(hp.model) != 8 || hp.model.head_dim % 128 != 0 || 16 % waves != 0 ||
+      info.bytes_read == 0)
+    return 0;
+  // Rounds of the 24 waves a compute unit holds without a cap.
+  if (2 * info.num_units * waves <= 8 * 24 * int64_t(hp.cus)) return 0;
   const double ratio = double(info.bytes_written) / double(info.bytes_read);
   return ratio >= 0.4 && ratio <= 0.85 ? 16 / waves : 0;
 }
@@ -964,6 +968,18 @@ pkv_status_t pkv_internal_gather_launch(const pkv_model_t* model, int64_t units,
   const pkv::GatherLaunch g = pkv::gather_launch(*model, units);
   const int64_t v[7] = {g.kernel, g.loads, g.split, g.group, g.threads, g.wide, g.grid};
   memcpy(out, v, sizeof(v));
+  return PKV_OK;
+}
+
+// Internal test hook (not part of pkv.h): gather_workgroups_per_cu() on a device of 256 compute units.
+pkv_status_t pkv_internal_gather_cap(const pkv_model_t* model, const pkv_checkpoint_request_t* requests,
+                                     int32_t num_requests, int32_t* per_cu) {
+  if (!per_cu) return PKV_ERR_INVALID_ARGUMENT;
+  pkv::HostPlan hp;
+  pkv_status_t st = pkv::build_checkpoint_plan(model, requests, num_requests, &hp);
+  if (st != PKV_OK) return st;
+  hp.cus = 256;
+  *per_cu = pkv::gather_workgroups_per_cu(hp);
   return PKV_OK;
 }
 

@@ -308,3 +308,26 @@ def test_kernel_choice_and_grid_limits(model, units, kernel):
 def test_wide_blocks(model, wide):
     """Blocks on more than three pages, and layer slices of 4 GiB and more, look their pages up."""
     assert gather_launch(1, **model)["wide"] == wide
+
+
+@pytest.mark.parametrize("H,D,B,tokens,mix,per_cu", [
+    (8, 128, 32, 400000, (1, 2, 7, 0), 2), (4, 256, 16, 200000, (1, 2, 7, 0), 4),
+    (8, 128, 32, 400000, (0, 0, 0, 1), 0), (8, 128, 32, 400000, (1, 0, 0, 0), 0),  # outside 0.4-0.85 written per read
+    (8, 128, 32, 32 * 3072, (1, 2, 7, 0), 0), (8, 128, 32, 32 * 3073, (1, 2, 7, 0), 2),  # eight rounds, and more
+    (8, 80, 32, 400000, (1, 2, 7, 0), 0), (8, 96, 32, 400000, (1, 2, 7, 0), 0), (3, 96, 32, 400000, (1, 2, 7, 0), 0),
+    (8, 64, 64, 400000, (1, 2, 7, 0), 0), (8, 128, 28, 400000, (1, 2, 7, 0), 0), (8, 128, 16, 400000, (1, 2, 7, 0), 0),
+])
+def test_write_residency(H, D, B, tokens, mix, per_cu):
+    """The cap on resident workgroups: tiles of 8 full loads per lane, in launches deep enough to gain from it."""
+    fn = pb.load().pkv_internal_gather_cap
+    fn.argtypes = [ctypes.POINTER(pb.PkvModel), ctypes.POINTER(pb.PkvCheckpointRequest), ctypes.c_int32,
+                   ctypes.POINTER(ctypes.c_int32)]
+    fn.restype = ctypes.c_int32
+    nb = -(-tokens // B)
+    tags = np.random.default_rng(1).choice(4, size=nb, p=np.array(mix) / sum(mix)).astype(np.uint8)
+    table = np.arange(-(-tokens // 16), dtype=np.int32)
+    shape = wl.Shape(1, H, D, B, 16, len(table), 1e4, wl.OUT_BF16)
+    req = wl.Request(tokens, 0, 0, tags, np.zeros(nb, np.uint8), table, 0, 0, src_row0=0, src_page_table=table)
+    m, reqs, got = pb.make_model(shape), pb._CheckpointRequests([req]), ctypes.c_int32()
+    assert fn(ctypes.byref(m), reqs.array, reqs.count, ctypes.byref(got)) == 0
+    assert got.value == per_cu
