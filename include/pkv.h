@@ -239,12 +239,12 @@ pkv_status_t pkv_restore_from_host(const pkv_plan_t* plan, const void* host_payl
 /* The streamed restore of pkv_restore_from_host for callers that cannot
  * allocate device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc): no device checkpoint buffers are passed,
- * and the call allocates nothing.  It takes one of two ways, by the sizes of
- * the plan.  Most checkpoints are read in place over the host link by one
- * launch, as pkv_restore does with pinned memory.  Checkpoints that are mostly
- * FP16, in large runs, and host memory that a kernel cannot read in place
- * (buffers not 16- / 8-byte aligned, hipHostMallocNonCoherent) are staged
- * through a buffer of the library, a static device array of 64 MiB (payload
+ * and the call allocates nothing.  The checkpoint is read in place over the host
+ * link by one launch, as pkv_restore does with pinned memory, but by no more
+ * workgroups than fill the link (16 to 256; narrow rows on one-token pages take
+ * more), so that other streams find room beside it.  Host memory that a kernel
+ * cannot read in place (buffers not 16- / 8-byte aligned,
+ * hipHostMallocNonCoherent) is staged through a buffer of the library, a static device array of 64 MiB (payload
  * windows) + 4 MiB (scales) that each GPU the library runs on holds until the
  * process ends: for each layer and request in turn, on `hip_stream` only, the
  * request's layer scales are copied into the stage, then the request's reused

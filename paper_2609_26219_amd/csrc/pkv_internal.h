@@ -173,8 +173,8 @@ struct PullPiece {
   uint32_t scales;       // 1: of the scales
 };
 
-// The allocation-free streamed restore stages the checkpoint through a
-// static device buffer: payload windows in its first kStagePayloadBytes, one
+// The allocation-free streamed restore stages a checkpoint that it cannot read in
+// place through a static device buffer: payload windows in its first kStagePayloadBytes, one
 // request-layer's scales in the kStageScaleBytes after them.
 constexpr uint64_t kStagePayloadBytes = 64ull << 20;
 constexpr uint64_t kStageScaleBytes = 4ull << 20;
@@ -210,7 +210,6 @@ struct RequestCopies {
   uint64_t payload_offset, layer_bytes;  // bytes
   uint64_t scale_offset, layer_scales;   // binary16 elements
   bool scales_needed;                    // some reused block is quantized
-  uint64_t fp16_bytes;                   // bytes of the reused FP16 blocks of a layer
   int64_t unit0, unit1;                  // the request's units of a layer
   std::vector<CopyRange> ranges;         // merged payload copies, from the layer's start, ascending
   std::vector<StageWindow> windows;
@@ -301,6 +300,25 @@ struct RestoreLaunch {
   bool single;     // work items of one row
 };
 RestoreLaunch restore_launch(const HostPlan& hp, int64_t units, uintptr_t k_cache, uintptr_t v_cache);
+
+// Workgroups of a launch of `units` work items that reads the checkpoint over
+// the host link and takes its items in a loop (restore_link_kernel); 0: an
+// ordinary launch.  240 KB of reads in flight fill the link, so the workgroups are
+// as many, in sixteens, as make that with one item each; at least 64 where the
+// whole launch reads up to 8 MB, which it is over with soon.  8 layers of 4096
+// tokens, 8 heads of 128, us with 16 / 32 / 64 / 128 / 256 workgroups, an ordinary
+// launch, and copied into the stage in windows:
+//   K8V4  817 / 858 / 803 / 802 / 811, 820, 1016    FP16  2182 / 2162 / 2132 / 2145 / 2389, 2439, 2359
+// and two large layers (32768 tokens, 208 MB) of FP16 4364 / 4327 / 4265 / 4279 / 4756, 5079, 4475.
+// Over 90 restores of all shapes these counts take 0.983 of the ordinary launch's
+// time (4 over 1.05 of it; 350 to 500 KB in flight are 1.05-1.15), and products and
+// additions of another stream beside one of them 245 us with 16 FP16 workgroups,
+// 306 with 32, 483 / 731 / 763 with 64 / 128 / 256, 849 beside an ordinary launch and
+// 172 alone.  Items under 1 KB (narrow rows on one-token pages) need thousands of
+// workgroups, which an ordinary launch starts faster (8 layers, 64-byte items: 4.9
+// times slower with 2048 in a loop); it takes them while it can hold them, fewer
+// than 2^32 threads.
+uint32_t link_groups(const HostPlan& hp, int64_t units);
 
 // The same for the checkpoint write, 0 for no cap: staged tiles of 8 loads per
 // lane (32-token blocks at head_dim 128) run best with 16 waves, 128 KB of

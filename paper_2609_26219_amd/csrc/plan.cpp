@@ -302,6 +302,14 @@ RestoreLaunch restore_launch(const HostPlan& hp, int64_t units, uintptr_t k_cach
   return r;
 }
 
+uint32_t link_groups(const HostPlan& hp, int64_t units) {
+  const int64_t item = std::max<int64_t>(1, int64_t(hp.info.bytes_read) / hp.info.num_units);
+  if (item < 1024 && units * hp.workgroup < (int64_t(1) << 32)) return 0;
+  int64_t groups = std::min<int64_t>(16 * ceil_div(240000, 16 * item), 4096);
+  if (item * units <= 8000000) groups = std::max<int64_t>(groups, 64);
+  return uint32_t(std::min(groups, units));
+}
+
 // Threads of a restore workgroup: enough that each thread owns at most four
 // tokens of the largest unit (units stop at page ends), in whole waves, at
 // most kWorkgroup.  Rows of 8 heads x 128 keep 256; a one-head row of 128
@@ -471,7 +479,6 @@ pkv_status_t build_host_plan(const pkv_model_t* model, const pkv_request_t* requ
       rc.layer_scales = uint64_t(nb) * H * 4;
       rc.layer_bytes = 0;
       rc.scales_needed = false;
-      rc.fp16_bytes = 0;
       // Block offsets inside one layer (runs by tag, ascending blocks) and the
       // reused ones' ranges in that order, so that neighbours merge into one
       // copy; merging stays inside this request's layer, so copies never overlap.
@@ -486,7 +493,6 @@ pkv_status_t build_host_plan(const pkv_model_t* model, const pkv_request_t* requ
             reused.push_back(CopyRange{rc.layer_bytes, len});
             add_range(rc.ranges, 0, rc.layer_bytes, len, kHostGapBytes);
             rc.scales_needed |= tag != PKV_TAG_FP16;
-            rc.fp16_bytes += tag == PKV_TAG_FP16 ? len : 0;
           }
           rc.layer_bytes += len;
         }
@@ -806,6 +812,17 @@ pkv_status_t pkv_internal_restore_launch(const pkv_model_t* model, const pkv_req
                                                    uintptr_t(k_cache), uintptr_t(v_cache));
   const int64_t v[5] = {hp.per_cu, r.late, r.one_round, r.device, r.single};
   memcpy(out, v, sizeof(v));
+  return PKV_OK;
+}
+
+// Internal test hook (not part of pkv.h): link_groups() for all layers, or for `units` work items if not 0.
+pkv_status_t pkv_internal_link_groups(const pkv_model_t* model, const pkv_request_t* requests, int32_t num_requests,
+                                      int64_t units, int64_t* groups) {
+  if (!groups) return PKV_ERR_INVALID_ARGUMENT;
+  pkv::HostPlan hp;
+  pkv_status_t st = pkv::build_host_plan(model, requests, num_requests, &hp);
+  if (st != PKV_OK || hp.info.num_units == 0) return PKV_ERR_INVALID_ARGUMENT;
+  *groups = pkv::link_groups(hp, units ? units : hp.info.num_units);
   return PKV_OK;
 }
 

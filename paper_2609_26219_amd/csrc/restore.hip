@@ -65,7 +65,7 @@ constexpr int kMinWavesPerEU = 4;
 struct KernelArgs {
   const Unit* units;  // of one layer
   LayerItems items;
-  uint32_t grid;      // workgroups of the launch
+  uint32_t grid;      // work items of the launch
   int32_t threads;    // threads of a workgroup
   const double* tables;
   const uint8_t* payload;
@@ -530,22 +530,10 @@ __device__ __forceinline__ void restore_unit(const KernelArgs& a, const LayerUni
   }
 }
 
-// SINGLE: work items of one row (one-token pages) leave the loads of the
-// launch arguments and of the item to the compiler, which takes them piece by
-// piece.  One-go loads (load_scalars) are 3-8% slower there (2 heads of 128, 8 of
-// 128 and 1 of 256, all four mixes: 1.079, 1.045 and 1.079 of the time of an
-// earlier kernel, 1.018, 1.005 and 1.012 piece by piece); with several rows an
-// item, they are 0-7% faster.
+// One work item; s_tab is kMaxHeadDim doubles of LDS.  SINGLE: see restore_kernel.
 template <bool BF16, int STYLE, bool LATE, bool DEVICE, bool SINGLE>
-__global__ __launch_bounds__(kWorkgroup, kMinWavesPerEU) void restore_kernel(KernelArgs args) {
-  __shared__ __attribute__((aligned(16))) double s_tab[kMaxHeadDim];
-  const KernelArgs a = [&] {
-    if constexpr (SINGLE)
-      return args;
-    else
-      return launch_args<KernelArgs>();
-  }();
-  const uint32_t item = uint32_t(xcd_grouped(blockIdx.x, a.grid)), l = layer_of(a.items, item);
+__device__ __forceinline__ void restore_item(const KernelArgs& a, uint32_t item, double* s_tab) {
+  const uint32_t l = layer_of(a.items, item);
   const uint32_t layer = a.items.first + l;
   const Unit* const at = a.units + (item - l * a.items.count.d);
   const Unit unit = [&] {
@@ -600,6 +588,37 @@ __global__ __launch_bounds__(kWorkgroup, kMinWavesPerEU) void restore_kernel(Ker
     case 5: restore_unit<PKV_TAG_K8V4, true, STYLE, BF16, LATE, DEVICE>(a, u, s_tab, st, t0, head, j); break;
     case 6: restore_unit<PKV_TAG_K4V4, false, STYLE, BF16, LATE, DEVICE>(a, u, s_tab, st, t0, head, j); break;
     default: restore_unit<PKV_TAG_K4V4, true, STYLE, BF16, LATE, DEVICE>(a, u, s_tab, st, t0, head, j); break;
+  }
+}
+
+// SINGLE: work items of one row (one-token pages) leave the loads of the
+// launch arguments and of the item to the compiler, which takes them piece by
+// piece.  One-go loads (load_scalars) are 3-8% slower there (2 heads of 128, 8 of
+// 128 and 1 of 256, all four mixes: 1.079, 1.045 and 1.079 of the time of an
+// earlier kernel, 1.018, 1.005 and 1.012 piece by piece); with several rows an
+// item, they are 0-7% faster.
+template <bool BF16, int STYLE, bool LATE, bool DEVICE, bool SINGLE>
+__global__ __launch_bounds__(kWorkgroup, kMinWavesPerEU) void restore_kernel(KernelArgs args) {
+  __shared__ __attribute__((aligned(16))) double s_tab[kMaxHeadDim];
+  const KernelArgs a = [&] {
+    if constexpr (SINGLE)
+      return args;
+    else
+      return launch_args<KernelArgs>();
+  }();
+  restore_item<BF16, STYLE, LATE, DEVICE, SINGLE>(a, uint32_t(xcd_grouped(blockIdx.x, a.grid)), s_tab);
+}
+
+// The restore of a checkpoint in host memory, read over the host link: a few
+// workgroups (link_groups) take the items in turn, so that the compute units are
+// left to other streams, where workgroups enough to fill the HBM would wait for
+// the link on all of them.  Bound by the link.
+template <bool BF16, int STYLE>
+__global__ __launch_bounds__(kWorkgroup, kMinWavesPerEU) void restore_link_kernel(KernelArgs a) {
+  __shared__ __attribute__((aligned(16))) double s_tab[kMaxHeadDim];
+  for (uint32_t item = blockIdx.x; item < a.grid; item += gridDim.x) {
+    restore_item<BF16, STYLE, true, false, true>(a, item, s_tab);
+    __syncthreads();  // the table's readers are done (every thread returns from the item)
   }
 }
 
@@ -786,10 +805,11 @@ pkv_status_t check_restore_buffers(const pkv_plan* plan, const void* payload, ui
 std::atomic<int> g_restore_order{0};
 
 // Enqueue the restore kernel over units [u0, u1) of layers [layer0, layer1),
-// those whose K rows start in payload bytes [win_lo, win_hi).
+// those whose K rows start in payload bytes [win_lo, win_hi); `link`: the
+// checkpoint is in host memory.
 pkv_status_t launch_restore(const pkv_plan* plan, const void* payload, const void* scales, void* k_cache,
                             void* v_cache, int64_t layer0, int64_t layer1, int64_t u0, int64_t u1, hipStream_t stream,
-                            uint64_t win_lo = 0, uint64_t win_hi = ~uint64_t(0)) {
+                            uint64_t win_lo = 0, uint64_t win_hi = ~uint64_t(0), bool link = false) {
   const pkv_model_t& m = plan->host.model;
   const int64_t n = (layer1 - layer0) * (u1 - u0);
   KernelArgs a;
@@ -836,7 +856,15 @@ pkv_status_t launch_restore(const pkv_plan* plan, const void* payload, const voi
   const auto kernel = bf16 ? half ? pick(std::true_type(), Half()) : pick(std::true_type(), Pairs())
                            : half ? pick(std::false_type(), Half()) : pick(std::false_type(), Pairs());
   const uint32_t lds = launch.one_round ? plan->one_round_lds : plan->cap_lds;
-  hipLaunchKernelGGL(kernel, dim3(uint32_t(n)), dim3(plan->host.workgroup), lds, stream, a);
+  const uint32_t groups = link ? link_groups(plan->host, n) : 0;
+  if (groups) {
+    const auto loop = bf16 ? half ? restore_link_kernel<true, PKV_ROPE_HALF> : restore_link_kernel<true, PKV_ROPE_INTERLEAVED>
+                           : half ? restore_link_kernel<false, PKV_ROPE_HALF>
+                                  : restore_link_kernel<false, PKV_ROPE_INTERLEAVED>;
+    hipLaunchKernelGGL(loop, dim3(groups), dim3(plan->host.workgroup), 0, stream, a);
+  } else {
+    hipLaunchKernelGGL(kernel, dim3(uint32_t(n)), dim3(plan->host.workgroup), lds, stream, a);
+  }
   return hipGetLastError() == hipSuccess ? PKV_OK : PKV_ERR_DEVICE;
 }
 
@@ -933,25 +961,6 @@ __global__ __launch_bounds__(kWorkgroup) void pull_kernel(PullArgs a) {
 // many bytes, so that the launches and the event between them are a few
 // percent of a transfer and the last restore, which nothing hides, is short.
 constexpr uint64_t kPullGroupBytes = 16ull << 20;
-
-// Whether the allocation-free restore copies windows of the checkpoint into the
-// stage, instead of reading it over the host link in one launch.  A window
-// costs about 50 us beyond its transfer (its copies' setup, the wait for its
-// restore), so reading in place is faster up to large windows: 1271 us
-// against 2261 for 4K tokens of 2 heads and 40 layers (70 MB), 190 against 1111
-// for 512 tokens, 7.7 ms against 9.3 for 8K tokens of 8 heads and 32 layers
-// (430 MB).  Only FP16 tiles are read in place more slowly than a copy moves
-// them, 47-51 GB/s against 57: with three quarters of the bytes in them,
-// windows above 16 MiB win (28 MB of FP16 each: 17.5 ms against 19.2).
-bool stage_windows(const HostPlan& h) {
-  uint64_t bytes = 0, fp16 = 0, windows = 0;
-  for (const RequestCopies& rc : h.copies) {
-    for (const CopyRange& c : rc.ranges) bytes += c.len;
-    fp16 += rc.fp16_bytes;
-    windows += rc.windows.size();
-  }
-  return 4 * fp16 >= 3 * bytes && bytes >= windows * (16ull << 20);
-}
 
 }  // namespace
 }  // namespace pkv
@@ -1155,9 +1164,10 @@ pkv_status_t pkv_restore_from_host_noalloc(const pkv_plan_t* plan, const void* h
   if ((st = pkv::device_resident(plan, k_cache)) != PKV_OK || (st = pkv::device_resident(plan, v_cache)) != PKV_OK)
     return st;
   const bool aligned = reinterpret_cast<uintptr_t>(p_mapped) % 16 == 0 && reinterpret_cast<uintptr_t>(s_mapped) % 8 == 0;
-  if (p_mapped && s_mapped && aligned && !pkv::stage_windows(h))
+  if (p_mapped && s_mapped && aligned)
     return pkv::launch_restore(plan, p_mapped, s_mapped, k_cache, v_cache, 0, h.model.num_layers, 0, h.layer_units,
-                               static_cast<hipStream_t>(hip_stream));
+                               static_cast<hipStream_t>(hip_stream), 0, ~uint64_t(0), true);
+  // Host memory that a kernel cannot read in place goes through the stage.
   uint8_t* stage = nullptr;
   if ((st = pkv::stage_address(dev, &stage)) != PKV_OK) return st;
   uint8_t* stage_scales = stage + pkv::kStagePayloadBytes;

@@ -106,3 +106,29 @@ def test_one_round_for_whole_sectors(dim):
 def test_residency_of_narrow_rows(args, per_cu):
     """Destination rows start twelve slots into a 16-token page, so a block's units are 4, 16 and 12 tokens."""
     assert restore_launch(make(**args))["per_cu"] == per_cu
+
+
+def link_groups(case, units=0):
+    fn = pb.load().pkv_internal_link_groups
+    fn.argtypes = [ctypes.POINTER(pb.PkvModel), ctypes.POINTER(pb.PkvRequest), ctypes.c_int32, ctypes.c_int64,
+                   ctypes.POINTER(ctypes.c_int64)]
+    fn.restype = ctypes.c_int32
+    m, reqs, out = pb.make_model(case.shape), pb._Requests(case.requests), ctypes.c_int64()
+    assert fn(ctypes.byref(m), reqs.array, reqs.count, units, ctypes.byref(out)) == 0
+    return out.value
+
+
+@pytest.mark.parametrize("args,groups", [
+    (dict(H=8, D=128, mix=K8V4, L=8), 16), (dict(H=32, D=128, mix=(1, 0, 0, 0), L=8), 16), (dict(H=2, D=128, L=8), 48),
+    (dict(H=1, D=128, mix=K4V4, L=32), 176), (dict(H=8, D=128, P=1, mix=K8V4, L=4), 160), (dict(H=2, D=128, P=1), 0),
+    (dict(H=8, D=128, mix=K8V4), 64), (dict(H=8, D=128, tokens=100), 7),  # 6 MB in all; never more than work items
+])
+def test_link_groups(args, groups):
+    """Workgroups of a restore over the host link: as many as keep some 256 KB of reads in flight; 0 is one per item."""
+    assert link_groups(make(**args)) == groups
+
+
+def test_link_launches_of_any_size():
+    """Narrow one-token pages take an ordinary launch while its threads are fewer than 2^32, a loop beyond."""
+    case = make(1, 16, B=2, P=1, tokens=512)
+    assert link_groups(case, (1 << 26) - 1) == 0 and link_groups(case, 1 << 26) == 4096

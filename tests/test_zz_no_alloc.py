@@ -1,8 +1,12 @@
 """The allocation-free streamed restore (pkv_restore_from_host_noalloc)
 against pkv_restore_from_host, through the C ABI: identical caches, bit for
 bit, on two calls in a row (the second with a smaller plan), and the oracle's
-restore on both.  The first case's request-layers span more than the 64 MiB
-stage, so they run in several payload windows."""
+restore on both.  Host buffers that a kernel can address in whole loads are
+read in place by one looping launch; buffers four bytes into an allocation
+cannot be, so they go through the stage, the first case's request-layers, which
+span more than its 64 MiB, in several payload windows."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -39,7 +43,15 @@ def _big():
                                   repair_frac=0.15, out_dtype=wl.OUT_BF16, theta=5e5, outlier_pairs=1))
 
 
-def _both(case, torch):
+def _pinned(torch, array, offset):
+    """The bytes of a host array, `offset` bytes into a pinned allocation: (tensor, address)."""
+    raw = array.view(np.uint8)
+    t = torch.zeros(raw.size + 64, dtype=torch.uint8).pin_memory()
+    t[offset:offset + raw.size] = torch.from_numpy(raw)
+    return t, t.data_ptr() + offset
+
+
+def _both(case, torch, offset):
     from paper_2609_26219_amd.device import DeviceRestore
 
     ckpt = oracle_checkpoint(case)
@@ -51,8 +63,9 @@ def _both(case, torch):
     torch.cuda.synchronize()
     ref = dr.host_caches()
     dr.prefill()
-    nb = lambda t: t.numel() * t.element_size()
-    st = pb.pkv_restore_from_host_noalloc_status(dr.plan, hp.data_ptr(), nb(hp), hs.data_ptr(), nb(hs),
+    (keep_p, p), (keep_s, s) = _pinned(torch, ckpt[0], offset), _pinned(torch, ckpt[1], offset)
+    assert p % 16 == offset and s % 8 == offset % 8
+    st = pb.pkv_restore_from_host_noalloc_status(dr.plan, p, ckpt[0].nbytes, s, ckpt[1].nbytes,
                                                  dr.k_cache.data_ptr(), dr.v_cache.data_ptr(),
                                                  pb.cache_nbytes(dr.k_cache, dr.v_cache),
                                                  torch.cuda.current_stream().cuda_stream)
@@ -63,13 +76,44 @@ def _both(case, torch):
     stats = check_full(dr, ckpt)
     log(f"  {case.name}: identical to pkv_restore_from_host; oracle: {stats.n} elements, "
         f"{stats.n_near_tie} near-tie neighbours, 0 wrong")
-    return dr, hp, hs
 
 
-def test_noalloc_matches_streamed_restore_two_calls(torch):
-    log("[gpu] allocation-free streamed restore: a two-window case, then tiny")
-    _both(_big(), torch)
-    _both(wl.make_case("tiny"), torch)
+@pytest.mark.parametrize("offset", [0, 4], ids=["in_place", "staged"])
+def test_noalloc_matches_streamed_restore_two_calls(offset, torch):
+    from test_stage_schedule import stage_schedule
+
+    big, tiny = _big(), wl.make_case("tiny")
+    steps = stage_schedule(big.shape, big.requests)[0]
+    assert len(steps) == 2 * (2 + 1)  # two layers: two windows of the long request, one of the short
+    log("[gpu] allocation-free streamed restore, %s: a case of two windows, then tiny" % ("staged" if offset else "in place"))
+    _both(big, torch, offset)
+    _both(tiny, torch, offset)
+
+
+def _groups(case):
+    fn = pb.load().pkv_internal_link_groups
+    fn.argtypes = [ctypes.POINTER(pb.PkvModel), ctypes.POINTER(pb.PkvRequest), ctypes.c_int32, ctypes.c_int64,
+                   ctypes.POINTER(ctypes.c_int64)]
+    m, reqs, out = pb.make_model(case.shape), pb._Requests(case.requests), ctypes.c_int64()
+    assert fn(ctypes.byref(m), reqs.array, reqs.count, 0, ctypes.byref(out)) == 0
+    return out.value
+
+
+@pytest.mark.parametrize("params,groups", [
+    # 16 and 64 workgroups and hundreds of items: requests with and without rotation follow each other in one workgroup
+    (dict(L=4, H=16, D=128, B=32, P=16, n_tokens=(600, 400, 33), deltas=(-3, 0, 70), rho0s=(7, 11, 90)), 16),
+    (dict(L=3, H=3, D=96, B=32, P=16, n_tokens=(700, 390), deltas=(5, 0), rho0s=(7, 11)), 64),
+    (dict(L=2, H=2, D=128, B=16, P=1, n_tokens=(40, 3), deltas=(5, 0), rho0s=(7, 1)), 0),  # an ordinary launch
+    (dict(L=1, H=32, D=128, B=16, P=16, n_tokens=(20,), deltas=(5,), rho0s=(0,)), 5),  # fewer items than workgroups
+])
+@pytest.mark.parametrize("style", [wl.ROPE_HALF, wl.ROPE_INTERLEAVED], ids=["half", "interleaved"])
+@pytest.mark.parametrize("dtype", [wl.OUT_BF16, wl.OUT_FP16], ids=["bf16", "fp16"])
+def test_noalloc_looping_launch(params, groups, style, dtype, torch):
+    import dataclasses
+    case = wl.make_custom(34, tag_set=(0, 1, 2, 3), mix=(1, 1, 1, 1), repair_frac=0.0, out_dtype=dtype, **params)
+    case.shape = dataclasses.replace(case.shape, rope_style=style)
+    assert _groups(case) == groups
+    _both(case, torch, 0)
 
 
 def test_noalloc_rejects_pageable_and_oversized(torch):
