@@ -417,7 +417,7 @@ using u32x4 = __attribute__((ext_vector_type(4))) unsigned;
 // of the table), then the NL rows through 64-bit addresses: one table latency
 // in front of a tile instead of one in front of every row.  Bound by the
 // memory streams: 64-token blocks on 16-token pages (32 layers x 8150 tokens, 8
-// heads x 128, fp16, 1.54 GB) take 280 us, 5.5 TB/s, against 467 us when each
+// heads x 128, fp16, 1.54 GB) take 270 us, 5.7 TB/s, against 467 us when each
 // row waited for its own page.
 template <int NL, bool WIDE>
 __device__ __forceinline__ void load_tile(const GatherArgs& a, const TileHdr& h, int t_base, int r, int c,

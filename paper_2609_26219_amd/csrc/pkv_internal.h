@@ -100,8 +100,9 @@ constexpr uint64_t unit_scale_off(const Unit& u, uint32_t layer) { return u.scal
 // before anything that uses them (the empty asm).  A workgroup's first load of
 // data waits for its launch arguments and then for its work item.  Left alone
 // the compiler loads both piece by piece, each where it is first used, seven
-// scalar loads one behind the other; in one go each, the restore of one layer
-// (690 workgroups) takes 10.4 us against 10.7.
+// scalar loads one behind the other; in one go each, units of several rows are
+// restored up to 7% faster (one layer, 690 workgroups, launches back to back: 8.0
+// us against 8.0-8.1).
 typedef uint32_t ScalarLine __attribute__((ext_vector_type(16), aligned(4)));
 template <typename T>
 __device__ __forceinline__ T load_scalars(const __attribute__((address_space(4))) void* p) {
@@ -287,8 +288,8 @@ int restore_workgroups_per_cu(const HostPlan& hp);
 // Launches that fit on the device at this many 256-thread workgroups to a
 // compute unit are all resident at once, whatever cap the plan has for longer
 // ones: one layer of the 8B-shaped restore (690 workgroups on 256 compute
-// units) takes 10.5 us at three and 11.1 at two, which leaves 178 for a second
-// round.  At four to a compute unit 1012 workgroups were slower than at two
+// units, separate caches, launches back to back) takes 8.0 us at three and 8.9 at
+// two, which leaves 178 for a second round.  At four to a compute unit 1012 workgroups were slower than at two
 // (14.3 against 13.7 us).
 constexpr int kOneRound = 3;
 

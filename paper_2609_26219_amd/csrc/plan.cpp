@@ -246,7 +246,8 @@ namespace {
 
 // Rows stored at device scope.  The write stream bounds the kernel, and the
 // 8B-shaped 32-layer restore takes 847 us that way against 886 (5.34 GB, 6.3
-// against 6.0 TB/s), one layer of it 10.5 against 11.3.  It needs
+// against 6.0 TB/s), one layer of 690 units, launches back to back, 8.0 against 9.6
+// (8.1 against 9.5 on paired pages).  It needs
 //   whole 64-byte sectors, by the rows and by the caches' addresses: parts of
 //     sectors are written through one by one (8 heads of 96, 16 layers: 1100 us
 //     against 550), where the L2 puts them together;
@@ -370,7 +371,10 @@ StageStep stage_step(const RequestCopies& rc, int64_t l, size_t window) {
 // streams move 57 GB/s and the kernel 54, so the kernel is ahead while copies
 // are small.  us by kernel / by DMA, 8 heads and 32 layers: 300 tokens 383 /
 // 1354, 1024 tokens (1 MB a copy) 1157 / 1540, 3000 tokens (2.6 MB) 3330 / 3617,
-// 8192 tokens (4.7 MB) 8336 / 8239; two heads (1.2 MB) 2258 / 2977.
+// 8192 tokens (4.7 MB) 8336 / 8239; two heads (1.2 MB) 2258 / 2977.  The average
+// counts payload and scale copies alike: over 190 streamed restores, 40 of them
+// with one payload copy of 0.5-8 MB and one scale copy a layer, the choice is
+// never behind DMA alone (at most 1.002 of its time).
 bool pulls(const HostPlan& h) {
   const uint64_t copies = uint64_t(h.info.host_copies);
   return h.info.host_copy_bytes < copies * (4ull << 20) &&

@@ -19,9 +19,10 @@
 // unit's one page comes with its work item, so no workgroup-wide staging or
 // barrier is needed except for the per-request cos/sin table (staged before
 // the payload loads or after them: the two start orders of Stage).  An LDS claim caps
-// the workgroups sharing a compute unit at two to four, chosen per plan from
-// its read:write byte ratio, its unit size, whether its keys rotate and the
-// cache layout (restore_workgroups_per_cu).
+// the workgroups sharing a compute unit, at two to four of 256 threads and 6 to
+// 16 waves of smaller ones, chosen per plan from its read:write byte ratio, its
+// unit size, whether its keys rotate and the cache layout
+// (restore_workgroups_per_cu); a launch that fits in one round takes kOneRound.
 //
 // Cache layouts.  With separate caches a page's K slots and V slots sit in
 // two buffers; with paired pages they are one contiguous run, K then V.
@@ -36,7 +37,7 @@
 // the hardware round-to-nearest-even conversions.
 //
 // Memory behaviour (8B-shaped 32K-token workload, measured): the kernel
-// moves 1.0025x the algorithmic bytes; the write-heavy mixed stream bounds it,
+// moves 1.0023x the algorithmic bytes; the write-heavy mixed stream bounds it,
 // and paired pages let the memory system stream the writes faster.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -58,8 +59,8 @@ namespace pkv {
 namespace {
 
 // Register budget for four waves per SIMD, so that the (cos, sin) pairs and
-// four tokens' payload of a thread stay in registers (the residency cap then
-// keeps two to four).
+// four tokens' payload of a thread stay in registers (the residency cap keeps
+// to that or less).
 constexpr int kMinWavesPerEU = 4;
 
 struct KernelArgs {
@@ -915,8 +916,9 @@ bool pinned_host(const void* p, const void** mapped) {
 // Copies pieces of the checkpoint from host memory to the device, over the
 // link: kPullGroups workgroups take the pieces of a launch's layers in turn.
 // Few workgroups, so that the restore of the layers before, and whatever else
-// runs, finds room beside them: 16 of 256 threads keep 256 KB of reads in
-// flight, which fills the link (54 GB/s; 32, 64 and 128 are no faster).
+// runs, finds room beside them: 16 of 256 threads with four 16-byte loads each
+// keep 256 KB of reads in flight, which fills the link (54 GB/s; 32, 64 and 128
+// are no faster).  A launch of fewer pieces than workgroups keeps less in flight.
 struct PullArgs {
   const PullPiece* pieces;  // of one layer
   LayerItems items;

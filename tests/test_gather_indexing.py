@@ -4,7 +4,10 @@ Replays, for every thread of every workgroup of the host-built work list, the
 address formulas of ``gather.hip`` and checks: every cache read is a suffix
 row of a request (in bounds); every byte of each request's checkpoint range
 and every scale element is written exactly once; nothing else is written.
-Keep the constants in step with the kernel."""
+The row and channel of a lane's loads are the same in the file's three kernels;
+which wave has which tile is replayed as the general kernel deals them
+(``emulate``), the tile kernel and the split kernel, whose launches the library
+reports.  Keep the constants in step with the kernels."""
 import ctypes
 
 import numpy as np
@@ -42,7 +45,7 @@ def checkpoint_units(shape, requests):
 
 
 def emulate(case):
-    """Workgroup 2u + which encodes the K (0) or V (1) tile of unit u; wave w
+    """As the general kernel deals tiles: workgroup 2u + which encodes the K (0) or V (1) tile of unit u; wave w
     of it encodes heads w, w + waves, ...; lane l holds channels
     [8c, 8c + 8) of row r of every load (r = l // (D/8), c = l % (D/8))."""
     s = case.src_shape
@@ -163,10 +166,10 @@ def _paired(case):
                                    tag_set=(0, 1, 2, 3), mix=(1, 1, 1, 1))),
     lambda: _paired(wl.make_custom(5, L=2, H=8, D=128, B=32, P=16, n_tokens=(75,), deltas=(-3,), rho0s=(7,),
                                    tag_set=(0, 1, 2, 3), mix=(1, 1, 1, 1))),
-    # general kernel: blocks over more than three pages
+    # blocks on more than three pages
     lambda: _paired(wl.make_custom(9, L=1, H=4, D=64, B=32, P=8, n_tokens=(77,), deltas=(1,), rho0s=(6,),
                                    tag_set=(0, 1, 2, 3), mix=(1, 1, 1, 1))),
-], ids=["tiny", "h8_b4_two_requests", "h8_d128", "general_kernel"])
+], ids=["tiny", "h8_b4_two_requests", "h8_d128", "many_pages"])
 def test_gather_addresses_paired_pages(maker):
     emulate(maker())
 
@@ -181,14 +184,13 @@ def test_gather_addresses_paired_pages(maker):
                            tag_set=(0, 1, 2, 3), mix=(1, 1, 1, 1)),
     lambda: wl.make_custom(8, L=1, H=20, D=16, B=8, P=8, n_tokens=(21,), deltas=(1,), rho0s=(3,),
                            tag_set=(0, 1, 2, 3), mix=(1, 1, 1, 1)),
-    # 70B-shaped blocks: 64 tokens over 32-token pages, 16 loads per lane in 8-wave workgroups
+    # 70B-shaped blocks: 64 tokens over 32-token pages, 16 loads per lane (the split kernel's; the same pages)
     lambda: wl.make_custom(13, L=1, H=8, D=128, B=64, P=32, n_tokens=(150, 64), deltas=(4096, 0), rho0s=(31, 96),
                            tag_set=(0, 1, 2, 3), mix=(1, 1, 1, 1)),
 ], ids=["tiny", "h8_b4_two_requests", "h4_d64_b64", "h8_d128", "h20_heads_loop", "h8_d128_b64_p32"])
 def test_tile_kernel_tiles_and_pages(maker):
-    """Tile kernel (blocks of at most 2P + 1 tokens, at most 16 loads per lane):
-    wave w of workgroup b encodes tile b * waves + w of the (unit, K|V, head)
-    order, so a grid of ceil(tiles / waves) workgroups encodes every tile
+    """Tile kernel on blocks of at most 2P + 1 tokens: wave w of workgroup b
+    encodes tile b * waves + w of the (unit, K|V, head) order, so a grid of ceil(tiles / waves) workgroups encodes every tile
     exactly once; the three source pages carried in each unit give every
     valid row's page, and rows past n_valid read the block's first row."""
     case = maker()
