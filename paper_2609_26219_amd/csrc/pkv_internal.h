@@ -387,7 +387,8 @@ struct GatherLaunch {
 };
 GatherLaunch gather_launch(const pkv_model_t& m, int64_t units);
 
-// The plan object behind pkv_plan_t (host metadata + one device allocation).
+// The plan object behind pkv_plan_t: host metadata and one piece of device memory (PlanMemory, or an allocation of its
+// own where it is larger).
 }  // namespace pkv
 struct pkv_plan {
   pkv::HostPlan host;  // units, tables, page tables and pieces are dropped after upload
