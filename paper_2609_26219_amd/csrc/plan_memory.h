@@ -23,8 +23,8 @@ namespace pkv {
 // follows its release, so a plan that is freed while a launch still reads it
 // stays readable, as with hipFree.  That synchronisation is made when no piece
 // is left and the released ones add up to half a slab, so a plan that is kept
-// holds back its own bytes and not its slab.  Slabs behind the newest are freed
-// with their last plan, and all are when no plan of the device is left.
+// holds back its own bytes and not its slab.  A slab but the newest is freed
+// with its last plan, and all are when no plan of the device is left.
 //
 // No lock is held while memory is freed or copied, which may wait for the device.
 template <typename Hip>
